@@ -166,64 +166,101 @@ __device__ inline bool in_sorted(const int32_t *col, int64_t lo, int64_t hi, int
     return f;
 }
 
-// induced adjacency code of one sample (bit q for the q-th pair i < j) and its
-// class through the lookup table; 0xffffffff for both when a vertex id is invalid.
-// Every vertex's row bounds are read once; a pair searches the shorter row.
-__device__ inline uint32_t classify_row(const GraphView &g, int k, const int32_t *row, const uint16_t *lut,
-                                        uint32_t *code_out)
+// The induced adjacency code of a sample (bit q for the q-th pair i < j) by a
+// group of GL lanes (GL a power of two, at least its k(k-1)/2 pairs): lane q of
+// the group reads the two row bounds of pair q and searches the shorter row, and
+// the group's share of the wave's ballot is the code. The searches are chains of
+// dependent random loads, so what bounds a small call is one lane's chain: a lane
+// that searched all the pairs of a sample in turn took 107 us for 1000 samples at
+// k = 6, a lane per pair takes 10 us (100 000 at k = 7: 212 -> 117 us; 5*10^6 at
+// k = 8: 5.5 -> 4.2 ms). Every lane of the wave calls it; lanes of a sample with
+// an invalid vertex id get 0xffffffff.
+template <int GL>
+__device__ inline uint32_t group_code(const GraphView &g, int k, const int32_t *row, bool active)
 {
-    int32_t vs[SCC_KMAX];
-    bool ok = true;
+    const int lane = lane_id(), q = lane & (GL - 1);
+    // pair q = (i, j), i < j, pairs numbered row by row
+    int i = 0, first = 0;
 #pragma unroll
-    for (int i = 0; i < SCC_KMAX; i++) {
-        vs[i] = i < k ? row[i] : 0;
-        ok = ok && (i >= k || (vs[i] >= 0 && vs[i] < g.n));
+    for (int r = 1; r < SCC_KMAX; r++) {
+        const int start = first + (k - r);   // first pair of row i + 1
+        if (r == i + 1 && r < k - 1 && q >= start) { i = r; first = start; }
     }
-    if (!ok) {
-        *code_out = 0xffffffffu;
-        return 0xffffffffu;
-    }
-    int64_t rb[SCC_KMAX], re[SCC_KMAX];
-#pragma unroll
-    for (int i = 0; i < SCC_KMAX; i++) {
-        rb[i] = i < k ? g.row_ptr[vs[i]] : 0;
-        re[i] = i < k ? g.row_ptr[vs[i] + 1] : 0;
-    }
-    // the pairs unrolled over SCC_KMAX vertices, so that the arrays stay in registers
-    uint32_t code = 0;
-    int q = 0;
-#pragma unroll
-    for (int i = 0; i < SCC_KMAX; i++)
-#pragma unroll
-        for (int j = i + 1; j < SCC_KMAX; j++) {
-            if (j >= k) continue;
-            const bool in_j = re[j] - rb[j] < re[i] - rb[i];
-            if (in_j ? in_sorted(g.col_idx, rb[j], re[j], vs[i]) : in_sorted(g.col_idx, rb[i], re[i], vs[j]))
-                code |= 1u << q;
-            q++;
+    const bool mine = active && q < k * (k - 1) / 2;
+    const int j = i + 1 + (q - first);
+    bool ok = true, hit = false;
+    if (mine) {
+        const int32_t a = row[i], b = row[j];
+        ok = a >= 0 && a < g.n && b >= 0 && b < g.n;
+        if (ok) {
+            const int64_t ra = g.row_ptr[a], ea = g.row_ptr[a + 1], rb = g.row_ptr[b], eb = g.row_ptr[b + 1];
+            const bool in_b = eb - rb < ea - ra;
+            hit = in_sorted(g.col_idx, in_b ? rb : ra, in_b ? eb : ea, in_b ? a : b);
         }
-    *code_out = code;
+    } else if (active && k == 1 && q == 0) {
+        ok = row[0] >= 0 && row[0] < g.n;
+    }
+    const uint64_t gmask = GL >= 64 ? ~0ull : (1ull << GL) - 1ull;
+    const int base = lane & ~(GL - 1);
+    const uint32_t code = (uint32_t)((__ballot(hit) >> base) & gmask);
+    return (__ballot(!ok) >> base) & gmask ? 0xffffffffu : code;
+}
+
+// its class through the lookup table (0xffffffff: none)
+__device__ inline uint32_t class_of(const uint16_t *lut, uint32_t code)
+{
+    if (code == 0xffffffffu) return 0xffffffffu;
     const uint16_t c = lut[code];
     return c == 0xffff ? 0xffffffffu : (uint32_t)c;
 }
 
-__global__ void k_classify(GraphView g, int k, const int32_t *verts, int64_t n, const uint16_t *lut,
-                           uint32_t *out_code, uint32_t *out_class)
+// Adds one to hist[c] for every lane with `add`: lanes that count in the same
+// word are added by one atomic (most samples of a round fall in a few classes,
+// and one atomic per sample serialised on their words).
+__device__ inline void wave_hist_add(unsigned long long *hist, uint32_t c, bool add)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    uint32_t code;
-    const uint32_t c = classify_row(g, k, verts + s * k, lut, &code);
-    if (out_code) out_code[s] = code;
-    out_class[s] = c;
+    const uint64_t word = add ? (uint64_t)(hist + c) : 0ull;
+    uint64_t todo = __ballot(add);
+    while (todo) {
+        const int lead = __ffsll((long long)todo) - 1;
+        const uint64_t same = __ballot(add && word == readlane64(word, lead));
+        if (lane_id() == lead) atomicAdd(hist + c, (unsigned long long)__popcll(same));
+        todo &= ~same;
+    }
 }
 
-// classes of the rows of a serving step (requests without a class output are skipped)
-__global__ void k_serve_classify(const ServeClassArgs *args, const ServeChunk *ch, const int64_t *cend, int nch,
-                                 int64_t total)
+template <int GL>
+__global__ void __launch_bounds__(256) k_classify(GraphView g, int k, const int32_t *verts, int64_t n,
+                                                  const uint16_t *lut, uint32_t *out_code, uint32_t *out_class)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= total) return;
+    const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / GL;
+    const uint32_t code = group_code<GL>(g, k, verts + s * k, s < n);
+    if (s < n && (threadIdx.x & (GL - 1)) == 0) {
+        if (out_code) out_code[s] = code;
+        out_class[s] = class_of(lut, code);
+    }
+}
+
+// the smallest group that holds the pairs of k vertices (28 at k = 8)
+void launch_classify(const GraphView &g, int k, const int32_t *verts, int64_t n, const uint16_t *lut, uint32_t *code,
+                     uint32_t *cls, hipStream_t st)
+{
+    auto blocks = [&](int gl) { return dim3((unsigned)((n * gl + 255) / 256)); };
+    if (k <= 4)
+        hipLaunchKernelGGL(k_classify<8>, blocks(8), dim3(256), 0, st, g, k, verts, n, lut, code, cls);
+    else if (k <= 6)
+        hipLaunchKernelGGL(k_classify<16>, blocks(16), dim3(256), 0, st, g, k, verts, n, lut, code, cls);
+    else
+        hipLaunchKernelGGL(k_classify<32>, blocks(32), dim3(256), 0, st, g, k, verts, n, lut, code, cls);
+}
+
+// classes of the rows of a serving step (requests without a class output are
+// skipped), 32 lanes a row; tables of any k in one step
+constexpr int SERVE_GL = 32;
+__global__ void __launch_bounds__(256) k_serve_classify(const ServeClassArgs *args, const ServeChunk *ch,
+                                                        const int64_t *cend, int nch, int64_t total)
+{
+    const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / SERVE_GL;
     int lo = 0, hi = nch - 1;
     while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -231,20 +268,40 @@ __global__ void k_serve_classify(const ServeClassArgs *args, const ServeChunk *c
     }
     const ServeChunk C = ch[lo];
     const ServeClassArgs &A = args[C.arg];
-    if (!A.cls) return;
-    const int64_t r = C.off + (s - (cend[lo] - C.count));
-    uint32_t code;
-    const uint32_t c = classify_row(A.g, A.k, A.verts + r * A.k, A.lut, &code);
-    A.cls[r] = c;
-    if (A.hist && c < A.nclass) atomicAdd(&A.hist[c], 1ull);
+    const bool act = s < total && A.cls;
+    const int64_t r = act ? C.off + (s - (cend[lo] - C.count)) : 0;
+    const uint32_t code = group_code<SERVE_GL>(A.g, A.k, A.verts + r * A.k, act);
+    const bool first = act && (threadIdx.x & (SERVE_GL - 1)) == 0;
+    uint32_t c = 0xffffffffu;
+    if (first) {
+        c = class_of(A.lut, code);
+        A.cls[r] = c;
+    }
+    wave_hist_add(A.hist, c, first && A.hist && c < A.nclass);
 }
 
-__global__ void k_hist(const uint32_t *cls, int64_t n, uint32_t nclass, unsigned long long *hist)
+// Class histogram of n samples: each block counts its share in LDS (nclass
+// words, 44 KB at k = 8) and adds the classes it met. One global atomic per
+// sample serialised on the few common classes (100 000 samples at k = 7: 0.4-1.2
+// ms a round), one per wave and class left the rounds of many classes at 0.1-0.2
+// ms; this takes 6 us.
+constexpr int HIST_T = 1024, HIST_PER = 4;
+__global__ void __launch_bounds__(HIST_T) k_hist(const uint32_t *cls, int64_t n, uint32_t nclass,
+                                                 unsigned long long *hist)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const uint32_t c = cls[s];
-    if (c < nclass) atomicAdd(&hist[c], 1ull);
+    extern __shared__ uint32_t cnt[];
+    for (uint32_t i = threadIdx.x; i < nclass; i += HIST_T) cnt[i] = 0;
+    __syncthreads();
+    const int64_t s0 = (int64_t)blockIdx.x * (HIST_T * HIST_PER) + threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < HIST_PER; j++) {
+        const int64_t s = s0 + (int64_t)j * HIST_T;
+        const uint32_t c = s < n ? cls[s] : 0xffffffffu;
+        if (c < nclass) atomicAdd(&cnt[c], 1u);
+    }
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < nclass; i += HIST_T)
+        if (cnt[i]) atomicAdd(&hist[i], (unsigned long long)cnt[i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -429,8 +486,7 @@ extern "C" scc_status scc_classify(const scc_table *T, const int32_t *verts, int
     scc_status s = ensure_classes(T->k, st, &cd);
     if (s) return s;
     GraphView g{T->n, T->row_ptr, T->col_idx, T->colors};
-    hipLaunchKernelGGL(k_classify, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, T->k, verts, n, cd->lut,
-                       out_code, out_class);
+    launch_classify(g, T->k, verts, n, cd->lut, out_code, out_class, st);
     HIP_TRY(hipGetLastError());
     return SCC_OK;
 }
@@ -497,8 +553,8 @@ void launch_serve_classify(const ServeClassArgs *args, const ServeChunk *ch, con
                            int64_t total, hipStream_t st)
 {
     if (total <= 0 || nch <= 0) return;
-    hipLaunchKernelGGL(k_serve_classify, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, args, ch, cend, nch,
-                       total);
+    hipLaunchKernelGGL(k_serve_classify, dim3((unsigned)((total * SERVE_GL + 255) / 256)), dim3(256), 0, st, args, ch,
+                       cend, nch, total);
 }
 
 void class_sigma_rows(int k, const std::vector<int> &ids, std::vector<const int64_t *> &rows)
@@ -653,7 +709,8 @@ extern "C" scc_status scc_ags(const scc_table *tc, int64_t cbar, int64_t round_s
         s = scc_classify(T, dv, round_size, nullptr, dc, st);
         if (s) return done(s);
         if (hipMemsetAsync(dh, 0, (size_t)S * 8, st) != hipSuccess) return done(set_error(SCC_EDEVICE, "AGS memset"));
-        hipLaunchKernelGGL(k_hist, dim3((unsigned)((round_size + 255) / 256)), dim3(256), 0, st, dc, round_size, (uint32_t)S, dh);
+        hipLaunchKernelGGL(k_hist, dim3((unsigned)((round_size + HIST_T * HIST_PER - 1) / (HIST_T * HIST_PER))), dim3(HIST_T),
+                           (size_t)S * 4, st, dc, round_size, (uint32_t)S, dh);
         if (hipMemcpyAsync(hh.data(), dh, (size_t)S * 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return done(set_error(SCC_EDEVICE, "AGS histogram"));

@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 import graphgen as gg
 import oracle as O
@@ -167,3 +168,37 @@ def test_estimates_equal_oracle():
     oc, og = O.estimate(ot, r["hits"], w=r["w"])
     assert np.array_equal(gc, oc) and np.allclose(gg_, og, rtol=1e-14, atol=0)
     assert (gc > 0).sum() == (r["hits"] > 0).sum()
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 65])
+def test_classify_group_edges(k, n):
+    # a group of 8, 16 or 32 lanes per sample: one sample, a wave's and a block's
+    # remainder, and a sample with a vertex id outside the graph (no class)
+    g = gg.chung_lu(400, 2400, 2.2, 60, seed=k)
+    gt, _ = build_pair(g, gg.colors(g.n, k, seed=1), k)
+    rng = np.random.default_rng(100 * k + n)
+    v = np.stack([rng.choice(g.n, k, replace=False) for _ in range(n)]).astype(np.int32)
+    code, cls = gt.classify(torch.from_numpy(v).cuda())
+    ocode, ocls = O.classify(g, k, v)
+    assert np.array_equal(code.cpu().numpy().view(np.uint32), np.asarray(ocode).view(np.uint32))
+    assert np.array_equal(cls.cpu().numpy().view(np.uint32), np.asarray(ocls).view(np.uint32))
+    v[n // 2, k - 1] = g.n
+    bad, _ = gt.classify(torch.from_numpy(v).cuda())
+    bad = bad.cpu().numpy().view(np.uint32)
+    assert bad[n // 2] == 0xffffffff and (np.delete(bad, n // 2) == np.delete(code.cpu().numpy().view(np.uint32), n // 2)).all()
+
+
+@pytest.mark.parametrize("round_size", [1, 4095, 4097, 8192])
+def test_ags_round_histogram_edges(round_size):
+    # the class histogram's blocks of 4096 samples: their remainders and whole blocks
+    g = gg.chung_lu(600, 2400, 2.2, 60, seed=9)
+    k = 5
+    gt, _ = build_pair(g, gg.colors(g.n, k, seed=10), k)
+    r = gt.ags(cbar=10 ** 9, round_size=round_size, budget=2 * round_size, seed=3)
+    assert len(r["round_shapes"]) == 2
+    want = np.zeros_like(r["hits"])
+    for q in range(2):
+        v, _ = gt.sample(round_size, seed=3, shape=int(r["round_shapes"][q]), first_index=q * round_size)
+        want += np.bincount(gt.classify(v)[1].cpu().numpy(), minlength=want.size)
+    assert np.array_equal(r["hits"], want)
