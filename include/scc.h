@@ -191,8 +191,9 @@ typedef struct {
                                   vertex per lane before the combine, as at levels where most
                                   vertices have high words in their top-level neighbour sums */
     int sorted_sum_rows;       /* bit h: the rows of the level-h neighbour sums were sorted into
-                                  64- and 128-bit ones (one per lane) before the gather, as where
-                                  many rows border a vertex whose level-h sum needs 128 bits */
+                                  64- and 128-bit ones (one per lane) before the gather: where a row
+                                  may need 128 bits (levels kept with dense records), or many rows
+                                  border a vertex whose level-h sum does */
     int grouped_combine;       /* bit h: level h was combined four vertices per wave (at most
                                   64 outputs per vertex) */
 } scc_table_info;
@@ -281,9 +282,9 @@ scc_status scc_export_level(const scc_table *t, int h, int64_t *nnz_out,
  *
  * out_verts: device int32[n * k], vertex ids in discovery order, root first.
  * out_parent: device int8[n * k], position of each vertex's parent (-1 for the
- * root). The first call on a table also stores, with the table, the colour of
- * every edge's head in CSR order (one byte per CSR entry), read by the
- * neighbour draw; it changes no sample. Errors: SCC_EINVAL (shape id),
+ * root). The draw reads the colour of every edge's head in CSR order (one byte
+ * per CSR entry), stored with the table by the build, or by the first call on a
+ * table of a batched build; it changes no sample. Errors: SCC_EINVAL (shape id),
  * SCC_EEMPTY (total 0), SCC_ENOMEM.
  */
 scc_status scc_sample(const scc_table *t, int32_t shape, int64_t n, uint64_t seed,

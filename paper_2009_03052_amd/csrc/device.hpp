@@ -20,6 +20,14 @@ struct LevelView {
     const uint64_t *bm;        // presence bitmaps, BW words per vertex
     int BW;
     int vlc;                   // records in the variable-length layout (below)
+    // Dense records (P > 0): levels most of whose counts are non-zero keep every
+    // count by position (DevLut::setpos) without keys or bitmaps: the low words of v
+    // are pool[v P ..], zeros included; a 128-bit vertex has its high words in row
+    // LOC_OFF(loc[v]) of hi (P words a row; hi is null when the level has none) and
+    // N[v] is the level sum.
+    int P;
+    const uint64_t *hi;
+    const u128 *N;
 };
 
 #define LOC_OFF(l) ((l) & 0xffffffffffull)
@@ -105,6 +113,15 @@ __device__ inline Rec rec_of(const LevelView &L, int64_t v)
     r.kw = key_words(r.len);
     r.p = L.pool + LOC_OFF(l);
     return r;
+}
+
+// count at a position of v's dense record
+__device__ inline u128 dense_cnt(const LevelView &L, int64_t v, int pos)
+{
+    const uint64_t lo = L.pool[(size_t)v * L.P + pos];
+    if (!L.hi) return lo;
+    const uint64_t l = L.loc[v];
+    return mk128(lo, LOC_WIDE(l) ? L.hi[(size_t)LOC_OFF(l) * L.P + pos] : 0);
 }
 
 struct GraphView {
@@ -233,19 +250,6 @@ __device__ inline u128 wave_satsum128(u128 x) { return last_lane128(wave_incl_sa
 __device__ inline uint64_t wave_sum64(uint64_t x) { return last_lane64(wave_incl_scan64(x)); }
 
 __device__ inline uint64_t lanemask_lt() { return (1ull << lane_id()) - 1ull; }
-
-// Count of the entry with dense level position li (>= 0) at v, via the presence
-// bitmap: its rank among v's present entries is its position in the record.
-__device__ inline u128 record_at(const LevelView &L, int64_t v, int li)
-{
-    const uint64_t *bw = L.bm + (size_t)v * L.BW;
-    const int w = li >> 6;
-    const uint64_t word = bw[w];
-    if (!((word >> (li & 63)) & 1ull)) return 0;
-    uint32_t pos = (uint32_t)__popcll(word & ((1ull << (li & 63)) - 1ull));
-    for (int q = 0; q < w; q++) pos += (uint32_t)__popcll(bw[q]);
-    return rec_of(L, v).cnt(pos);
-}
 
 // Count of a key in a stored record by binary search (0 if absent).
 __device__ inline u128 record_lookup(const LevelView &L, int64_t v, uint32_t key)

@@ -13,6 +13,10 @@
 //   pack    an exclusive scan of record sizes and a copy into one vertex-ordered
 //           pool of succinct records (u16 keys, then low words, then high words
 //           for 128-bit vertices) (Sec. 3.2 "Count tables").
+// Below level k, a level most of whose counts are non-zero is kept dense instead
+// (every count by position, no keys): the combine writes the records in place, with
+// no slots and no pack, and the gather reads from a neighbour only the counts whose
+// colour sets lack c_v (see DGatherArgs).
 // Level k is kept at colour-0 vertices under zero-rooting (Sec. 3.4).
 #include <algorithm>
 #include <chrono>
@@ -85,7 +89,13 @@ __global__ void k_validate_edges(GraphView g, int64_t nnz, int k, int *err)
 // ---------------------------------------------------------------------------
 // Level-1 neighbour sums: S_1(v)[j] = number of neighbours of colour j != c_v
 // ---------------------------------------------------------------------------
-__device__ inline void gather1_vertex(const GraphView &g, int k, uint64_t *S1, u128 *M1, int64_t v, unsigned *cnt)
+// (ecol: the colour of each edge's head, or null: looked up)
+__device__ inline int head_colour(const GraphView &g, const uint8_t *ecol, int64_t e)
+{
+    return ecol ? ecol[e] : g.colors[g.col_idx[e]];
+}
+__device__ inline void gather1_vertex(const GraphView &g, const uint8_t *ecol, int k, uint64_t *S1, u128 *M1, int64_t v,
+                                      unsigned *cnt)
 {
   {
     const int lane = threadIdx.x;
@@ -94,7 +104,7 @@ __device__ inline void gather1_vertex(const GraphView &g, int k, uint64_t *S1, u
     __syncthreads();
     const int64_t a = g.row_ptr[v], b = g.row_ptr[v + 1];
     for (int64_t e = a + lane; e < b; e += WAVE) {
-        int cu = g.colors[g.col_idx[e]];
+        int cu = head_colour(g, ecol, e);
         if (cu != cv) atomicAdd(&cnt[cu], 1u);
     }
     __syncthreads();
@@ -113,8 +123,8 @@ __device__ inline void gather1_vertex(const GraphView &g, int k, uint64_t *S1, u
 // word. Returns the ballot of the lanes whose vertex has more neighbours (left
 // to the caller).
 constexpr int64_t GATHER1_LANE_DEG = 64;
-__device__ inline uint64_t gather1_lanes(const GraphView &g, int k, uint64_t *S1, u128 *M1, int64_t v0, int64_t v1,
-                                         int64_t lane_deg)
+__device__ inline uint64_t gather1_lanes(const GraphView &g, const uint8_t *ecol, int k, uint64_t *S1, u128 *M1,
+                                         int64_t v0, int64_t v1, int64_t lane_deg)
 {
     const int64_t v = v0 + lane_id();
     bool big = false;
@@ -127,13 +137,13 @@ __device__ inline uint64_t gather1_lanes(const GraphView &g, int k, uint64_t *S1
             uint64_t packed = 0;   // byte c: neighbours of colour c
             int64_t e = a;
             for (; e + 4 <= b; e += 4) {   // four ids, then four colours, in flight together
-                int32_t u[4];
+                int c[4];
 #pragma unroll
-                for (int j = 0; j < 4; j++) u[j] = g.col_idx[e + j];
+                for (int j = 0; j < 4; j++) c[j] = head_colour(g, ecol, e + j);
 #pragma unroll
-                for (int j = 0; j < 4; j++) packed += 1ull << (8 * g.colors[u[j]]);
+                for (int j = 0; j < 4; j++) packed += 1ull << (8 * c[j]);
             }
-            for (; e < b; e++) packed += 1ull << (8 * g.colors[g.col_idx[e]]);
+            for (; e < b; e++) packed += 1ull << (8 * head_colour(g, ecol, e));
             for (int c = 0, pos = 0; c < k; c++) {
                 if (c == cv) continue;
                 S1[v * (k - 1) + pos] = (packed >> (8 * c)) & 0xffu;
@@ -148,16 +158,16 @@ __device__ inline uint64_t gather1_lanes(const GraphView &g, int k, uint64_t *S1
 // one block of 64 vertices per wave (grid-stride), longer rows by the whole
 // wave; rows above hub_degree only get zero sums and their degree here, their
 // counts coming from k_gather1_hub's chunks
-__global__ void __launch_bounds__(WAVE) k_gather1(GraphView g, int k, uint64_t *S1, u128 *M1, int64_t hub_degree)
+__global__ void __launch_bounds__(WAVE) k_gather1(GraphView g, const uint8_t *ecol, int k, uint64_t *S1, u128 *M1, int64_t hub_degree)
 {
     __shared__ unsigned cnt[SCC_KMAX];
     for (int64_t v0 = (int64_t)blockIdx.x * WAVE; v0 < g.n; v0 += (int64_t)gridDim.x * WAVE) {
-        for (uint64_t m = gather1_lanes(g, k, S1, M1, v0, min(g.n, v0 + WAVE), min(GATHER1_LANE_DEG, hub_degree)); m;
+        for (uint64_t m = gather1_lanes(g, ecol, k, S1, M1, v0, min(g.n, v0 + WAVE), min(GATHER1_LANE_DEG, hub_degree)); m;
              m &= m - 1) {
             const int64_t v = v0 + (__ffsll((long long)m) - 1);
             const int64_t d = g.row_ptr[v + 1] - g.row_ptr[v];
             if (d <= hub_degree) {
-                gather1_vertex(g, k, S1, M1, v, cnt);
+                gather1_vertex(g, ecol, k, S1, M1, v, cnt);
             } else {
                 if (lane_id() < k - 1) S1[v * (k - 1) + lane_id()] = 0;
                 if (lane_id() == 0) M1[v] = (u128)d;
@@ -168,7 +178,7 @@ __global__ void __launch_bounds__(WAVE) k_gather1(GraphView g, int k, uint64_t *
 
 // level-1 counts of a hub row, one chunk of its neighbours per workgroup, added
 // into the row (zeroed by k_gather1, which runs first)
-__global__ void __launch_bounds__(WAVE) k_gather1_hub(GraphView g, int k, const int32_t *chunk_v,
+__global__ void __launch_bounds__(WAVE) k_gather1_hub(GraphView g, const uint8_t *ecol, int k, const int32_t *chunk_v,
                                                       const int64_t *chunk_e, int chunk, uint64_t *S1)
 {
     __shared__ unsigned cnt[SCC_KMAX];
@@ -179,7 +189,7 @@ __global__ void __launch_bounds__(WAVE) k_gather1_hub(GraphView g, int k, const 
     if (lane < SCC_KMAX) cnt[lane] = 0;
     __syncthreads();
     for (int64_t e = a + lane; e < b; e += WAVE) {
-        const int cu = g.colors[g.col_idx[e]];
+        const int cu = head_colour(g, ecol, e);
         if (cu != cv) atomicAdd(&cnt[cu], 1u);
     }
     __syncthreads();
@@ -512,18 +522,6 @@ __global__ void __launch_bounds__(256) k_gather_classify(GatherArgs A, const u12
     if (nar) narrow[bn0 + __popcll(bn & below)] = (int32_t)v;
 }
 
-// the degrees of the vertices whose level sum N has a high word, summed: the
-// rows of the next level's gather that will need 128-bit sums are at least
-// their neighbours
-__global__ void __launch_bounds__(256) k_heavy_degree(GraphView g, const u128 *N, unsigned long long *out)
-{
-    unsigned long long d = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < g.n; v += (int64_t)gridDim.x * blockDim.x)
-        if (hi64(N[v])) d += (unsigned long long)(g.row_ptr[v + 1] - g.row_ptr[v]);
-    d = wave_sum64(d);
-    if (lane_id() == 0 && d) atomicAdd(out, d);
-}
-
 // hrow[rows[i]] = base + i
 __global__ void k_set_rows(int32_t *hrow, const int32_t *rows, const int *count, int64_t fixed, int32_t base)
 {
@@ -772,7 +770,7 @@ __device__ inline void hub_chunk(const GatherArgs &A, int64_t v, int64_t a, int6
 }
 
 // level-1 block sums of the hub running sums: neighbours of each colour per block
-__global__ void __launch_bounds__(WAVE) k_hub_l1_blocks(GraphView g, int k, const int32_t *hubs,
+__global__ void __launch_bounds__(WAVE) k_hub_l1_blocks(GraphView g, const uint8_t *ecol, int k, const int32_t *hubs,
                                                         const int64_t *chunk_e, const int32_t *chunk_q,
                                                         uint64_t *hub_pre, const int64_t *hub_poff)
 {
@@ -785,7 +783,7 @@ __global__ void __launch_bounds__(WAVE) k_hub_l1_blocks(GraphView g, int k, cons
     const int64_t e = a + lane;
     int j = -1;
     if (e < rb && lane < HUB_BLOCK) {
-        const int cu = g.colors[g.col_idx[e]];
+        const int cu = head_colour(g, ecol, e);
         if (cu != cx) j = cu < cx ? cu : cu - 1;   // the S_1 entry of colour set {c_u} seen from x
     }
     uint64_t *plo = hub_pre + hub_poff[(size_t)q * (SCC_KMAX + 1) + 1];
@@ -801,9 +799,12 @@ __global__ void __launch_bounds__(WAVE) k_hub_l1_blocks(GraphView g, int k, cons
 
 // block sums -> running sums at block ends, in place: one wave per (hub, entry),
 // 64 blocks per step; high words kept only where the hub's bound M reaches 2^64
+// (has_hi: the block sums have high words). The last running sum is the row's sum:
+// stored to it where Slo is given (Shi: rows hrow[x]).
 __global__ void __launch_bounds__(WAVE) k_hub_block_scan(GraphView g, const int32_t *hubs, int WS, int hs,
                                                          int rows_zero, const u128 *M, uint64_t *hub_pre,
-                                                         const int64_t *hub_poff)
+                                                         const int64_t *hub_poff, int has_hi, uint64_t *Slo,
+                                                         uint64_t *Shi, const int32_t *hrow)
 {
     const int q = blockIdx.x / WS, i = blockIdx.x - q * WS;
     const int64_t x = hubs[q];
@@ -817,13 +818,17 @@ __global__ void __launch_bounds__(WAVE) k_hub_block_scan(GraphView g, const int3
     u128 carry = 0;
     for (int64_t b0 = 0; b0 < nb; b0 += WAVE) {
         const int64_t b = b0 + threadIdx.x;
-        const u128 val = b < nb ? mk128(plo[b], phi[b]) : (u128)0;
+        const u128 val = b < nb ? mk128(plo[b], has_hi ? phi[b] : 0) : (u128)0;
         const u128 run = carry + wave_incl_scan128(val);
         if (b < nb) {
             plo[b] = lo64(run);
             if (pw) phi[b] = hi64(run);
         }
         carry = shfl128(run, WAVE - 1);
+    }
+    if (Slo && threadIdx.x == 0) {
+        Slo[(size_t)x * WS + i] = lo64(carry);
+        if (Shi) Shi[(size_t)hrow[x] * WS + i] = hi64(carry);
     }
 }
 
@@ -834,6 +839,317 @@ __global__ void __launch_bounds__(WAVE) k_gather_hub(GatherArgs A, int chunk)
     const int64_t a = A.chunk_e[blockIdx.x];
     const int64_t b = min(A.g.row_ptr[v + 1], a + (int64_t)chunk);
     hub_chunk<false>(A, v, a, b, sm, A.chunk_q ? A.chunk_q[blockIdx.x] : -1);
+}
+
+// ---------------------------------------------------------------------------
+// Gather from dense records. A sum row has WS = r_h binom(k-1, h) entries; entry
+// (C, rank) takes, from every neighbour u with c_u in C, the one count of its
+// record at position setpos(C without c_u) r_h + rank. So lane i owns entry i of
+// the row for its whole length, in registers: it reads one word per neighbour at
+// an offset that depends on the neighbour's colour only (DevLut::gsel), and
+// nothing is added through LDS. The entries whose sets hold c_v, of which a
+// record has h - 1 in every k - 1, are never read; the record's order keeps the
+// others in few runs of whole lines.
+// GW lanes hold a row's entries, R each (GW R >= WS); a wave has 64 / GW groups,
+// which take a row each (short rows) or every (64/GW)-th neighbour of one row.
+// W128: some neighbour or row may need 128 bits.
+// The gather is bound by HBM reads. At k = 8 (Chung-Lu, 4*10^6 vertices, 6*10^7
+// edges) the sparse records of levels 2..7 took 1.26 TB of reads and 250 ms a build
+// (6.2 TB/s of requests), the dense ones take 110 ms; with what the combine and the
+// pack no longer do the build went from 418 to 237 ms (k = 6, 10^6 vertices, 10^7
+// edges: 10.4 to 8.1 ms; k = 7, 5*10^5 and 5*10^6: 13.3 to 9.3 ms).
+// ---------------------------------------------------------------------------
+struct DGatherArgs {
+    GraphView g;
+    const uint8_t *ecol;           // colour of each edge's head
+    const DevLut *L;
+    int hs, rr, P, WS, nq;         // level, its shapes, words per record, entries, sets per row
+    int rows_zero, hub_degree, bounded;   // bounded: M and hrow are already set
+    const uint64_t *lo, *hi, *loc; // the level's records (hi null: no 128-bit vertex)
+    const u128 *N;                 // its level sums
+    u128 *M;
+    uint64_t *Slo, *Shi;
+    const int32_t *hrow;           // high-word row of v, or -1 (null when not bounded)
+    const int32_t *chunk_v;        // hub chunks: vertex, first edge, hub number
+    const int64_t *chunk_e;
+    const int32_t *chunk_q;
+    uint64_t *hub_pre;             // the sampler's hub running sums, or null
+    const int64_t *hub_poff;
+    int *err;
+};
+
+// This lane's entries of the row: i = gl + GW r is entry (set q, rank t); off the
+// row every byte of its selector is 0xff
+template <int GW, int R> struct DLane {
+    int q[R], t[R];
+    bool on[R];
+    __device__ DLane(const DGatherArgs &A)
+    {
+        const int gl = lane_id() & (GW - 1);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int i = gl + GW * r;
+            on[r] = i < A.WS;
+            q[r] = on[r] ? i / A.rr : 0;
+            t[r] = i - q[r] * A.rr;
+        }
+    }
+};
+
+template <int R> struct DAcc {
+    uint64_t lo[R], hi[R];
+    u128 m;
+};
+
+// Adds the group's edges start, start + stride, ... below end (the same trip in
+// every lane of the wave). U neighbours' words are requested before any is added.
+template <int GW, int R, bool W128>
+__device__ inline void dgather_edges(const DGatherArgs &A, const DLane<GW, R> &D, int cv, int64_t start, int64_t end,
+                                     int64_t stride, bool bound, DAcc<R> &acc)
+{
+    constexpr int U = R * (W128 ? 2 : 1) >= 4 ? 2 : 4;
+    const int lane = lane_id(), gl = lane & (GW - 1), gb = lane & ~(GW - 1);
+    uint64_t tab[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) tab[r] = D.on[r] ? A.L->gsel[A.hs][cv][D.q[r]] : ~0ull;
+    for (int64_t base = start;; base += GW * stride) {
+        const int64_t e = base + gl * stride;
+        const bool act = e < end;
+        const uint64_t am = __ballot(act);
+        if (!am) break;
+        int32_t u = 0, c = 0, hr = -1;
+        if (act) {
+            u = A.g.col_idx[e];
+            c = A.ecol[e];
+            if (W128 && A.hi) {
+                const uint64_t l = A.loc[u];
+                if (LOC_WIDE(l)) hr = (int32_t)LOC_OFF(l);
+            }
+            if (bound) acc.m = sat_add(acc.m, A.N[u]);
+        }
+        uint64_t f = am;   // a group's edges are its first lanes: the longest group's count
+#pragma unroll
+        for (int s = 32; s >= GW; s >>= 1) f |= f >> s;
+        if (GW < 64) f &= (1ull << (GW & 63)) - 1ull;
+        const int mx = 64 - __clzll((long long)f);
+        const int cnt = GW < 64 ? __popcll(am >> gb & ((1ull << (GW & 63)) - 1ull)) : mx;
+        for (int n = 0; n < mx; n += U) {
+            uint64_t xl[U][R], xh[U][R];
+#pragma unroll
+            for (int j = 0; j < U; j++) {
+                const int src = n + j;
+                const bool ok = src < cnt;
+                int32_t nu, nc, nh = -1;
+                if (GW == 64) {
+                    nu = __builtin_amdgcn_readlane(u, src & 63);
+                    nc = __builtin_amdgcn_readlane(c, src & 63);
+                    if (W128) nh = __builtin_amdgcn_readlane(hr, src & 63);
+                } else {
+                    nu = __shfl(u, gb + (src & (GW - 1)), WAVE);
+                    nc = __shfl(c, gb + (src & (GW - 1)), WAVE);
+                    if (W128) nh = __shfl(hr, gb + (src & (GW - 1)), WAVE);
+                }
+                const uint64_t *row = A.lo + (size_t)nu * A.P;
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    const uint32_t p = (uint32_t)(tab[r] >> (8 * nc)) & 0xffu;
+                    const bool in = ok && p != 0xffu;
+                    const uint32_t off = p * (uint32_t)A.rr + (uint32_t)D.t[r];
+                    xl[j][r] = 0;
+                    xh[j][r] = 0;
+                    if (in) {
+                        xl[j][r] = row[off];
+                        if (W128 && nh >= 0) xh[j][r] = A.hi[(size_t)nh * A.P + off];
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < U; j++)
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    acc.lo[r] += xl[j][r];
+                    if (W128) acc.hi[r] += xh[j][r] + (acc.lo[r] < xl[j][r] ? 1u : 0u);
+                }
+        }
+    }
+}
+
+// sums of the groups of one row, in every lane
+template <int GW, int R, bool W128>
+__device__ inline void dgather_join(DAcc<R> &acc)
+{
+#pragma unroll
+    for (int s = GW; s < WAVE; s <<= 1)
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint64_t x = shfl64(acc.lo[r], lane_id() ^ s);
+            acc.lo[r] += x;
+            if (W128) acc.hi[r] += shfl64(acc.hi[r], lane_id() ^ s) + (acc.lo[r] < x ? 1u : 0u);
+        }
+}
+
+template <int GW, int R, bool W128>
+__device__ inline void dgather_store(const DGatherArgs &A, const DLane<GW, R> &D, int64_t v, bool mine, const DAcc<R> &acc)
+{
+    const int hr = W128 && A.hrow && mine ? A.hrow[v] : -1;
+#pragma unroll
+    for (int r = 0; r < R; r++)
+        if (mine && D.on[r]) {
+            const int s = D.t[r] * A.nq + D.q[r];   // sums stay in (rank, colex) order
+            A.Slo[(size_t)v * A.WS + s] = acc.lo[r];
+            if (W128 && hr >= 0) A.Shi[(size_t)hr * A.WS + s] = acc.hi[r];
+        }
+}
+
+// one row per wave: every row (rows null) or the listed ones, hubs left out
+template <int GW, int R, bool W128>
+__global__ void __launch_bounds__(WAVE) k_dgather_row(DGatherArgs A, const int32_t *rows)
+{
+    const int64_t v = rows ? (int64_t)__builtin_amdgcn_readfirstlane(rows[blockIdx.x]) : (int64_t)blockIdx.x;
+    const int cv = A.g.colors[v];
+    if (A.rows_zero && cv != 0) return;
+    const int64_t a = A.g.row_ptr[v], b = A.g.row_ptr[v + 1];
+    if (b - a > A.hub_degree) return;
+    const DLane<GW, R> D(A);
+    DAcc<R> acc{};
+    dgather_edges<GW, R, W128>(A, D, cv, a + lane_id() / GW, b, WAVE / GW, !A.bounded, acc);
+    dgather_join<GW, R, W128>(acc);
+    if (!A.bounded) {
+        const u128 m = wave_satsum128(acc.m);
+        if (lane_id() == 0) A.M[v] = m;
+    }
+    dgather_store<GW, R, W128>(A, D, v, lane_id() < GW, acc);
+}
+
+// rows of at most GROUP_DEG neighbours, one per group of lanes (a list, or all)
+template <int GW, int R, bool W128>
+__global__ void __launch_bounds__(WAVE) k_dgather_group(DGatherArgs A, const int32_t *rows, int64_t nrows)
+{
+    const int64_t i = (int64_t)blockIdx.x * (WAVE / GW) + lane_id() / GW;
+    const bool in = i < nrows;
+    const int64_t v = in ? (rows ? (int64_t)rows[i] : i) : 0;
+    const int cv = in ? (int)A.g.colors[v] : 0;
+    const int64_t a = in ? A.g.row_ptr[v] : 0, b = in ? A.g.row_ptr[v + 1] : 0;
+    const bool mine = in && b - a <= min((int64_t)GROUP_DEG, (int64_t)A.hub_degree) && !(A.rows_zero && cv != 0);
+    const DLane<GW, R> D(A);
+    DAcc<R> acc{};
+    dgather_edges<GW, R, W128>(A, D, cv, a, mine ? b : a, 1, !A.bounded, acc);
+    if (!A.bounded) {
+        u128 m = acc.m;
+#pragma unroll
+        for (int s = GW / 2; s >= 1; s >>= 1) m = sat_add(m, shfl128(m, lane_id() ^ s));
+        if (mine && (lane_id() & (GW - 1)) == 0) A.M[v] = m;
+    }
+    dgather_store<GW, R, W128>(A, D, v, mine, acc);
+}
+
+// A chunk of a hub row. With the sampler's running sums (hub_pre) the chunk is
+// one block of HUB_BLOCK neighbours and its sums are stored as that block's; the
+// scan over the blocks then leaves the row's sums (k_hub_block_scan). Without
+// them the chunks are merged into the row (cleared before) by atomics.
+template <int GW, int R, bool W128>
+__global__ void __launch_bounds__(WAVE) k_dgather_hub(DGatherArgs A, int chunk)
+{
+    const int64_t v = A.chunk_v[blockIdx.x];
+    const int cv = A.g.colors[v];
+    if (A.rows_zero && cv != 0) return;
+    const int64_t a = A.chunk_e[blockIdx.x], ra = A.g.row_ptr[v], rb = A.g.row_ptr[v + 1];
+    const int64_t b = min(rb, a + (int64_t)chunk);
+    const DLane<GW, R> D(A);
+    DAcc<R> acc{};
+    dgather_edges<GW, R, W128>(A, D, cv, a + lane_id() / GW, b, WAVE / GW, true, acc);
+    dgather_join<GW, R, W128>(acc);
+    const u128 m = wave_satsum128(acc.m);
+    bool over = false;
+    if (lane_id() == 0) {
+        unsigned long long *Mw = (unsigned long long *)&A.M[v];
+        over = atomic_add128(&Mw[0], &Mw[1], lo64(m), hi64(m)) || m == ~(u128)0;
+    }
+    if (lane_id() < GW) {
+        const int64_t nb = (rb - ra + HUB_BLOCK - 1) / HUB_BLOCK, blk = (a - ra) / HUB_BLOCK;
+        uint64_t *plo = A.hub_pre ? A.hub_pre + A.hub_poff[(size_t)A.chunk_q[blockIdx.x] * (SCC_KMAX + 1) + A.hs] : nullptr;
+        uint64_t *phi = plo + (size_t)A.WS * nb;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (!D.on[r]) continue;
+            const int s = D.t[r] * A.nq + D.q[r];
+            if (A.hub_pre) {
+                plo[(size_t)s * nb + blk] = acc.lo[r];
+                if (W128) phi[(size_t)s * nb + blk] = acc.hi[r];
+            } else {
+                unsigned long long *Slo = (unsigned long long *)(A.Slo + (size_t)v * A.WS + s);
+                if (W128) {
+                    unsigned long long *Shi = (unsigned long long *)(A.Shi + (size_t)A.hrow[v] * A.WS + s);
+                    over |= atomic_add128(Slo, Shi, acc.lo[r], acc.hi[r]);
+                } else if (acc.lo[r]) {
+                    atomicAdd(Slo, (unsigned long long)acc.lo[r]);
+                }
+            }
+        }
+    }
+    if (over) atomicOr(A.err, 2);   // the bound left 128 bits: the build reports overflow
+}
+
+// cleared bound and (merged by atomics) sums of the hub rows
+__global__ void __launch_bounds__(WAVE) k_dhub_prepare(DGatherArgs A, const int32_t *hubs, int sums)
+{
+    const int64_t v = hubs[blockIdx.x];
+    if (threadIdx.x == 0) A.M[v] = 0;
+    for (int i = threadIdx.x; sums && i < A.WS; i += WAVE) {
+        A.Slo[(size_t)v * A.WS + i] = 0;
+        if (A.Shi) A.Shi[(size_t)A.hrow[v] * A.WS + i] = 0;
+    }
+}
+
+// The bounds M_hs(v) of the rows below the hub threshold, one row per lane (the
+// form that measured best for k_gather_classify), and compact high-word rows
+// base, base + 1, ... for those whose bound reaches 2^64; hub rows get their
+// bound with their chunks. Run before the gather where a row's bound may reach
+// 2^64, so that the one gather pass knows which sums need high words.
+__global__ void __launch_bounds__(256) k_row_bounds(GraphView g, int hub_degree, int rows_zero, const u128 *N, u128 *M,
+                                                    int32_t *hrow, int32_t base, int *count)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool in = v < g.n;
+    const int64_t a = in ? g.row_ptr[v] : 0, b = in ? g.row_ptr[v + 1] : 0;
+    const bool act = in && b - a <= hub_degree && !(rows_zero && g.colors[v] != 0);
+    u128 m = 0;
+    for (int64_t e0 = a; act && e0 < b; e0 += 4) {
+        int32_t u[4];
+        u128 x[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) u[j] = e0 + j < b ? g.col_idx[e0 + j] : -1;
+#pragma unroll
+        for (int j = 0; j < 4; j++) x[j] = u[j] >= 0 ? N[u[j]] : (u128)0;
+#pragma unroll
+        for (int j = 0; j < 4; j++) m = sat_add(m, x[j]);
+    }
+    const bool wide = act && hi64(m) != 0;
+    const uint64_t bw = __ballot(wide);
+    int at = 0;
+    if (lane_id() == 0 && bw) at = atomicAdd(count, __popcll(bw));
+    at = __shfl(at, 0);
+    if (act) M[v] = m;
+    if (in) hrow[v] = wide ? base + at + __popcll(bw & lanemask_lt()) : -1;
+}
+
+// The gather kernels for a row of WS entries: the narrowest group of lanes that
+// holds it, two or three entries a lane above 64
+struct DGatherKernels {
+    void (*row)(DGatherArgs, const int32_t *);
+    void (*group)(DGatherArgs, const int32_t *, int64_t);   // null: one row per wave only
+    void (*hub)(DGatherArgs, int);
+    int gw;
+};
+template <int GW, int R, bool W128> DGatherKernels dgather_of()
+{
+    if constexpr (GW < 64) return {k_dgather_row<GW, R, W128>, k_dgather_group<GW, R, W128>, k_dgather_hub<GW, R, W128>, GW};
+    else return {k_dgather_row<GW, R, W128>, nullptr, k_dgather_hub<GW, R, W128>, GW};
+}
+template <bool W128> DGatherKernels dgather_kernels(int WS)
+{
+    return WS <= 8 ? dgather_of<8, 1, W128>() : WS <= 16 ? dgather_of<16, 1, W128>() : WS <= 32 ? dgather_of<32, 1, W128>()
+         : WS <= 64 ? dgather_of<64, 1, W128>() : WS <= 128 ? dgather_of<64, 2, W128>() : dgather_of<64, 3, W128>();
 }
 
 // algorithmic bytes of one gather launch (for reports): 4 d_v + neighbours'
@@ -915,7 +1231,8 @@ __global__ void k_hub_list(GraphView g, int hub_degree, int32_t *hubs, int *coun
 
 // hub rows (count[0]), the rows between the grouped ones and the hubs
 // (count[1]), the number of rows of at most GROUP_LOW_DEG neighbours (count[2])
-// and the colour-0 rows (count[3]), each list in no particular order. One atomic
+// and the colour-0 rows (count[3]), each list in no particular order, and the
+// largest degree, clamped to 2^31 - 1 (count[4]). One atomic
 // per list and block of ROW_LIST_T rows: the four counters are shared by the
 // whole grid.
 constexpr int ROW_LIST_T = 1024;
@@ -924,6 +1241,7 @@ __global__ void __launch_bounds__(ROW_LIST_T) k_row_lists(GraphView g, int hub_d
 {
     __shared__ int wcnt[ROW_LIST_T / WAVE][4];   // per wave: hubs, mids, colour-0 rows, low rows
     __shared__ int wbase[ROW_LIST_T / WAVE][3];
+    __shared__ int wmax[ROW_LIST_T / WAVE];
     const int w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t d = v < g.n ? g.row_ptr[v + 1] - g.row_ptr[v] : 0;
@@ -931,7 +1249,10 @@ __global__ void __launch_bounds__(ROW_LIST_T) k_row_lists(GraphView g, int hub_d
     const bool zero = v < g.n && g.colors[v] == 0;
     const uint64_t hm = __ballot(hub), mm = __ballot(mid), zm = __ballot(zero);
     const uint64_t low = __ballot(v < g.n && d <= GROUP_LOW_DEG);
+    int dm = (int)min(d, (int64_t)0x7fffffff);
+    for (int o = WAVE / 2; o >= 1; o >>= 1) dm = max(dm, __shfl_xor(dm, o, WAVE));
     if (lane_id() == 0) {
+        wmax[w] = dm;
         wcnt[w][0] = __popcll(hm);
         wcnt[w][1] = __popcll(mm);
         wcnt[w][2] = __popcll(zm);
@@ -945,7 +1266,12 @@ __global__ void __launch_bounds__(ROW_LIST_T) k_row_lists(GraphView g, int hub_d
                 wbase[q][l] = tot[l];
                 tot[l] += wcnt[q][l];
             }
-        for (int q = 0; q < nw; q++) tot[3] += wcnt[q][3];
+        int dm = 0;
+        for (int q = 0; q < nw; q++) {
+            tot[3] += wcnt[q][3];
+            dm = max(dm, wmax[q]);
+        }
+        if (dm) atomicMax(&count[4], dm);
         const int b0 = tot[0] ? atomicAdd(&count[0], tot[0]) : 0;
         const int b1 = tot[1] ? atomicAdd(&count[1], tot[1]) : 0;
         const int b2 = tot[2] ? atomicAdd(&count[3], tot[2]) : 0;
@@ -986,88 +1312,10 @@ struct CombineArgs {
     int *err;                             // [0]: overflow
     uint64_t *bm;                         // the level's presence bitmaps (BW words a vertex), or null
     int BW;
+    // > 0: the level's records are dense: slot_lo is the pool itself (P words a
+    // vertex, by position), slot_hi holds high words likewise, no keys are written
+    int P;
 };
-
-template <int ILP>
-__device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, const uint64_t *Xlo,
-                                       const uint64_t *Slo, const uint64_t *Xhi, const uint64_t *Shi, bool owide,
-                                       bool wide, int s_hi0 = 0, const uint16_t *tx_lds = nullptr);
-
-// Counts of vertex v at level h. The low words of v's own counts X and of its
-// neighbour sums S are staged in lo_area (LDS); high words are needed only when
-// v's bound U reaches 2^64 and are staged in hi_area. With hi_area null, such a
-// vertex is appended to wide_list instead and left for a second pass.
-template <bool SLOTS>
-__device__ inline void combine_vertex(const CombineArgs &A, int64_t v, uint64_t *lo_area, uint64_t *hi_area,
-                                      int *wide_list, int *wide_count)
-{
-    const DevLut &L = *A.L;
-    const int lane = threadIdx.x;
-    const int h = A.h;
-    const int cv = A.g.colors[v];
-    if (A.zero_only && cv != 0) {
-        if (lane == 0) { A.meta[v] = 0; A.Nout[v] = 0; }
-        return;
-    }
-    // per-vertex bound: U >= sum over (T, C) of beta_T c(T_C, v) >= every partial sum.
-    // Under round skipping both parts of a designated shape have 2..h-2 nodes, so
-    // only those part sizes are bounded and staged (level h-1 is not built).
-    const int plo = A.bal ? 2 : 1, phi = A.bal ? h - 2 : h - 1;
-    u128 U = 0;
-    for (int hp = plo; hp <= phi; hp++) {
-        if (!A.M[h - hp]) continue;   // sums not built: no evaluated term uses them
-        u128 Nv = hp == 1 ? (u128)1 : h_N<SLOTS>(A.lev[hp], src_handle<SLOTS>(A.lev[hp], v));
-        U = sat_add(U, sat_mul(Nv, A.M[h - hp][v]));
-    }
-    if (U == ~(u128)0 || bitlen128(U) > A.max_bits) {
-        if (lane == 0) { atomicOr(A.err, 1); A.meta[v] = 0; A.Nout[v] = 0; }
-        return;
-    }
-    // owide: some output or partial sum may reach 2^64 (accumulate and store 128
-    // bits); wide: some input has high words too (stage them). Below 2^64 every
-    // product and partial sum fits in the low words (U bounds them).
-    const bool owide = hi64(U) != 0;
-    bool wide = false;
-    if (owide) {
-        for (int hp = 2; hp <= phi; hp++) wide |= h_wide<SLOTS>(src_handle<SLOTS>(A.lev[hp], v));
-        for (int hs = 1; hs <= phi; hs++) wide |= A.M[hs] && hi64(A.M[hs][v]) != 0;
-    }
-    if (wide && !hi_area) {
-        if (lane == 0) wide_list[atomicAdd(wide_count, 1)] = (int)v;
-        return;
-    }
-    const int XT = L.xoff[h];
-    uint64_t *Xlo = lo_area, *Slo = lo_area + XT;
-    uint64_t *Xhi = hi_area, *Shi = hi_area + XT;
-    for (int i = lane; i < XT; i += WAVE) {
-        Xlo[i] = 0;
-        if (wide) Xhi[i] = 0;
-    }
-    __syncthreads();
-    if (lane == 0) Xlo[L.xoff[1]] = 1;   // level 1: the single node, coloured c_v
-    const int16_t *xidx = A.key_xidx + (size_t)cv * L.nkeys;
-    for (int hp = 2; hp <= phi; hp++) {
-        const RecView<SLOTS> r = h_rec<SLOTS>(A.lev[hp], src_handle<SLOTS>(A.lev[hp], v));
-        for (uint32_t e = lane; e < r.len; e += WAVE) {
-            const int x = L.xoff[hp] + xidx[r.key[e]];
-            Xlo[x] = r.lo[e];
-            if (wide) Xhi[x] = r.hi ? r.hi[e] : 0;
-        }
-    }
-    for (int hs = 1; hs <= phi; hs++) {
-        if (!A.Slo[hs]) continue;
-        const int ws = L.WS[hs];
-        const uint64_t *gl = A.Slo[hs] + (size_t)v * ws;
-        const bool sw = hi64(A.M[hs][v]) != 0;
-        const uint64_t *gh = sw ? A.Shi[hs] + hi_row(A.Shrow[hs], v) * ws : nullptr;
-        for (int i = lane; i < ws; i += WAVE) {
-            Slo[L.soff[hs] + i] = gl[i];
-            if (wide) Shi[L.soff[hs] + i] = sw ? gh[i] : 0;
-        }
-    }
-    __syncthreads();
-    combine_outputs<4>(A, v, cv, Xlo, Slo, Xhi, Shi, owide, wide);
-}
 
 // The outputs of vertex v at level h from its staged counts (X) and neighbour
 // sums (S): lane o evaluates outputs o, o + 64, ..., and the nonzero ones are
@@ -1083,7 +1331,12 @@ __device__ inline u128 mul_64x128(uint64_t x, u128 s) { return (u128)x * lo64(s)
 // s_hi0 on (the sums below have none); with own counts in 64 bits, an output
 // whose T'' block lies below s_hi0 takes 64 x 64-bit products. tx_lds: the
 // level's term descriptors copied to LDS (level_term_words), else read from L.
-template <int ILP>
+// POS: own counts are staged by dense position (outd, xterm), else by output
+// index (out, term_xs). A level with dense records takes its outputs in position
+// order and stores every one, zeros included.
+template <bool POS> __device__ inline int term_xi(uint32_t xs) { return (int)(POS ? xs & 0x1ffu : xs & 0xffu); }
+template <bool POS> __device__ inline int term_si(uint32_t xs) { return (int)(POS ? xs >> 9 : xs >> 8); }
+template <int ILP, bool POS>
 __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, const uint64_t *Xlo,
                                        const uint64_t *Slo, const uint64_t *Xhi, const uint64_t *Shi, bool owide,
                                        bool wide, int s_hi0, const uint16_t *tx_lds)
@@ -1097,13 +1350,19 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
     const uint16_t *okey = L.out_key[cv] + ob;
     uint32_t cnt = 0;
     u128 nsum = 0;
+    const int stride = A.P ? A.P : A.W;
     uint16_t *sk = A.slot_key + (size_t)v * A.W;
-    uint64_t *sl = A.slot_lo + (size_t)v * A.W;
-    uint64_t *sh = owide ? A.slot_hi + (size_t)v * A.W : nullptr;
+    uint64_t *sl = A.slot_lo + (size_t)v * stride;
+    uint64_t *sh = owide ? A.slot_hi + (size_t)v * stride : nullptr;
+    // own counts by position and outputs by index, or the reverse, occur only where
+    // some levels of a table are dense and some are not
+    const uint64_t *outs = POS ? L.outd : L.out;
+    const bool reorder = A.P ? !POS : (POS && h < L.k);
+    const uint16_t *ord = A.P ? L.xord : L.xpos;
     for (int o0 = 0; o0 < Wh; o0 += WAVE) {
         const int o = o0 + lane;
         u128 val = 0;
-        const uint64_t d = o < Wh ? L.out[ob + o] : 0ull;
+        const uint64_t d = o < Wh ? outs[ob + (reorder ? ord[ob + o] : o)] : 0ull;
         if (o < Wh && !(A.bal && !(d >> 63))) {
             const int xb = (int)(d & 0xffffu), sb = (int)((d >> 16) & 0xffffu), tb = (int)((d >> 32) & 0xffffu);
             const int nsplit = (int)((d >> 48) & 0xffu);
@@ -1111,7 +1370,7 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
             // terms four at a time: the four descriptors, then all their LDS
             // operands, are requested before any product, so that the loads of
             // a group overlap instead of one latency per term
-            const uint16_t *txs = tx_lds ? tx_lds + (tb - L.term_base[h][1]) : L.term_xs + tb;
+            const uint16_t *txs = tx_lds ? tx_lds + (tb - L.term_base[h][1]) : (POS ? L.xterm : L.term_xs) + tb;
             const int n4 = ILP >= 4 ? (nsplit & ~3) : 0;
             if (!owide) {
                 uint64_t a64 = 0;
@@ -1121,13 +1380,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
 #pragma unroll
                     for (int j = 0; j < 4; j++) xs[j] = txs[i + j];
 #pragma unroll
-                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + (xs[j] & 0xffu)]; sv[j] = Slo[sb + (xs[j] >> 8)]; }
+                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + term_xi<POS>(xs[j])]; sv[j] = Slo[sb + term_si<POS>(xs[j])]; }
 #pragma unroll
                     for (int j = 0; j < 4; j++) a64 += xv[j] * sv[j];
                 }
                 for (int i = n4; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    a64 += Xlo[xb + (xs & 0xffu)] * Slo[sb + (xs >> 8)];
+                    a64 += Xlo[xb + term_xi<POS>(xs)] * Slo[sb + term_si<POS>(xs)];
                 }
                 acc = a64;
             } else if (!wide || (!Xhi && sb < s_hi0)) {
@@ -1137,13 +1396,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
 #pragma unroll
                     for (int j = 0; j < 4; j++) xs[j] = txs[i + j];
 #pragma unroll
-                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + (xs[j] & 0xffu)]; sv[j] = Slo[sb + (xs[j] >> 8)]; }
+                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + term_xi<POS>(xs[j])]; sv[j] = Slo[sb + term_si<POS>(xs[j])]; }
 #pragma unroll
                     for (int j = 0; j < 4; j++) acc += (u128)xv[j] * sv[j];
                 }
                 for (int i = n4; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    acc += (u128)Xlo[xb + (xs & 0xffu)] * Slo[sb + (xs >> 8)];
+                    acc += (u128)Xlo[xb + term_xi<POS>(xs)] * Slo[sb + term_si<POS>(xs)];
                 }
             } else if (!Xhi) {
                 // own counts in 64 bits, neighbour sums in 128
@@ -1154,8 +1413,8 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
                     for (int j = 0; j < 4; j++) xs[j] = txs[i + j];
 #pragma unroll
                     for (int j = 0; j < 4; j++) {
-                        const int si = sb + (int)(xs[j] >> 8);
-                        xv[j] = Xlo[xb + (xs[j] & 0xffu)];
+                        const int si = sb + term_si<POS>(xs[j]);
+                        xv[j] = Xlo[xb + term_xi<POS>(xs[j])];
                         sl[j] = Slo[si];
                         sh2[j] = Shi[si - s_hi0];
                     }
@@ -1164,13 +1423,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
                 }
                 for (int i = n4; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    const int xi = xb + (int)(xs & 0xffu), si = sb + (int)(xs >> 8);
+                    const int xi = xb + term_xi<POS>(xs), si = sb + term_si<POS>(xs);
                     acc += mul_64x128(Xlo[xi], mk128(Slo[si], Shi[si - s_hi0]));
                 }
             } else {
                 for (int i = 0; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    const int xi = xb + (int)(xs & 0xffu), si = sb + (int)(xs >> 8);
+                    const int xi = xb + term_xi<POS>(xs), si = sb + term_si<POS>(xs);
                     u128 x = mk128(Xlo[xi], Xhi[xi]), s = mk128(Slo[si], Shi[si]);
                     acc += x * s;
                 }
@@ -1188,7 +1447,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
         // output o is dense position o of the vertex's colour, so this round's
         // ballot is word o0 / 64 of its presence bitmap
         if (A.bm && lane == 0) A.bm[(size_t)v * A.BW + (o0 >> 6)] = bal;
-        if (nz) {
+        if (A.P) {
+            if (o < Wh) {
+                sl[o] = lo64(val);
+                if (owide) sh[o] = hi64(val);
+                nsum += val;
+            }
+        } else if (nz) {
             const uint32_t pos = cnt + (uint32_t)__popcll(bal & lanemask_lt());
             sk[pos] = okey[o];
             sl[pos] = lo64(val);
@@ -1232,7 +1497,10 @@ __device__ inline void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // DMA: the neighbour sums reach lo_area (LDS) by direct-to-LDS loads; HI_LDS:
 // hi_area is LDS too, so their high words may go the same way (the batched
 // worker's hi_area is global scratch: filled by ordinary stores)
-template <bool SLOTS, int PMAX, bool DMA, bool HI_LDS = false>
+// POS: every own level has dense records, staged by position: one run of direct
+// loads per level, like the neighbour sums, with no keys to read and no index to
+// look up first
+template <bool SLOTS, int PMAX, bool DMA, bool HI_LDS = false, bool POS = false>
 __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64_t *lo_area, uint64_t *hi_area,
                                          int *wide_list, int *wide_count, bool own_hi = true,
                                          const uint16_t *tx_lds = nullptr)
@@ -1260,6 +1528,9 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     auto dma_sums = [&]() {
         for (int hs = 1; hs <= phi; hs++)
             if (A.Slo[hs]) lds_dma_words(A.Slo[hs] + (size_t)v * L.WS[hs], Slo + L.soff[hs], L.WS[hs]);
+        if (POS)
+            for (int q = 2; q <= phi; q++)
+                lds_dma_words(A.lev[q].P.pool + (size_t)v * A.lev[q].P.P, Xlo + L.xoff[q], L.W[q]);
     };
     const bool late = DMA && !hi_area && A.late_dma;
     if (DMA && !late) dma_sums();
@@ -1278,7 +1549,8 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
                 if (SLOTS) { metap = A.lev[q].meta; Np = A.lev[q].N; }
                 else {
                     locp = A.lev[q].P.loc; poolp = A.lev[q].P.pool;
-                    if (A.lev[q].P.BW == 1) bmp = A.lev[q].P.bm;
+                    if (POS || A.lev[q].P.P) Np = A.lev[q].P.N;
+                    else if (A.lev[q].P.BW == 1) bmp = A.lev[q].P.bm;
                 }
             }
         }
@@ -1294,8 +1566,10 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
         if (!DMA && q <= phi && A.Slo[q] && lane < L.WS[q]) sw[q] = A.Slo[q][(size_t)v * L.WS[q] + lane];
     }
     u128 Nq = 0;
-    if (h_len<SLOTS>(hd)) {
-        if (SLOTS) Nq = Np[v];
+    if (POS) {
+        if (Np) Nq = Np[v];
+    } else if (h_len<SLOTS>(hd)) {
+        if (SLOTS || Np) Nq = Np[v];
         else { const uint64_t *rp = poolp + LOC_OFF(hd); Nq = mk128(rp[0], rp[1]); }
     }
     uint32_t ek[PMAX + 1];
@@ -1304,9 +1578,11 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     for (int q = 2; q <= PMAX; q++) {
         ek[q] = 0;
         el[q] = 0;
-        if (q <= phi) {
+        if (!POS && q <= phi) {
             const RecView<SLOTS> r = h_rec<SLOTS>(A.lev[q], readlane64(hd, q));
-            if (!SLOTS && A.lev[q].P.BW == 1) {
+            if (!SLOTS && A.lev[q].P.P) {
+                if (lane < L.W[q]) el[q] = A.lev[q].P.pool[(size_t)v * A.lev[q].P.P + lane];
+            } else if (!SLOTS && A.lev[q].P.BW == 1) {
                 const uint64_t word = readlane64(bmw, q);
                 if ((word >> lane) & 1ull) el[q] = r.lo[__popcll(word & ((1ull << lane) - 1ull))];
             } else if ((uint32_t)lane < r.len) {
@@ -1356,10 +1632,11 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     }
     if (late) dma_sums();
     const bool stage_xhi = wide && Xhi;
-    for (int i = lane; i < XT; i += WAVE) {
-        Xlo[i] = 0;
-        if (stage_xhi) Xhi[i] = 0;
-    }
+    if (!POS)
+        for (int i = lane; i < XT; i += WAVE) {
+            Xlo[i] = 0;
+            if (stage_xhi) Xhi[i] = 0;
+        }
     if (!DMA) {
 #pragma unroll
         for (int q = 1; q <= PMAX; q++)
@@ -1381,11 +1658,33 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
         }
     }
     __syncthreads();
-    if (lane == 0) Xlo[L.xoff[1]] = 1;   // level 1: the single node, coloured c_v
+    if (lane == 0) {   // level 1: the single node, coloured c_v
+        Xlo[L.xoff[1]] = 1;
+        if (POS && stage_xhi) Xhi[L.xoff[1]] = 0;
+    }
+    if (POS && stage_xhi)
+        for (int q = 2; q <= phi; q++) {
+            const LevelView &V = A.lev[q].P;
+            const uint64_t l = readlane64(hd, q);
+            if (LOC_WIDE(l)) lds_dma_words(V.hi + (size_t)LOC_OFF(l) * V.P, Xhi + L.xoff[q], L.W[q]);
+            else for (int i = lane; i < L.W[q]; i += WAVE) Xhi[L.xoff[q] + i] = 0;
+        }
     const int16_t *xidx = A.key_xidx + (size_t)cv * L.nkeys;
 #pragma unroll
     for (int q = 2; q <= PMAX; q++) {
-        if (q > phi) continue;
+        if (POS || q > phi) continue;
+        if (!SLOTS && A.lev[q].P.P) {
+            // a dense level beside one that is not: from position order to index order
+            const LevelView &V = A.lev[q].P;
+            const uint64_t l = readlane64(hd, q);
+            const uint64_t *lo = V.pool + (size_t)v * V.P, *hi = LOC_WIDE(l) ? V.hi + (size_t)LOC_OFF(l) * V.P : nullptr;
+            for (int i = lane; i < L.W[q]; i += WAVE) {
+                const int x = L.xoff[q] + L.xord[L.out_off[q] + i];
+                Xlo[x] = i < WAVE ? el[q] : lo[i];
+                if (stage_xhi) Xhi[x] = hi ? hi[i] : 0;
+            }
+            continue;
+        }
         const RecView<SLOTS> r = h_rec<SLOTS>(A.lev[q], readlane64(hd, q));
         if (!SLOTS && A.lev[q].P.BW == 1) {
             if ((readlane64(bmw, q) >> lane) & 1ull) Xlo[L.xoff[q] + lane] = el[q];
@@ -1421,26 +1720,26 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     }
     if (DMA) wait_vm_all();
     __syncthreads();
-    combine_outputs<SLOTS ? 1 : 4>(A, v, cv, Xlo, Slo, stage_xhi ? Xhi : nullptr, Shi, owide, wide, s_hi0, tx_lds);
+    combine_outputs<SLOTS ? 1 : 4, POS>(A, v, cv, Xlo, Slo, stage_xhi ? Xhi : nullptr, Shi, owide, wide, s_hi0, tx_lds);
 }
 
 // one workgroup per vertex, low words in LDS; vertices that need 128 bits are
 // listed for k_combine_wide
 // eight waves per SIMD (one register below the compiler's own choice): the
 // combine waits on memory, and the extra waves measured 9 % faster
-template <int PMAX>
+template <int PMAX, bool POS>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_combine(CombineArgs A, int *wide_list, int *wide_count)
 {
     extern __shared__ uint64_t sm[];
-    if ((int64_t)blockIdx.x < A.g.n) combine_vertex_pf<false, PMAX, true>(A, blockIdx.x, sm, nullptr, wide_list, wide_count);
+    if ((int64_t)blockIdx.x < A.g.n) combine_vertex_pf<false, PMAX, true, false, POS>(A, blockIdx.x, sm, nullptr, wide_list, wide_count);
 }
 
 // the listed vertices only (level k under zero-rooting: the colour-0 vertices)
-template <int PMAX>
+template <int PMAX, bool POS>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_combine_list(CombineArgs A, const int32_t *rows, int *wide_list, int *wide_count)
 {
     extern __shared__ uint64_t sm[];
-    combine_vertex_pf<false, PMAX, true>(A, __builtin_amdgcn_readfirstlane(rows[blockIdx.x]), sm, nullptr, wide_list, wide_count);
+    combine_vertex_pf<false, PMAX, true, false, POS>(A, __builtin_amdgcn_readfirstlane(rows[blockIdx.x]), sm, nullptr, wide_list, wide_count);
 }
 
 // The combine of a level with at most 64 outputs per vertex, four vertices per
@@ -1452,7 +1751,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
 // combine_vertex_pf: slot, meta, N and the level's single bitmap word.
 constexpr int CGL = 16;   // lanes per vertex of the grouped combine
 __device__ inline uint64_t grp_shfl64(uint64_t x, int src) { return shfl64(x, (lane_id() & ~(CGL - 1)) + src); }
-template <int PMAX>
+template <int PMAX, bool POS>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_combine_group(CombineArgs A, const int32_t *rows, int64_t nrows, int32_t *fallback, int *count)
 {
     extern __shared__ uint64_t sm[];
@@ -1470,17 +1769,22 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
     if (in && !act && s == 0) { A.meta[v] = 0; A.Nout[v] = 0; }
     // sub-lane q: the handle of v's level-q record (q >= 2) and M_q(v)
     const u128 *mp = nullptr;
+    const u128 *Np = nullptr;
     const uint64_t *locp = nullptr, *poolp = nullptr;
 #pragma unroll
     for (int q = 1; q <= PMAX; q++)
         if (s == q && q <= phi) {
             mp = A.M[q];
-            if (q >= 2) { locp = A.lev[q].P.loc; poolp = A.lev[q].P.pool; }
+            if (q >= 2) {
+                locp = A.lev[q].P.loc; poolp = A.lev[q].P.pool;
+                if (POS || A.lev[q].P.P) Np = A.lev[q].P.N;
+            }
         }
-    const uint64_t hd = act && locp ? locp[v] : 0ull;
+    const uint64_t hd = !POS && act && locp ? locp[v] : 0ull;
     const u128 Mq = act && mp ? mp[v] : (u128)0;
     u128 Nq = 0;
-    if (LOC_LEN(hd)) { const uint64_t *rp = poolp + LOC_OFF(hd); Nq = mk128(rp[0], rp[1]); }
+    if (Np) { if (act) Nq = Np[v]; }
+    else if (LOC_LEN(hd)) { const uint64_t *rp = poolp + LOC_OFF(hd); Nq = mk128(rp[0], rp[1]); }
     // bound: sub-lane hp contributes N_hp(v) M_{h-hp}(v) (level 1: N = 1), summed
     // (saturating) over the group
     const int pr = (h - s) & (CGL - 1);
@@ -1501,7 +1805,14 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
     if (isfb) fallback[fbase + __popcll(fb & lanemask_lt())] = (int32_t)v;
     // staging: own counts X (zeroed, then the records) and neighbour sums S
     if (run) {
-        for (int j = s; j < XT; j += CGL) Xlo[j] = 0;
+        if (POS) {
+            for (int q = 2; q <= phi; q++) {
+                const uint64_t *gx = A.lev[q].P.pool + (size_t)v * A.lev[q].P.P;
+                for (int j = s; j < L.W[q]; j += CGL) Xlo[L.xoff[q] + j] = gx[j];
+            }
+        } else {
+            for (int j = s; j < XT; j += CGL) Xlo[j] = 0;
+        }
         for (int hs = 1; hs <= phi; hs++) {
             if (!A.Slo[hs]) continue;
             const int ws = L.WS[hs];
@@ -1515,7 +1826,12 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
 #pragma unroll
     for (int q = 2; q <= PMAX; q++) {
         const uint64_t hq = grp_shfl64(hd, q);
-        if (!run || q > phi) continue;
+        if (POS || !run || q > phi) continue;
+        if (A.lev[q].P.P) {   // a dense level beside one that is not
+            const uint64_t *gx = A.lev[q].P.pool + (size_t)v * A.lev[q].P.P;
+            for (int j = s; j < L.W[q]; j += CGL) Xlo[L.xoff[q] + L.xord[L.out_off[q] + j]] = gx[j];
+            continue;
+        }
         const RecView<false> r = h_rec<false>(A.lev[q], hq);
         // four entries per lane with their loads issued before any store
         for (uint32_t e0 = s; e0 < r.len; e0 += 4 * CGL) {
@@ -1540,28 +1856,34 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
     const uint32_t ob = L.out_off[h];
     const uint16_t *okey = L.out_key[cv] + ob;
     uint16_t *sk = A.slot_key + (size_t)v * A.W;
-    uint64_t *sl = A.slot_lo + (size_t)v * A.W;
+    uint64_t *sl = A.slot_lo + (size_t)v * (A.P ? A.P : A.W);
+    const uint64_t *outs = POS ? L.outd : L.out;   // as in combine_outputs
+    const bool reorder = A.P ? !POS : (POS && h < L.k);
+    const uint16_t *ord = A.P ? L.xord : L.xpos;
     uint32_t cnt = 0;
     uint64_t nsum = 0, bmw = 0;
     for (int o0 = 0; o0 < Wh; o0 += CGL) {
         const int o = o0 + s;
         uint64_t val = 0;
-        const uint64_t d = run && o < Wh ? L.out[ob + o] : 0ull;
+        const uint64_t d = run && o < Wh ? outs[ob + (reorder ? ord[ob + o] : o)] : 0ull;
         if (run && o < Wh && !(A.bal && !(d >> 63))) {
             const int xb = (int)(d & 0xffffu), sb = (int)((d >> 16) & 0xffffu), tb = (int)((d >> 32) & 0xffffu);
             const int nsplit = (int)((d >> 48) & 0xffu);
-            const uint16_t *txs = L.term_xs + tb;
+            const uint16_t *txs = (POS ? L.xterm : L.term_xs) + tb;
             uint64_t a64 = 0;
             for (int t = 0; t < nsplit; t++) {
                 const uint32_t xs = txs[t];
-                a64 += Xlo[xb + (xs & 0xffu)] * Slo[sb + (xs >> 8)];
+                a64 += Xlo[xb + term_xi<POS>(xs)] * Slo[sb + term_si<POS>(xs)];
             }
             const uint32_t beta = (uint32_t)((d >> 56) & 0x7fu);
             val = beta == 1 ? a64 : div_exact_small64(a64, beta);
         }
         const bool nz = val != 0;
         const uint32_t gm = (uint32_t)(__ballot(nz) >> (g * CGL)) & 0xffffu;
-        if (nz) {
+        if (A.P) {
+            if (run && o < Wh) sl[o] = val;
+            nsum += val;
+        } else if (nz) {
             const uint32_t pos = cnt + (uint32_t)__popc(gm & ((1u << s) - 1u));
             sk[pos] = okey[o];
             sl[pos] = val;
@@ -1608,7 +1930,7 @@ __global__ void __launch_bounds__(256) k_combine_classify(CombineArgs A, const i
             if (q >= 2) {
                 const uint64_t hd = A.lev[q].P.loc[v];
                 xwide |= h_wide<false>(hd);
-                N[q] = h_N<false>(A.lev[q], hd);
+                N[q] = A.lev[q].P.P ? A.lev[q].P.N[v] : h_N<false>(A.lev[q], hd);
             }
             if (A.M[q]) M[q] = A.M[q][v];
             mwide |= hi64(M[q]) != 0;
@@ -1628,7 +1950,7 @@ __global__ void __launch_bounds__(256) k_combine_classify(CombineArgs A, const i
             atomicOr(A.err, 1);
             A.meta[v] = 0;
             A.Nout[v] = 0;
-        } else if (U == 0) {
+        } else if (U == 0 && !A.P) {   // (a dense record's zeros are written by the combine)
             A.meta[v] = 0;
             A.Nout[v] = 0;
         } else {
@@ -1675,7 +1997,7 @@ __host__ __device__ inline int level_term_words(int k, int h)
 
 // persistent over the listed vertices: the LDS holds the level's term
 // descriptors (copied once), then each vertex's staging areas
-template <bool OWN, bool BACK = OWN>
+template <bool OWN, bool BACK, bool POS>
 __global__ void __launch_bounds__(WAVE) k_combine_wide(CombineArgs A, const int *wide_list, const int *wide_count)
 {
     extern __shared__ uint64_t sm[];
@@ -1684,38 +2006,77 @@ __global__ void __launch_bounds__(WAVE) k_combine_wide(CombineArgs A, const int 
     const DevLut &L = *A.L;
     const int tw = level_term_words(L.k, A.h);
     uint16_t *tx = (uint16_t *)sm;
-    const uint16_t *src = L.term_xs + L.term_base[A.h][1];
+    const uint16_t *src = (POS ? L.xterm : L.term_xs) + L.term_base[A.h][1];
     for (int i = threadIdx.x; i < tw * 4; i += WAVE) tx[i] = src[i];
     uint64_t *lo = sm + tw;
     const int lo_words = L.xoff[A.h] + L.soff[A.h];
     __syncthreads();
     for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
         const int v = __builtin_amdgcn_readfirstlane(BACK ? wide_list[A.g.n - 1 - i] : wide_list[i]);
-        combine_vertex_pf<false, SCC_KMAX - 1, true, true>(A, v, lo, lo + lo_words, nullptr, nullptr, OWN, tx);
+        combine_vertex_pf<false, SCC_KMAX - 1, true, true, POS>(A, v, lo, lo + lo_words, nullptr, nullptr, OWN, tx);
         __syncthreads();
     }
 }
 
-// stored entries and 128-bit vertices of a level
-__global__ void __launch_bounds__(256) k_meta_sum(int64_t n, const uint32_t *meta, unsigned long long *out)
+// A finished level in numbers: stored entries, 128-bit vertices, the largest level
+// sum N (2^64 - 1 from there on), and the degrees of the vertices whose N has a
+// high word, summed (the rows of the next gather that need 128-bit sums are at
+// least their neighbours): out[0..3]
+struct LevelStats { uint64_t nnz, wide, max_n, heavy; };
+__global__ void __launch_bounds__(256) k_level_stats(GraphView g, const uint32_t *meta, const u128 *N,
+                                                     unsigned long long *out)
 {
-    __shared__ uint64_t part[2][256 / WAVE];
-    uint64_t len = 0, wide = 0;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
+    __shared__ uint64_t part[4][256 / WAVE];
+    uint64_t x[4] = {0, 0, 0, 0};
+    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < g.n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t m = meta[v];
-        len += META_LEN(m);
-        wide += META_WIDE(m);
+        const u128 nv = N[v];
+        x[0] += META_LEN(m);
+        x[1] += META_WIDE(m);
+        x[2] = max(x[2], hi64(nv) ? ~0ull : lo64(nv));
+        if (hi64(nv)) x[3] += (uint64_t)(g.row_ptr[v + 1] - g.row_ptr[v]);
     }
-    len = wave_sum64(len);
-    wide = wave_sum64(wide);
-    if (lane_id() == 0) { part[0][threadIdx.x / WAVE] = len; part[1][threadIdx.x / WAVE] = wide; }
+    for (int o = WAVE / 2; o >= 1; o >>= 1) x[2] = max(x[2], shfl64(x[2], lane_id() ^ o));
+    x[0] = wave_sum64(x[0]);
+    x[1] = wave_sum64(x[1]);
+    x[3] = wave_sum64(x[3]);
+    if (lane_id() == 0)
+        for (int j = 0; j < 4; j++) part[j][threadIdx.x / WAVE] = x[j];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t a = 0, b = 0;
-        for (int w = 0; w < 256 / WAVE; w++) { a += part[0][w]; b += part[1][w]; }
-        if (a) atomicAdd(&out[0], (unsigned long long)a);
-        if (b) atomicAdd(&out[1], (unsigned long long)b);
+    if (threadIdx.x < 4) {
+        const int j = threadIdx.x;
+        uint64_t a = part[j][0];
+        for (int w = 1; w < 256 / WAVE; w++) a = j == 2 ? max(a, part[j][w]) : a + part[j][w];
+        if (a && j == 2) atomicMax(&out[j], (unsigned long long)a);
+        else if (a) atomicAdd(&out[j], (unsigned long long)a);
     }
+}
+
+// Locators of a dense level: the stored entries, the 128-bit flag and, for a
+// 128-bit vertex, its row of high words (its own number, or, compact, the next
+// free one, listed in rows)
+__global__ void __launch_bounds__(256) k_dense_loc(int64_t n, const uint32_t *meta, int compact, int *count,
+                                                   int32_t *rows, uint64_t *loc)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t m = v < n ? meta[v] : 0u;
+    const bool wide = META_WIDE(m) != 0;
+    uint64_t row = (uint64_t)(v < n ? v : 0);
+    if (compact) {
+        const uint64_t bw = __ballot(wide);
+        int at = 0;
+        if (lane_id() == 0 && bw) at = atomicAdd(count, __popcll(bw));
+        row = (uint64_t)(__shfl(at, 0) + __popcll(bw & lanemask_lt()));
+        if (wide) rows[row] = (int32_t)v;
+    }
+    if (v < n) loc[v] = make_loc(wide ? row : 0, META_LEN(m), META_WIDE(m));
+}
+
+// high words of the listed vertices into compact rows
+__global__ void __launch_bounds__(WAVE) k_dense_hi(const int32_t *rows, int W, int P, const uint64_t *src, uint64_t *hi)
+{
+    const int64_t v = rows[blockIdx.x];
+    for (int i = threadIdx.x; i < W; i += WAVE) hi[(size_t)blockIdx.x * P + i] = src[(size_t)v * P + i];
 }
 
 // record size in 64-bit words
@@ -1905,6 +2266,53 @@ __global__ void __launch_bounds__(256) k_reduce_parts(const u128 *part, int nb, 
         u128 t = 0;
         for (int w = 0; w < 256 / WAVE; w++) t += ws[w];
         out[j] = t;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// A dense level's records in the sparse layout: sizes from the locators, then one
+// wave per vertex compacts the non-zero counts in output (ascending key) order.
+// ---------------------------------------------------------------------------
+__global__ void k_loc_words(int64_t n, const uint64_t *loc, uint64_t *words)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v < n) words[v] = rec_words(LOC_LEN(loc[v]) | LOC_WIDE(loc[v]) << 31);
+}
+
+__global__ void __launch_bounds__(WAVE) k_dense_to_sparse(LevelView V, const DevLut *Lp, int h, const uint8_t *colors,
+                                                          const uint64_t *incl, uint64_t *pool, uint64_t *loc,
+                                                          uint64_t *bm, int BW)
+{
+    const DevLut &L = *Lp;
+    const int lane = threadIdx.x;
+    const int64_t v = blockIdx.x;
+    const uint64_t l = V.loc[v];
+    const uint32_t len = LOC_LEN(l), wide = LOC_WIDE(l), kw = key_words(len);
+    const uint64_t start = incl[v] - rec_words(len | wide << 31);
+    if (lane == 0) loc[v] = make_loc(start, len, wide);
+    uint64_t *p = pool + start;
+    uint16_t *keys = (uint16_t *)(p + REC_HDR);
+    uint64_t *lo = p + REC_HDR + kw, *hi = lo + len;
+    if (len) {
+        if (lane == 0) p[0] = lo64(V.N[v]);
+        if (lane == 1) p[1] = hi64(V.N[v]);
+        if (lane < (int)(kw * 4 - len)) keys[len + lane] = 0;
+    }
+    const uint32_t ob = L.out_off[h];
+    const uint16_t *okey = L.out_key[colors[v]] + ob;
+    uint32_t cnt = 0;
+    for (int o0 = 0; o0 < L.W[h]; o0 += WAVE) {
+        const int o = o0 + lane;
+        const u128 c = len && o < L.W[h] ? dense_cnt(V, v, L.xpos[ob + o]) : (u128)0;
+        const uint64_t bal = __ballot(c != 0);
+        if (lane == 0) bm[(size_t)v * BW + (o0 >> 6)] = bal;
+        if (c != 0) {
+            const uint32_t e = cnt + (uint32_t)__popcll(bal & lanemask_lt());
+            keys[e] = okey[o];
+            lo[e] = lo64(c);
+            if (wide) hi[e] = hi64(c);
+        }
+        cnt += (uint32_t)__popcll(bal);
     }
 }
 
@@ -2208,10 +2616,7 @@ scc_status scan_incl(scc_table *T_, const T *in, T *out, int64_t n)
 // dispatcher balance them)
 unsigned grid_of(int64_t n) { return (unsigned)std::min<int64_t>(n, 256 * 80); }
 
-LevelView view(const TableLevel &l)
-{
-    return LevelView{l.pool, l.loc, l.bm, l.BW, l.vlc ? 1 : 0};
-}
+LevelView view(const TableLevel &l) { return level_view(l); }
 
 LevelSrc packed_src(const TableLevel &l)
 {
@@ -2252,14 +2657,17 @@ __global__ void __launch_bounds__(256) k_combine_level2(CombineArgs A)
     const uint64_t *s1 = A.Slo[1] + (size_t)v * W;          // S_1 has W_2 = k - 1 entries
     const uint16_t *okey = L.out_key[cv] + L.out_off[2];
     uint16_t *sk = A.slot_key + (size_t)v * A.W;
-    uint64_t *sl = A.slot_lo + (size_t)v * A.W;
+    uint64_t *sl = A.slot_lo + (size_t)v * (A.P ? A.P : A.W);
     uint32_t cnt = 0;
     uint64_t sum = 0;
     for (int o = 0; o < W; o++) {
         const uint64_t c = s1[o];
+        if (A.P) sl[o] = c;   // level 2 keeps its sets in the order of S_1
         if (!c) continue;
-        sk[cnt] = okey[o];
-        sl[cnt] = c;
+        if (!A.P) {
+            sk[cnt] = okey[o];
+            sl[cnt] = c;
+        }
         cnt++;
         sum += c;
     }
@@ -2299,13 +2707,16 @@ __global__ void __launch_bounds__(256) k_combine_level3(CombineArgs A, int *wide
     }
     const uint32_t ob = L.out_off[3];
     const uint16_t *okey = L.out_key[cv] + ob;
+    const bool dense = A.P != 0;
+    const int stride = dense ? A.P : A.W;
     uint16_t *sk = A.slot_key + (size_t)v * A.W;
-    uint64_t *sl = A.slot_lo + (size_t)v * A.W;
-    uint64_t *sh = A.slot_hi + (size_t)v * A.W;
+    uint64_t *sl = A.slot_lo + (size_t)v * stride;
+    uint64_t *sh = A.slot_hi + (size_t)v * stride;
     uint32_t cnt = 0;
     u128 nsum = 0;
     for (int o = 0; o < L.W[3]; o++) {
-        const uint64_t d = L.out[ob + o];
+        // own levels 1 and 2 are staged alike by index and by position (one shape each)
+        const uint64_t d = dense ? L.outd[ob + o] : L.out[ob + o];
         const int xb = (int)(d & 0xffffu), sb = (int)((d >> 16) & 0xffffu), tb = (int)((d >> 32) & 0xffffu);
         const int nsplit = (int)((d >> 48) & 0xffu);
         const uint32_t beta = (uint32_t)((d >> 56) & 0x7fu);
@@ -2318,10 +2729,16 @@ __global__ void __launch_bounds__(256) k_combine_level3(CombineArgs A, int *wide
             acc += (u128)x * sv;
         }
         const u128 val = beta == 1 ? acc : div_exact_small(acc, beta);
+        if (dense) {
+            sl[o] = lo64(val);
+            if (owide) sh[o] = hi64(val);
+        }
         if (val == 0) continue;
-        sk[cnt] = okey[o];
-        sl[cnt] = lo64(val);
-        if (owide) sh[cnt] = hi64(val);
+        if (!dense) {
+            sk[cnt] = okey[o];
+            sl[cnt] = lo64(val);
+            if (owide) sh[cnt] = hi64(val);
+        }
         cnt++;
         nsum += val;
     }
@@ -2329,17 +2746,27 @@ __global__ void __launch_bounds__(256) k_combine_level3(CombineArgs A, int *wide
     A.Nout[v] = nsum;
 }
 
-template <int PMAX>
-static void launch_combine(const CombineArgs &C, int64_t n, const int32_t *rows, int64_t nrows, size_t lds,
-                           hipStream_t st, int *wide_list, int *wide_count)
+template <int PMAX, bool POS>
+static void launch_combine_as(const CombineArgs &C, int64_t n, const int32_t *rows, int64_t nrows, size_t lds,
+                              hipStream_t st, int *wide_list, int *wide_count)
 {
     if (rows) {
         if (nrows)
-            hipLaunchKernelGGL(k_combine_list<PMAX>, dim3((unsigned)nrows), dim3(WAVE), lds, st, C, rows, wide_list,
+            hipLaunchKernelGGL((k_combine_list<PMAX, POS>), dim3((unsigned)nrows), dim3(WAVE), lds, st, C, rows, wide_list,
                                wide_count);
     } else {
-        hipLaunchKernelGGL(k_combine<PMAX>, dim3((unsigned)n), dim3(WAVE), lds, st, C, wide_list, wide_count);
+        hipLaunchKernelGGL((k_combine<PMAX, POS>), dim3((unsigned)n), dim3(WAVE), lds, st, C, wide_list, wide_count);
     }
+}
+
+// phi: the highest own level and sum level that the combine reads
+static void launch_combine(const CombineArgs &C, int phi, bool pos, int64_t n, const int32_t *rows, int64_t nrows,
+                           size_t lds, hipStream_t st, int *wide_list, int *wide_count)
+{
+    auto go = [&](auto f) { f(C, n, rows, nrows, lds, st, wide_list, wide_count); };
+    if (phi <= 3) pos ? go(launch_combine_as<3, true>) : go(launch_combine_as<3, false>);
+    else if (phi <= 5) pos ? go(launch_combine_as<5, true>) : go(launch_combine_as<5, false>);
+    else pos ? go(launch_combine_as<SCC_KMAX - 1, true>) : go(launch_combine_as<SCC_KMAX - 1, false>);
 }
 
 static scc_status build_levels(scc_table *T)
@@ -2366,8 +2793,9 @@ static scc_status build_levels(scc_table *T)
     // queued is safe: the allocator hooks free in the table's stream order
     // (hipFree, without hooks, waits for the device).
     // [0] flags; [1], [3] combine lists; [2] gather's wide rows; [4..5] pool size;
-    // [6], [7] combine lists; [8..9] heavy degree (u64); [10] gather's narrow rows
-    int *err = (int *)T->mem.get(64);
+    // [6], [7] combine lists; [8] rows of high words of a dense level; [10] gather's
+    // narrow rows; bytes 64..95 the level's LevelStats
+    int *err = (int *)T->mem.get(128);
     std::vector<void *> scratch{err};
     struct Guard {
         scc_table *T; std::vector<void *> *s;
@@ -2403,7 +2831,7 @@ static scc_status build_levels(scc_table *T)
 
     // hub rows and their neighbour chunks, and the rows between the grouped
     // low-degree ones and the hubs (the same for every level)
-    int nhub = 0, nmid = 0, nzero = 0;
+    int nhub = 0, nmid = 0, nzero = 0, max_deg = 0;
     int64_t low_rows = 0;
     int32_t *hubs = nullptr, *mids = nullptr, *zrows = nullptr;
     int32_t *chunk_v = nullptr, *chunk_q = nullptr;
@@ -2415,17 +2843,19 @@ static scc_status build_levels(scc_table *T)
         mids = (int32_t *)get((size_t)n * 4 + 8);
         zrows = (int32_t *)get((size_t)n * 4 + 8);
         if (!hubs || !mids || !zrows) return set_error(SCC_ENOMEM, "row lists");
-        HIP_TRY(hipMemsetAsync(err, 0, 16, st));
+        HIP_TRY(hipMemsetAsync(err, 0, 32, st));
         hipLaunchKernelGGL(k_row_lists, dim3((unsigned)((n + ROW_LIST_T - 1) / ROW_LIST_T)), dim3(ROW_LIST_T), 0, st, g,
                            hub_degree, hubs, mids, zrows, err);
-        int cnt[4] = {0, 0, 0, 0};
-        HIP_TRY(hipMemcpyAsync(cnt, err, 16, hipMemcpyDeviceToHost, st));
+        int cnt[5] = {0, 0, 0, 0, 0};
+        HIP_TRY(hipMemcpyAsync(cnt, err, sizeof cnt, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         nhub = cnt[0];
         nmid = cnt[1];
         low_rows = cnt[2];
         nzero = cnt[3];
+        max_deg = cnt[4];
     }
+    if (scc_status se = enqueue_edge_colours(T)) return se;
     if (nhub) {
         std::vector<int32_t> hh(nhub);
         std::vector<int64_t> rp(2 * (size_t)nhub);
@@ -2491,26 +2921,21 @@ static scc_status build_levels(scc_table *T)
     if (!S1.lo || !S1.M) return set_error(SCC_ENOMEM, "level-1 sums");
     HIP_TRY(hipEventRecord(ev[1][0], st));
     if (n)
-        hipLaunchKernelGGL(k_gather1, dim3(grid_of((n + WAVE - 1) / WAVE)), dim3(WAVE), 0, st, g, k, S1.lo, S1.M,
+        hipLaunchKernelGGL(k_gather1, dim3(grid_of((n + WAVE - 1) / WAVE)), dim3(WAVE), 0, st, g, T->ecol, k, S1.lo, S1.M,
                            (int64_t)(nhub ? hub_degree : INT64_MAX));
     if (nhub)
-        hipLaunchKernelGGL(k_gather1_hub, dim3((unsigned)nchunk), dim3(WAVE), 0, st, g, k, chunk_v, chunk_e, T->hub_chunk,
+        hipLaunchKernelGGL(k_gather1_hub, dim3((unsigned)nchunk), dim3(WAVE), 0, st, g, T->ecol, k, chunk_v, chunk_e, T->hub_chunk,
                            S1.lo);
     if (fused) {
-        hipLaunchKernelGGL(k_hub_l1_blocks, dim3((unsigned)nchunk), dim3(WAVE), 0, st, g, k, hubs, chunk_e, chunk_q,
+        hipLaunchKernelGGL(k_hub_l1_blocks, dim3((unsigned)nchunk), dim3(WAVE), 0, st, g, T->ecol, k, hubs, chunk_e, chunk_q,
                            T->hub_pre, T->hub_poff);
         hipLaunchKernelGGL(k_hub_block_scan, dim3((unsigned)((int64_t)nhub * (k - 1))), dim3(WAVE), 0, st, g, hubs,
-                           k - 1, 1, 0, S1.M, T->hub_pre, T->hub_poff);
+                           k - 1, 1, 0, S1.M, T->hub_pre, T->hub_poff, 1, (uint64_t *)nullptr, (uint64_t *)nullptr,
+                           (const int32_t *)nullptr);
     }
     HIP_TRY(hipEventRecord(ev[1][1], st));
     T->gather_bytes[1] = (double)n * 8.0 + (double)T->nnz_g * 5.0 + (double)n * (k - 1) * 8.0;
 
-    // scratch slots for the combine, sized for the widest level
-    int maxW = 0;
-    for (int h = 2; h <= k; h++) maxW = std::max(maxW, HL.W[h]);
-    uint16_t *slot_key = (uint16_t *)get((size_t)n * maxW * 2 + 256);
-    uint64_t *slot_lo = (uint64_t *)get((size_t)n * maxW * 8 + 256);
-    uint64_t *slot_hi = (uint64_t *)get((size_t)n * maxW * 8 + 256);
     uint64_t *words = (uint64_t *)get((size_t)n * 8 + 256);
     uint32_t *meta = (uint32_t *)get((size_t)n * 4 + 256);
     u128 *Nsc = (u128 *)get((size_t)n * 16 + 256);
@@ -2519,17 +2944,97 @@ static scc_status build_levels(scc_table *T)
     // then the combine's 64-bit vertices (width test per lane) or the grouped
     // combine's vertices whose bound reaches 2^64
     int32_t *narrow = (int32_t *)get((size_t)n * 4 + 256);
-    if (!slot_key || !slot_lo || !slot_hi || !words || !meta || !Nsc || !wide_list || !narrow)
-        return set_error(SCC_ENOMEM, "combine scratch (%lld bytes)", (long long)n * maxW * 18);
+    if (!words || !meta || !Nsc || !wide_list || !narrow) return set_error(SCC_ENOMEM, "combine scratch");
+    // the slots of a level with sparse records, grown to the widest one met so far
+    uint16_t *slot_key = nullptr;
+    uint64_t *slot_lo = nullptr, *slot_hi = nullptr;
+    int slot_w = 0;
+    auto slots = [&](int W) -> bool {
+        if (W <= slot_w) return true;
+        for (void *p : {(void *)slot_key, (void *)slot_lo, (void *)slot_hi}) {
+            scratch.erase(std::remove(scratch.begin(), scratch.end(), p), scratch.end());
+            T->mem.put(p);   // stream-ordered
+        }
+        slot_w = W;
+        slot_key = (uint16_t *)get((size_t)n * W * 2 + 256);
+        slot_lo = (uint64_t *)get((size_t)n * W * 8 + 256);
+        slot_hi = (uint64_t *)get((size_t)n * W * 8 + 256);
+        return slot_key && slot_lo && slot_hi;
+    };
 
     int64_t heavy_prev = 0;   // sum of degrees of the vertices whose previous-level N has a high word
+    // the largest level sum N_h and neighbour-sum bound M_h any vertex can have
+    // (saturating): where they stay below 2^64 no high words are provided for
+    u128 max_n[SCC_KMAX + 1] = {0, 1}, max_m[SCC_KMAX + 1] = {0, (u128)max_deg};
+    // the previous level's density: a level is kept dense where at least half of the
+    // previous level's counts were non-zero (the density hardly changes from level
+    // to level). At one half a dense record takes 60 % more bytes than a sparse one,
+    // which the slots that a sparse level is first written to take as well, and the
+    // gather reads a third as much; below, memory decides. Level 2 (one line a
+    // vertex) is always dense.
+    double density = 1.0;
     for (int h = 2; h <= k; h++) {
         const bool last = h == k;
         int64_t top_wide_rows = 0;   // rows of the sums gathered now whose high words exist
         HIP_TRY(hipEventRecord(ev[h][0], st));
-        HIP_TRY(hipMemsetAsync(err, 0, 64, st));   // flags and the level's counts of listed rows
+        HIP_TRY(hipMemsetAsync(err, 0, 128, st));   // flags, the level's counts of listed rows, its statistics
         const int hs = h - 1;   // neighbour sums needed now
-        if (hs >= 2 && s_need[hs]) {
+        max_m[hs] = sat_mul(max_n[hs], (u128)max_deg);
+        if (hs >= 2 && s_need[hs] && T->lev[hs].P) {
+            TableSums &Sx = T->S[hs];
+            const TableLevel &Lx = T->lev[hs];
+            const size_t row_bytes = (size_t)HL.WS[hs] * 8;
+            Sx.M = (u128 *)T->alloc((size_t)n * 16 + 16);
+            Sx.lo = (uint64_t *)T->alloc((size_t)n * row_bytes + 8);
+            if (!Sx.M || !Sx.lo) return set_error(SCC_ENOMEM, "neighbour sums level %d (%zu bytes)", hs, (size_t)n * row_bytes);
+            DGatherArgs G{};
+            G.g = g; G.ecol = T->ecol; G.L = T->dlut;
+            G.hs = hs; G.rr = HL.r[hs]; G.P = Lx.P; G.WS = HL.WS[hs]; G.nq = HL.bk1[hs];
+            G.rows_zero = zero && h == k; G.hub_degree = hub_degree;
+            G.lo = Lx.pool; G.hi = Lx.hi; G.loc = Lx.loc; G.N = Lx.N; G.M = Sx.M; G.Slo = Sx.lo;
+            G.chunk_v = chunk_v; G.chunk_e = chunk_e; G.chunk_q = chunk_q; G.err = err;
+            if (fused) { G.hub_pre = T->hub_pre; G.hub_poff = T->hub_poff; }
+            HIP_TRY(hipEventRecord(gev[hs][0], st));
+            const bool w128 = hi64(max_m[hs]) != 0;   // some row's bound may reach 2^64
+            if (w128) {
+                Sx.hrow = (int32_t *)T->alloc((size_t)n * 4 + 8);
+                if (!Sx.hrow) return set_error(SCC_ENOMEM, "neighbour sums level %d", hs);
+                T->sorted_sum_rows |= 1 << hs;
+                hipLaunchKernelGGL(k_row_bounds, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g, hub_degree,
+                                   G.rows_zero, Lx.N, Sx.M, Sx.hrow, nhub, err + 2);
+                if (nhub)
+                    hipLaunchKernelGGL(k_set_rows, dim3((unsigned)((nhub + 255) / 256)), dim3(256), 0, st, Sx.hrow, hubs,
+                                       (const int *)nullptr, (int64_t)nhub, 0);
+                int nw = 0;
+                HIP_TRY(hipMemcpyAsync(&nw, err + 2, 4, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipStreamSynchronize(st));
+                top_wide_rows = (int64_t)nw + nhub;
+                Sx.hi_rows = top_wide_rows;
+                Sx.hi = (uint64_t *)T->alloc((size_t)Sx.hi_rows * row_bytes + 8);
+                if (!Sx.hi) return set_error(SCC_ENOMEM, "neighbour sums level %d, high words", hs);
+                G.bounded = 1; G.Shi = Sx.hi; G.hrow = Sx.hrow;
+            }
+            const DGatherKernels K = w128 ? dgather_kernels<true>(G.WS) : dgather_kernels<false>(G.WS);
+            const int32_t *rows = G.rows_zero ? zrows : nullptr;
+            const int64_t nrows = G.rows_zero ? nzero : n;
+            if (nrows && K.group && T->gather_mode != SCC_GATHER_ROW) {
+                // short rows several to a wave, the others one per wave
+                if (nmid) hipLaunchKernelGGL(K.row, dim3((unsigned)nmid), dim3(WAVE), 0, st, G, mids);
+                const int per = WAVE / K.gw;
+                hipLaunchKernelGGL(K.group, dim3((unsigned)((nrows + per - 1) / per)), dim3(WAVE), 0, st, G, rows, nrows);
+            } else if (nrows) {
+                hipLaunchKernelGGL(K.row, dim3((unsigned)nrows), dim3(WAVE), 0, st, G, rows);
+            }
+            if (nhub) {
+                hipLaunchKernelGGL(k_dhub_prepare, dim3((unsigned)nhub), dim3(WAVE), 0, st, G, hubs, fused ? 0 : 1);
+                hipLaunchKernelGGL(K.hub, dim3((unsigned)nchunk), dim3(WAVE), 0, st, G, T->hub_chunk);
+                if (fused)
+                    hipLaunchKernelGGL(k_hub_block_scan, dim3((unsigned)((int64_t)nhub * HL.WS[hs])), dim3(WAVE), 0, st, g,
+                                       hubs, HL.WS[hs], hs, G.rows_zero, Sx.M, T->hub_pre, T->hub_poff, w128 ? 1 : 0,
+                                       Sx.lo, Sx.hi, Sx.hrow);
+            }
+            HIP_TRY(hipEventRecord(gev[hs][1], st));
+        } else if (hs >= 2 && s_need[hs]) {
             TableSums &Sx = T->S[hs];
             const size_t sz = (size_t)n * HL.WS[hs] * 8;
             Sx.M = (u128 *)T->alloc((size_t)n * 16 + 16);
@@ -2610,14 +3115,29 @@ static scc_status build_levels(scc_table *T)
             // the sampler's hub running sums of this level (not part of the gather)
             if (fused)
                 hipLaunchKernelGGL(k_hub_block_scan, dim3((unsigned)((int64_t)nhub * HL.WS[hs])), dim3(WAVE), 0, st, g,
-                                   hubs, HL.WS[hs], hs, G.rows_zero, Sx.M, T->hub_pre, T->hub_poff);
+                                   hubs, HL.WS[hs], hs, G.rows_zero, Sx.M, T->hub_pre, T->hub_poff, 1,
+                                   (uint64_t *)nullptr, (uint64_t *)nullptr, (const int32_t *)nullptr);
         }
         // combine into slots: a vertex needing 128 bits waits for the second kernel
         TableLevel &Lv = T->lev[h];
         Lv.loc = (uint64_t *)T->alloc((size_t)n * 8 + 8);
         if (!Lv.loc) return set_error(SCC_ENOMEM, "level %d locators", h);
         const bool skipped = bal && h == k - 1;
-        if (!skipped) {
+        const bool dense = !skipped && h < k && density >= 0.5;
+        // high words of a dense level before its 128-bit vertices are counted, a row per vertex
+        uint64_t *dense_hi = nullptr;
+        struct PutHi { scc_table *T; uint64_t *&p; ~PutHi() { T->mem.put(p); } } put_hi{T, dense_hi};
+        u128 max_u = 0;   // bounds every vertex's U of this level
+        for (int hp = 1; hp < h; hp++) max_u = sat_add(max_u, sat_mul(max_n[hp], max_m[h - hp]));
+        if (dense) {
+            Lv.P = HL.plane[h];
+            Lv.pool = (uint64_t *)T->alloc((size_t)n * Lv.P * 8 + 64);
+            Lv.N = (u128 *)T->alloc((size_t)n * 16 + 16);
+            if (hi64(max_u)) dense_hi = (uint64_t *)T->mem.get((size_t)n * Lv.P * 8 + 64);
+            if (!Lv.pool || !Lv.N || (hi64(max_u) && !dense_hi))
+                return set_error(SCC_ENOMEM, "level %d records (%lld bytes)", h, (long long)n * Lv.P * 8);
+        } else if (!skipped) {
+            if (!slots(HL.W[h])) return set_error(SCC_ENOMEM, "combine scratch (%lld bytes)", (long long)n * HL.W[h] * 18);
             // sized by the level's width alone: allocated while the GPU still works
             Lv.BW = (HL.W[h] + 63) / 64;
             Lv.bm = (uint64_t *)T->alloc((size_t)n * Lv.BW * 8 + 8);
@@ -2632,6 +3152,8 @@ static scc_status build_levels(scc_table *T)
             Lv.pool_words = 0;
             Lv.BW = 0;
             Lv.bm = nullptr;
+            Lv.nnz = Lv.wide = 0;
+            max_n[h] = 0;
             HIP_TRY(hipMemsetAsync(Lv.loc, 0, (size_t)n * 8 + 8, st));
             HIP_TRY(hipEventRecord(ev[h][1], st));
             continue;
@@ -2652,6 +3174,11 @@ static scc_status build_levels(scc_table *T)
         C.slot_key = slot_key; C.slot_lo = slot_lo; C.slot_hi = slot_hi;
         C.meta = meta; C.Nout = Nsc; C.err = err;
         C.bm = Lv.bm; C.BW = Lv.BW;
+        if (dense) {
+            C.P = Lv.P;
+            C.slot_key = nullptr; C.slot_lo = Lv.pool; C.slot_hi = dense_hi;
+            C.Nout = Lv.N;
+        }
         const size_t lds = (size_t)(HL.xoff[h] + HL.soff[h]) * 8;
         if (n) {
             // level k under zero-rooting: only the colour-0 vertices have records
@@ -2661,6 +3188,8 @@ static scc_status build_levels(scc_table *T)
                 HIP_TRY(hipMemsetAsync(Nsc, 0, (size_t)n * 16, st));
             }
             const int phi = C.bal ? h - 2 : h - 1;
+            bool pos = true;   // every own level read has dense records
+            for (int q = 2; q <= phi; q++) pos = pos && T->lev[q].P > 0;
             const bool classified = h >= 4 && (T->width_test == SCC_WIDTH_PER_LANE ||
                                                (T->width_test == SCC_WIDTH_AUTO && C.late_dma));
             // at most 64 outputs per vertex: four vertices per wave
@@ -2678,36 +3207,28 @@ static scc_status build_levels(scc_table *T)
                 HIP_TRY(hipStreamSynchronize(st));
                 CombineArgs Cn = C;
                 Cn.late_dma = 0;
-                if (phi <= 3) launch_combine<3>(Cn, n, narrow, nn, lds, st, wide_list, err + 1);
-                else if (phi <= 5) launch_combine<5>(Cn, n, narrow, nn, lds, st, wide_list, err + 1);
-                else launch_combine<SCC_KMAX - 1>(Cn, n, narrow, nn, lds, st, wide_list, err + 1);
+                launch_combine(Cn, phi, pos, n, narrow, nn, lds, st, wide_list, err + 1);
             } else if (grouped) {
                 T->grouped_combine |= 1 << h;
                 const int64_t nr = zl ? nzero : n;
                 const size_t lds_g = (size_t)(WAVE / CGL) * (HL.xoff[h] + HL.soff[h]) * 8;
                 if (nr) {
                     const dim3 grid((unsigned)((nr + WAVE / CGL - 1) / (WAVE / CGL)));
-                    if (phi <= 3)
-                        hipLaunchKernelGGL(k_combine_group<3>, grid, dim3(WAVE), lds_g, st, C, zl ? zrows : nullptr, nr,
-                                           narrow, err + 1);
-                    else
-                        hipLaunchKernelGGL(k_combine_group<5>, grid, dim3(WAVE), lds_g, st, C, zl ? zrows : nullptr, nr,
-                                           narrow, err + 1);
+                    const auto kg = phi <= 3 ? (pos ? k_combine_group<3, true> : k_combine_group<3, false>)
+                                             : (pos ? k_combine_group<5, true> : k_combine_group<5, false>);
+                    hipLaunchKernelGGL(kg, grid, dim3(WAVE), lds_g, st, C, zl ? zrows : nullptr, nr, narrow, err + 1);
                 }
                 // the vertices whose bound reaches 2^64, one per wave
                 int nf = 0;
                 HIP_TRY(hipMemcpyAsync(&nf, err + 6, 4, hipMemcpyDeviceToHost, st));
                 HIP_TRY(hipStreamSynchronize(st));
-                if (phi <= 3) launch_combine<3>(C, n, narrow, nf, lds, st, wide_list, err + 1);
-                else launch_combine<5>(C, n, narrow, nf, lds, st, wide_list, err + 1);
+                launch_combine(C, phi, pos, n, narrow, nf, lds, st, wide_list, err + 1);
             } else if (h == 2 && !zl && !C.bal)
                 hipLaunchKernelGGL(k_combine_level2, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C);
             else if (h == 3 && !zl && !C.bal)
                 hipLaunchKernelGGL(k_combine_level3, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C, wide_list,
                                    err + 1);
-            else if (phi <= 3) launch_combine<3>(C, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
-            else if (phi <= 5) launch_combine<5>(C, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
-            else launch_combine<SCC_KMAX - 1>(C, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
+            else launch_combine(C, phi, pos, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
             // the 128-bit vertices (at k = 8 most of level 7, nearly all with high
             // words in neighbour sums only) stride over as many waves as each
             // kernel's LDS staging lets the chip hold
@@ -2716,12 +3237,15 @@ static scc_status build_levels(scc_table *T)
             const size_t lds_s = (size_t)(HL.xoff[h] + 2 * HL.soff[h]) * 8 + ltw, lds_o = 2 * lds + ltw;
             HIP_TRY(hipGetDevice(&dev));
             HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_s, k_combine_wide<false>, WAVE, lds_s));
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_own, k_combine_wide<true>, WAVE, lds_o));
+            const auto kw_s = pos ? k_combine_wide<false, false, true> : k_combine_wide<false, false, false>;
+            const auto kw_o = pos ? k_combine_wide<true, true, true> : k_combine_wide<true, true, false>;
+            const auto kw_t = pos ? k_combine_wide<false, true, true> : k_combine_wide<false, true, false>;
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_s, (const void *)kw_s, WAVE, lds_s));
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_own, (const void *)kw_o, WAVE, lds_o));
             const int64_t gs = std::min<int64_t>(n, std::max<int64_t>(1024, (int64_t)ncu * per_s));
             const int64_t go = std::min<int64_t>(n, std::max<int64_t>(1024, (int64_t)ncu * per_own));
-            hipLaunchKernelGGL(k_combine_wide<false>, dim3((unsigned)gs), dim3(WAVE), lds_s, st, C, wide_list, err + 1);
-            hipLaunchKernelGGL(k_combine_wide<true>, dim3((unsigned)go), dim3(WAVE), lds_o, st, C, wide_list, err + 3);
+            hipLaunchKernelGGL(kw_s, dim3((unsigned)gs), dim3(WAVE), lds_s, st, C, wide_list, err + 1);
+            hipLaunchKernelGGL(kw_o, dim3((unsigned)go), dim3(WAVE), lds_o, st, C, wide_list, err + 3);
             if (classified) {
                 // high words in the top-level sums only (listed at the back of narrow):
                 // the high-word area holds that level alone, so more waves fit per CU
@@ -2729,21 +3253,27 @@ static scc_status build_levels(scc_table *T)
                 Ct.hi_cap = HL.WS[phi];
                 const size_t lds_t = (size_t)(HL.xoff[h] + HL.soff[h] + HL.WS[phi]) * 8 + ltw;
                 int per_t = 0;
-                HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_t, (k_combine_wide<false, true>), WAVE, lds_t));
+                HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_t, (const void *)kw_t, WAVE, lds_t));
                 const int64_t gt = std::min<int64_t>(n, std::max<int64_t>(1024, (int64_t)ncu * per_t));
-                hipLaunchKernelGGL((k_combine_wide<false, true>), dim3((unsigned)gt), dim3(WAVE), lds_t, st, Ct,
+                hipLaunchKernelGGL(kw_t, dim3((unsigned)gt), dim3(WAVE), lds_t, st, Ct,
                                    (const int *)narrow, err + 7);
             }
         }
-        if (n && !last)
-            hipLaunchKernelGGL(k_heavy_degree, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0,
-                               st, g, Nsc, (unsigned long long *)(err + 8));
-        // record sizes and offsets; the pool size and the error flags in one read
-        if (n) hipLaunchKernelGGL(k_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, meta, words);
-        scc_status sst = scan_incl<uint64_t>(T, words, words, n);
-        if (sst) return sst;
-        struct { int f[4]; uint64_t total; int g[2]; uint64_t heavy; } hr{};   // the layout of err
-        if (n) HIP_TRY(hipMemcpyAsync(err + 4, words + (n - 1), 8, hipMemcpyDeviceToDevice, st));
+        if (n)
+            hipLaunchKernelGGL(k_level_stats, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0, st, g,
+                               meta, C.Nout, (unsigned long long *)(err + 16));
+        if (!dense) {
+            // record sizes and offsets; the pool size, the statistics and the error flags in one read
+            if (n) hipLaunchKernelGGL(k_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, meta, words);
+            scc_status sst = scan_incl<uint64_t>(T, words, words, n);
+            if (sst) return sst;
+            if (n) HIP_TRY(hipMemcpyAsync(err + 4, words + (n - 1), 8, hipMemcpyDeviceToDevice, st));
+        } else if (n && !dense_hi) {
+            hipLaunchKernelGGL(k_dense_loc, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, meta, 0, err + 8,
+                               (int32_t *)nullptr, Lv.loc);
+        }
+        struct { int f[4]; uint64_t total; int g[2]; int u[8]; LevelStats ls; } hr{};   // the layout of err
+        static_assert(sizeof hr == 96, "the layout of err");
         HIP_TRY(hipMemcpyAsync(&hr, err, sizeof hr, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         const int *herr = hr.f;
@@ -2752,10 +3282,39 @@ static scc_status build_levels(scc_table *T)
         if (herr[0] & 2) return set_error(SCC_EOVERFLOW, "a level-%d neighbour sum may exceed 128 bits", h);
         if (herr[0] & 4)
             return set_error(SCC_EDEVICE, "level %d: a vertex listed for the top-level 128-bit combine has more high words", h);
-        heavy_prev = (int64_t)hr.heavy;
+        heavy_prev = (int64_t)hr.ls.heavy;
         T->wide_input_rows[h][0] = herr[1];
         T->wide_input_rows[h][1] = hr.g[1];
         T->wide_input_rows[h][2] = herr[3];
+        Lv.nnz = (int64_t)hr.ls.nnz;
+        Lv.wide = (int64_t)hr.ls.wide;
+        max_n[h] = hr.ls.max_n == ~0ull ? ~(u128)0 : (u128)hr.ls.max_n;
+        density = n ? (double)Lv.nnz / ((double)n * HL.W[h]) : 1.0;
+        if (dense) {
+            Lv.pool_words = (uint64_t)n * Lv.P;
+            if (dense_hi) {
+                // most vertices in 128 bits: the rows stay where they are; else they move
+                // into as many rows as are used
+                const bool keep = 2 * Lv.wide > n;
+                if (keep) {
+                    T->adopt(dense_hi, (size_t)n * Lv.P * 8 + 64);
+                    Lv.hi = dense_hi;
+                    dense_hi = nullptr;
+                } else if (Lv.wide) {
+                    Lv.hi = (uint64_t *)T->alloc((size_t)Lv.wide * Lv.P * 8 + 64);
+                    if (!Lv.hi) return set_error(SCC_ENOMEM, "level %d high words", h);
+                }
+                Lv.pool_words += (uint64_t)(keep ? n : Lv.wide) * Lv.P;
+                hipLaunchKernelGGL(k_dense_loc, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, meta, keep ? 0 : 1,
+                                   err + 8, (int32_t *)wide_list, Lv.loc);
+                if (!keep && Lv.wide)
+                    hipLaunchKernelGGL(k_dense_hi, dim3((unsigned)Lv.wide), dim3(WAVE), 0, st, (const int32_t *)wide_list,
+                                       HL.W[h], Lv.P, dense_hi, Lv.hi);
+            }
+            HIP_TRY(hipEventRecord(ev[h][1], st));
+            HIP_TRY(hipGetLastError());
+            continue;
+        }
         Lv.pool_words = total;
         Lv.pool = (uint64_t *)T->alloc((size_t)total * 8 + 64);
         if (!Lv.pool) return set_error(SCC_ENOMEM, "level %d pool (%llu words)", h, (unsigned long long)total);
@@ -2770,8 +3329,6 @@ static scc_status build_levels(scc_table *T)
             else hipLaunchKernelGGL(k_pack<false>, dim3((unsigned)((n + 3) / 4)), dim3(WAVE), 0, st, P);
         }
         HIP_TRY(hipEventRecord(ev[h][1], st));
-        if (n) hipLaunchKernelGGL(k_meta_sum, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, st,
-                                  n, meta, (unsigned long long *)T->dsum + 2 * h);
         HIP_TRY(hipGetLastError());
     }
     if (fused) {
@@ -2899,7 +3456,7 @@ static scc_status totals_finish(scc_table *T)
     if (e != hipSuccess) return set_error(SCC_EDEVICE, "totals: %s", hipGetErrorString(e));
     const int k = T->k;
     const bool zero = T->rooting == SCC_ROOT_ZERO;
-    for (int lv = 2; lv <= k; lv++) {
+    for (int lv = 2; lv <= k && !T->level_stats; lv++) {
         T->lev[lv].nnz = (int64_t)h[2 * lv];
         T->lev[lv].wide = (int64_t)h[2 * lv + 1];
     }
@@ -2954,6 +3511,43 @@ static scc_status build_totals(scc_table *T)
     return SCC_OK;
 }
 
+// A dense level rewritten with sparse records and bitmaps, in T's memory.
+static scc_status sparse_from_dense(scc_table *T, int h)
+{
+    TableLevel &Lv = T->lev[h];
+    const int64_t n = T->n;
+    hipStream_t st = T->stream;
+    uint64_t *words = (uint64_t *)T->mem.get((size_t)n * 8 + 8);
+    if (!words) return set_error(SCC_ENOMEM, "record sizes");
+    struct Put { scc_table *T; uint64_t *w; ~Put() { T->mem.put(w); } } put{T, words};
+    if (n) hipLaunchKernelGGL(k_loc_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, Lv.loc, words);
+    scc_status s = scan_u64(T, words, words, n);
+    if (s) return s;
+    uint64_t total = 0;
+    if (n) HIP_TRY(hipMemcpyAsync(&total, words + (n - 1), 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    TableLevel to;
+    to.nnz = Lv.nnz; to.wide = Lv.wide;
+    to.pool_words = total;
+    to.BW = (T->hlut.W[h] + 63) / 64;
+    to.pool = (uint64_t *)T->alloc((size_t)total * 8 + 64);
+    to.loc = (uint64_t *)T->alloc((size_t)n * 8 + 8);
+    to.bm = (uint64_t *)T->alloc((size_t)n * to.BW * 8 + 8);
+    if (!to.pool || !to.loc || !to.bm) return set_error(SCC_ENOMEM, "level %d sparse records (%llu words)", h,
+                                                        (unsigned long long)total);
+    if (n) hipLaunchKernelGGL(k_dense_to_sparse, dim3((unsigned)n), dim3(WAVE), 0, st, view(Lv), T->dlut, h, T->colors,
+                              words, to.pool, to.loc, to.bm, to.BW);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(st));
+    const size_t plane = (size_t)Lv.P * 8;
+    T->release(Lv.pool, (size_t)n * plane + 64);
+    if (Lv.hi) T->release(Lv.hi, (Lv.pool_words - (uint64_t)n * Lv.P) * 8 + 64);
+    T->release(Lv.N, (size_t)n * 16 + 16);
+    T->release(Lv.loc, (size_t)n * 8 + 8);
+    Lv = to;
+    return SCC_OK;
+}
+
 // Re-encodes every stored level with variable-length counts (Sec. 3.3). The
 // sampler's running sums are prepared first, from the fixed layout; every
 // reader after this point goes through the layout-aware record view.
@@ -2966,6 +3560,10 @@ static scc_status compact_levels(scc_table *T)
     const unsigned grid = (unsigned)std::min<int64_t>(std::max<int64_t>(n, 1), 65536);
     for (int h = 2; h <= T->k; h++) {
         TableLevel &Lv = T->lev[h];
+        if (Lv.P) {
+            s = sparse_from_dense(T, h);
+            if (s) return s;
+        }
         uint64_t *words = (uint64_t *)T->mem.get((size_t)n * 8 + 8);
         if (!words) return set_error(SCC_ENOMEM, "record sizes");
         struct Put { scc_table *T; uint64_t *w; ~Put() { T->mem.put(w); } } put{T, words};
@@ -2997,10 +3595,10 @@ static scc_status make_key_maps(scc_table *T)
 {
     const DevLut &L = T->hlut;
     const int k = T->k;
-    // both maps live in the table's host copy, so that their uploads need no wait here
+    // the maps live in the table's host copy, so that their upload needs no wait here
     const size_t nk = (size_t)k * L.nkeys;
-    T->key_maps_host.assign(2 * nk, (int16_t)-1);
-    int16_t *sidx = T->key_maps_host.data(), *xidx = sidx + nk;
+    T->key_maps_host.assign(3 * nk, (int16_t)-1);
+    int16_t *sidx = T->key_maps_host.data(), *xidx = sidx + nk, *xpos = xidx + nk;
     for (int h = 1; h <= k; h++)
         for (int t = 0; t < L.r[h]; t++)
             for (int ci = 0; ci < L.bk[h]; ci++) {
@@ -3011,19 +3609,20 @@ static scc_status make_key_maps(scc_table *T)
                     if (C >> c & 1u) {
                         // own count at a colour-c vertex: compressed set of size h-1
                         xidx[(size_t)c * L.nkeys + key] = (int16_t)(t * L.bk1[h - 1] + L.colex_s[D]);
+                        xpos[(size_t)c * L.nkeys + key] = (int16_t)(L.setpos[h][D] * L.r[h] + t);
                     } else if (h <= k - 1) {
                         sidx[(size_t)c * L.nkeys + key] = (int16_t)(t * L.bk1[h] + L.colex_s[D]);
                     }
                 }
             }
-    T->key_sidx = (int16_t *)T->alloc(nk * 2);
-    T->key_xidx = (int16_t *)T->alloc(nk * 2);
+    T->key_sidx = (int16_t *)T->alloc(3 * nk * 2);
+    T->key_xidx = T->key_sidx ? T->key_sidx + nk : nullptr;
+    T->key_xpos = T->key_sidx ? T->key_xidx + nk : nullptr;
     T->dlut = (DevLut *)T->alloc(sizeof(DevLut));
     T->dsum = (uint64_t *)T->alloc(DSUM_WORDS * 8);
-    if (!T->key_sidx || !T->key_xidx || !T->dlut || !T->dsum) return set_error(SCC_ENOMEM, "lookup tables");
+    if (!T->key_sidx || !T->dlut || !T->dsum) return set_error(SCC_ENOMEM, "lookup tables");
     HIP_TRY(hipMemsetAsync(T->dsum, 0, DSUM_WORDS * 8, T->stream));
-    HIP_TRY(hipMemcpyAsync(T->key_sidx, sidx, nk * 2, hipMemcpyHostToDevice, T->stream));
-    HIP_TRY(hipMemcpyAsync(T->key_xidx, xidx, nk * 2, hipMemcpyHostToDevice, T->stream));
+    HIP_TRY(hipMemcpyAsync(T->key_sidx, sidx, 3 * nk * 2, hipMemcpyHostToDevice, T->stream));
     HIP_TRY(hipMemcpyAsync(T->dlut, &T->hlut, sizeof(DevLut), hipMemcpyHostToDevice, T->stream));
     return SCC_OK;
 }
@@ -3116,9 +3715,9 @@ extern "C" scc_status scc_build_table(const scc_csr *g, const uint8_t *colors, i
     scc_status s = attach_graph(T, g, colors);
     if (!s && !o.no_validate) s = validate_graph(T);
     if (!s) s = make_key_maps(T);
+    T->level_stats = true;
     if (!s) s = build_levels(T);
     if (!s) s = build_totals(T);
-    if (!s) T->lev[1].nnz = T->n;
     if (!s && o.vlc) s = compact_levels(T);
     if (s) { delete T; return s; }
     *out = T;
@@ -3273,9 +3872,9 @@ __device__ __attribute__((always_inline)) inline void batch_worker(BatchArgs B)
             switch (I.phase) {
             case BI_G1:
                 for (int64_t v0 = I.a; v0 < I.b; v0 += WAVE)
-                    for (uint64_t m = gather1_lanes(P.g, P.k, P.S1, P.M1, v0, min(I.b, v0 + WAVE), GATHER1_LANE_DEG); m;
+                    for (uint64_t m = gather1_lanes(P.g, nullptr, P.k, P.S1, P.M1, v0, min(I.b, v0 + WAVE), GATHER1_LANE_DEG); m;
                          m &= m - 1)
-                        gather1_vertex(P.g, P.k, P.S1, P.M1, v0 + (__ffsll((long long)m) - 1), cnt1);
+                        gather1_vertex(P.g, nullptr, P.k, P.S1, P.M1, v0 + (__ffsll((long long)m) - 1), cnt1);
                 break;
             case BI_COMBINE: {
                 // 64 vertices at a time; at level k under zero-rooting only the colour-0

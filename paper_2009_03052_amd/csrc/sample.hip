@@ -107,11 +107,12 @@ __device__ inline u128 draw_cached(const DrawCache &D, u128 N, uint64_t seed, ui
 __device__ inline u128 own_count_c(const SampleArgs &A, int h, int64_t x, int cx, uint32_t key)
 {
     if (h == 1) return (key == (uint32_t)cx) ? 1 : 0;   // key of ({.}, {c}) is c
-    const int li = A.key_xidx[(size_t)cx * A.nkeys + key];
-    if (li < 0) return 0;
-    // dense position li: its bitmap word, then the popcount of the words before
-    // it gives the entry; the locator goes out with the word
     const LevelView &L = A.lev[h];
+    const int li = (L.P ? A.key_xpos : A.key_xidx)[(size_t)cx * A.nkeys + key];
+    if (li < 0) return 0;
+    if (L.P) return dense_cnt(L, x, li);
+    // index li: its bitmap word, then the popcount of the words before it gives
+    // the entry; the locator goes out with the word
     const uint64_t *bw = L.bm + (size_t)x * L.BW;
     const int w = li >> 6;
     const uint64_t l = L.loc[x];
@@ -453,6 +454,7 @@ struct HubPreArgs {
     LevelView lev[SCC_KMAX + 1];
     const u128 *M[SCC_KMAX + 1];
     const int16_t *key_sidx;
+    const int16_t *key_xpos;
     const int32_t *hubs;
     const int64_t *hub_rows;     // [2 * nhub]
     const int64_t *poff;         // [nhub * (k+1)]
@@ -480,8 +482,8 @@ __device__ inline u128 block256_incl_scan(u128 x, u128 *ws)
 
 // one neighbour's record location, read once and reused for every entry
 struct NbrRec {
-    const uint64_t *rec;    // count words (low), after the keys
-    const uint64_t *bm;     // presence bitmap
+    const uint64_t *rec;    // count words (low), after the keys, or a dense record's
+    const uint64_t *bm;     // presence bitmap (a dense record's high words)
     uint32_t len;
     bool wide;
     int cu;
@@ -494,6 +496,14 @@ __device__ inline NbrRec nbr_load(const HubPreArgs &A, int hpp, int32_t u)
     r.cu = A.g.colors[u];
     if (hpp == 1) return r;
     const LevelView &L = A.lev[hpp];
+    if (L.P) {
+        const uint64_t l = L.loc[u];
+        r.len = LOC_LEN(l);
+        r.wide = LOC_WIDE(l) != 0;
+        r.rec = L.pool + (size_t)u * L.P;
+        r.bm = r.wide ? L.hi + (size_t)LOC_OFF(l) * L.P : nullptr;
+        return r;
+    }
     const Rec rr = rec_of(L, u);
     r.len = rr.len;
     r.wide = rr.wide;
@@ -505,8 +515,10 @@ __device__ inline NbrRec nbr_load(const HubPreArgs &A, int hpp, int32_t u)
 __device__ inline u128 nbr_count(const HubPreArgs &A, int hpp, const NbrRec &r, uint32_t key)
 {
     if (hpp == 1) return key == (uint32_t)r.cu ? 1 : 0;
-    const int li = A.key_xidx[(size_t)r.cu * A.nkeys + key];
+    const bool dense = A.lev[hpp].P != 0;
+    const int li = (dense ? A.key_xpos : A.key_xidx)[(size_t)r.cu * A.nkeys + key];
     if (li < 0 || !r.len) return 0;
+    if (dense) return mk128(r.rec[li], r.wide ? r.bm[li] : 0);
     const uint64_t word = r.bm[li >> 6];
     if (!((word >> (li & 63)) & 1ull)) return 0;
     uint32_t pos = (uint32_t)__popcll(word & ((1ull << (li & 63)) - 1ull));
@@ -616,11 +628,16 @@ __global__ void k_hub_index(const int32_t *hubs, int nhub, int32_t *index)
 }
 
 __global__ void k_occ(GraphView g, const DevLut *Lp, LevelView lev_h, int h, int64_t v, int32_t key,
-                      const u128 *eta, u128 *out)
+                      const int16_t *key_xpos, const u128 *eta, u128 *out)
 {
     if (threadIdx.x != 0) return;
     if (key < 0) { *out = eta[v]; return; }
     if (h == 1) { *out = ((uint32_t)key == g.colors[v]) ? 1 : 0; return; }
+    if (lev_h.P) {
+        const int li = key_xpos[(size_t)g.colors[v] * Lp->nkeys + key];
+        *out = li >= 0 ? dense_cnt(lev_h, v, li) : (u128)0;
+        return;
+    }
     *out = record_lookup(lev_h, v, (uint32_t)key);
 }
 
@@ -631,14 +648,14 @@ __global__ void k_len(int64_t n, const uint64_t *loc, int h1, const uint8_t *col
     len[v] = h1 ? 1 : LOC_LEN(loc[v]);
 }
 
-__global__ void __launch_bounds__(WAVE) k_export(int64_t n, LevelView Lv, int h1, const uint8_t *colors,
+__global__ void __launch_bounds__(WAVE) k_export(int64_t n, LevelView Lv, const DevLut *Lp, int h, const uint8_t *colors,
                                                  const uint64_t *incl, int64_t *off, uint16_t *key,
                                                  uint64_t *lo, uint64_t *hi)
 {
     const int64_t v = blockIdx.x;
     const int lane = threadIdx.x;
     const uint64_t end = incl[v];
-    if (h1) {
+    if (h == 1) {
         if (lane == 0) {
             off[v] = (int64_t)end - 1;
             if (v == n - 1) off[n] = (int64_t)end;
@@ -654,6 +671,25 @@ __global__ void __launch_bounds__(WAVE) k_export(int64_t n, LevelView Lv, int h1
         off[v] = (int64_t)start;
         if (v == n - 1) off[n] = (int64_t)end;
     }
+    if (Lv.P) {   // the non-zero counts in output (ascending key) order
+        const DevLut &L = *Lp;
+        const uint32_t ob = L.out_off[h];
+        const uint16_t *okey = L.out_key[colors[v]] + ob;
+        uint64_t at = start;
+        for (int o0 = 0; r.len && o0 < L.W[h]; o0 += WAVE) {
+            const int o = o0 + lane;
+            const u128 c = o < L.W[h] ? dense_cnt(Lv, v, L.xpos[ob + o]) : (u128)0;
+            const uint64_t bal = __ballot(c != 0);
+            if (c != 0) {
+                const uint64_t e = at + (uint64_t)__popcll(bal & lanemask_lt());
+                key[e] = okey[o];
+                lo[e] = lo64(c);
+                hi[e] = hi64(c);
+            }
+            at += (uint64_t)__popcll(bal);
+        }
+        return;
+    }
     for (uint32_t e = lane; e < r.len; e += WAVE) {
         key[start + e] = (uint16_t)r.key(e);
         lo[start + e] = r.lo(e);
@@ -661,7 +697,7 @@ __global__ void __launch_bounds__(WAVE) k_export(int64_t n, LevelView Lv, int h1
     }
 }
 
-LevelView lview(const TableLevel &l) { return LevelView{l.pool, l.loc, l.bm, l.BW, l.vlc ? 1 : 0}; }
+LevelView lview(const TableLevel &l) { return level_view(l); }
 
 }  // namespace
 
@@ -683,19 +719,28 @@ __global__ void k_edge_colours(const int32_t *col_idx, const uint8_t *colors, in
         if (e0 + j < nnz) ecol[e0 + j] = colors[col_idx[e0 + j]];
 }
 
-// The per-edge colours of the neighbour draw (nnz bytes, built once per table).
-static scc_status ensure_edge_colours(scc_table *T)
+scc_status enqueue_edge_colours(scc_table *T)
 {
-    std::lock_guard<std::mutex> g(T->hub_mu);
     if (T->ecol || T->nnz_g == 0) return SCC_OK;
     uint8_t *ec = (uint8_t *)T->alloc((size_t)T->nnz_g + 8);
     if (!ec) return set_error(SCC_ENOMEM, "edge colours (%lld bytes)", (long long)T->nnz_g);
     const int64_t nt = (T->nnz_g + 3) / 4;
     hipLaunchKernelGGL(k_edge_colours, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, T->stream, T->col_idx,
                        T->colors, T->nnz_g, ec);
-    HIP_TRY(hipStreamSynchronize(T->stream));
     HIP_TRY(hipGetLastError());
     T->ecol = ec;
+    return SCC_OK;
+}
+
+// The per-edge colours of the neighbour draw (nnz bytes), where the build did not
+// leave them (batched builds).
+static scc_status ensure_edge_colours(scc_table *T)
+{
+    std::lock_guard<std::mutex> g(T->hub_mu);
+    if (T->ecol || T->nnz_g == 0) return SCC_OK;
+    scc_status s = enqueue_edge_colours(T);
+    if (s) return s;
+    HIP_TRY(hipStreamSynchronize(T->stream));
     return SCC_OK;
 }
 
@@ -790,7 +835,7 @@ static scc_status ensure_hub_prefix(scc_table *T)
     HIP_TRY(hipMemcpyAsync(dce, ce.data(), ce.size() * 8, hipMemcpyHostToDevice, st));
     A.hubs = dhubs; A.hub_rows = drows; A.poff = T->hub_poff; A.pre = T->hub_pre;
     A.chunk_hub = dch; A.chunk_e = dce; A.chunk = CH; A.hub_first_chunk = dfirst;
-    A.key_xidx = T->key_xidx; A.part = dpart; A.part_stride = pstride;
+    A.key_xidx = T->key_xidx; A.key_xpos = T->key_xpos; A.part = dpart; A.part_stride = pstride;
     hipLaunchKernelGGL(k_hub_index, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, dhubs, nc, T->hub_index);
     hipLaunchKernelGGL(k_hubpre_chunk, dim3((unsigned)ch.size(), (unsigned)(k - 1)), dim3(256), 0, st, A);
     hipLaunchKernelGGL(k_hubpre_fix, dim3((unsigned)ch.size(), (unsigned)(k - 1)), dim3(256), 0, st, A);
@@ -903,7 +948,7 @@ static scc_status sampling_args(scc_table *T, int shape, SampleArgs *out)
     A.mode = mode;
     A.spre = T->bal_spre;
     A.stj = T->bal_stj;
-    A.key_xidx = T->key_xidx; A.nkeys = T->hlut.nkeys;
+    A.key_xidx = T->key_xidx; A.key_xpos = T->key_xpos; A.nkeys = T->hlut.nkeys;
     if (T->hub_count_pre) { A.hub_index = T->hub_index; A.hub_poff = T->hub_poff; A.hub_pre = T->hub_pre; }
     A.g = GraphView{T->n, T->row_ptr, T->col_idx, T->colors};
     A.L = T->dlut; A.k = T->k; A.shape = shape; A.zero = T->rooting == SCC_ROOT_ZERO;
@@ -1067,7 +1112,7 @@ extern "C" scc_status scc_occ(const scc_table *T, int64_t v, int32_t key, uint64
     u128 *d = (u128 *)const_cast<scc_table *>(T)->mem.get(16);
     if (!d) return set_error(SCC_ENOMEM, "occ");
     GraphView g{T->n, T->row_ptr, T->col_idx, T->colors};
-    hipLaunchKernelGGL(k_occ, dim3(1), dim3(WAVE), 0, T->stream, g, T->dlut, lview(T->lev[h]), h, v, key, T->eta, d);
+    hipLaunchKernelGGL(k_occ, dim3(1), dim3(WAVE), 0, T->stream, g, T->dlut, lview(T->lev[h]), h, v, key, T->key_xpos, T->eta, d);
     u128 r = 0;
     hipError_t e = hipMemcpyAsync(&r, d, 16, hipMemcpyDeviceToHost, T->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(T->stream);
@@ -1103,7 +1148,7 @@ extern "C" scc_status scc_export_level(const scc_table *tc, int h, int64_t *nnz_
     scc_status s = scan_u64(T, len, len, n);
     T->stream = keep;
     if (s) { T->mem.put(len); return s; }
-    hipLaunchKernelGGL(k_export, dim3((unsigned)n), dim3(WAVE), 0, st, n, lview(T->lev[h]), h == 1, T->colors, len,
+    hipLaunchKernelGGL(k_export, dim3((unsigned)n), dim3(WAVE), 0, st, n, lview(T->lev[h]), T->dlut, h, T->colors, len,
                        off, key, lo, hi);
     hipError_t e = hipStreamSynchronize(st);
     T->mem.put(len);

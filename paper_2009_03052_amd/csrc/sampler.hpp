@@ -13,7 +13,8 @@ struct SampleArgs {
     const uint64_t *Shi[SCC_KMAX + 1];
     const int32_t *Shrow[SCC_KMAX + 1];   // compact high-word rows, or null (one row per vertex)
     const u128 *M[SCC_KMAX + 1];
-    const int16_t *key_xidx;              // [k * nkeys] dense own position of a key, or -1
+    const int16_t *key_xidx;              // [k * nkeys] own index of a key (its bitmap position), or -1
+    const int16_t *key_xpos;              // [k * nkeys] its position in a dense record, or -1
     int nkeys;
     const int32_t *hub_index;             // [n] hub number or -1
     const int64_t *hub_poff;              // [nhub * (k+1)]

@@ -69,6 +69,25 @@ struct DevLut {
     uint64_t out[1400];
     uint16_t out_key[SCC_KMAX][1400];
     uint16_t term_xs[2200];
+    // Dense records (levels 2..k-1, see LevelView): a vertex's level-h counts by
+    // position, the colour sets D (size h-1, without the vertex's own colour) in the
+    // order of setpos[h], and within a set the r_h shapes by rank:
+    //   position = setpos[h][D] r_h + rank.
+    // Consecutive sets differ in one colour, so that the sets without a given colour,
+    // which are all that a neighbour of that colour reads, lie in few runs. plane[h] is
+    // the record's words, W_h rounded up to whole 64-byte lines.
+    uint8_t setpos[SCC_KMAX + 1][128];
+    int plane[SCC_KMAX + 2];
+    uint16_t xord[1400];        // [out_off[h] + position] -> output index o of level h
+    uint16_t xpos[1400];        // [out_off[h] + o] -> position
+    // out[] and term_xs[] for own counts staged by position: descriptor of the output
+    // at position i, and terms (setpos of D') r_h' | (colex rank of D'') << 9
+    uint64_t outd[1400];
+    uint16_t xterm[2200];
+    // the sums S_h seen from a colour-c vertex: byte c_u of gsel[h][c][q] is
+    // setpos[h] of the q-th h-set C (colex, without c) in the records of colour-c_u
+    // vertices, 0xff where c_u is not in C
+    uint64_t gsel[SCC_KMAX + 1][SCC_KMAX][35];
 };
 
 // Host-side treelet algebra (treelets.cpp).

@@ -18,7 +18,15 @@ struct TableLevel {
     uint64_t *bm = nullptr;     // [n * BW] presence bitmaps over the dense level layout
     int BW = 0;
     bool vlc = false;           // records in the variable-length layout
+    int P = 0;                  // dense records: words per plane (pool: n planes), else 0
+    uint64_t *hi = nullptr;     // dense: high words of the 128-bit vertices, or null
+    u128 *N = nullptr;          // dense: [n] level sums
 };
+
+inline LevelView level_view(const TableLevel &l)
+{
+    return LevelView{l.pool, l.loc, l.bm, l.BW, l.vlc ? 1 : 0, l.P, l.hi, l.N};
+}
 
 struct TableSums {
     uint64_t *lo = nullptr;     // [n * WS_h]
@@ -40,6 +48,7 @@ struct scc_table {
     DevLut *dlut = nullptr;          // device copy of hlut
     int16_t *key_sidx = nullptr;     // [k * nkeys] neighbour-sum index of a key seen from colour c, or -1
     int16_t *key_xidx = nullptr;     // [k * nkeys] own-count index of a key at a colour-c vertex, or -1
+    int16_t *key_xpos = nullptr;     // [k * nkeys] its position in a dense record, or -1
     TableLevel lev[SCC_KMAX + 1];
     TableSums S[SCC_KMAX + 1];
     u128 *eta = nullptr;             // [n] admissible level-k total per vertex (all shapes)
@@ -55,8 +64,10 @@ struct scc_table {
     const u128 **bal_spre = nullptr;
     u128 *bal_stj = nullptr;
     // device summary read once at the end of a build: [2h], [2h+1] = stored entries and
-    // 128-bit vertices of level h; then 32 u128 per-shape totals; then the root total
+    // 128-bit vertices of level h (batched builds; the level kernels read them level by
+    // level, level_stats); then 32 u128 per-shape totals; then the root total
     uint64_t *dsum = nullptr;
+    bool level_stats = false;
     std::map<int, u128 *> pre_shape; // per unrooted shape: running sums, built on demand
     std::map<int, u128> tot_shape;
     std::mutex mu;
@@ -79,7 +90,7 @@ struct scc_table {
     bool vlc = false;                // levels re-encoded with variable-length counts after the build
     int nhub = 0;
     bool stats_done = false;
-    std::vector<int16_t> key_maps_host;   // host copy of key_sidx then key_xidx (source of their uploads)
+    std::vector<int16_t> key_maps_host;   // host copy of key_sidx, key_xidx, key_xpos (source of their upload)
     std::vector<int32_t> hub_host;   // hub vertices (ascending) and their row bounds
     std::vector<int64_t> hub_rows_host;
     // per-hub running sums over neighbours of every neighbour-sum entry, for the
@@ -106,6 +117,12 @@ struct scc_table {
             bytes += (int64_t)bytes_;
         }
         return p;
+    }
+    // takes over a block got from mem
+    void adopt(void *p, size_t bytes_)
+    {
+        owned.push_back(p);
+        bytes += (int64_t)bytes_;
     }
     void release(void *p, size_t bytes_)
     {
@@ -140,5 +157,7 @@ scc_status table_prefix(scc_table *T, int shape, const u128 **pre, u128 *total);
 scc_status scan_u128(scc_table *T, const u128 *in, u128 *out, int64_t n);
 scc_status scan_u64(scc_table *T, const uint64_t *in, uint64_t *out, int64_t n);
 scc_status scan_u32(scc_table *T, const uint32_t *in, uint32_t *out, int64_t n);
+// the colour of every edge's head, unless the table has it (enqueued on T's stream)
+scc_status enqueue_edge_colours(scc_table *T);
 // admissible level-k totals of one unrooted shape per vertex (enqueued on T's stream)
 void launch_eta_shape(scc_table *T, int shape, u128 *eta);

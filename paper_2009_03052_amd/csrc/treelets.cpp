@@ -14,6 +14,7 @@
 #include <functional>
 #include <memory>
 #include <mutex>
+#include <vector>
 
 #include "scc_common.hpp"
 
@@ -178,6 +179,8 @@ int tree_unrooted_id(int k, const uint32_t *adjmask)
     return -1;
 }
 
+static void build_dense(int k, DevLut *L);
+
 void build_lut(int k, DevLut *L)
 {
     const HostShapes &S = host_shapes();
@@ -300,6 +303,68 @@ void build_lut(int k, DevLut *L)
             }
         }
     }
+    build_dense(k, L);
+}
+
+// Order of the m-subsets of [n] in which consecutive ones differ by exchanging one
+// element (the revolving-door order: the subsets without n, then those with it in
+// reverse order of the rest).
+static void revolving_door(int n, int m, std::vector<uint32_t> &out)
+{
+    out.clear();
+    if (m < 0 || m > n) return;
+    if (m == 0 || m == n) { out.push_back((1u << m) - 1u); return; }
+    std::vector<uint32_t> with;
+    revolving_door(n - 1, m, out);
+    revolving_door(n - 1, m - 1, with);
+    for (size_t i = with.size(); i-- > 0;) out.push_back(with[i] | 1u << (n - 1));
+}
+
+// the dense record layout of levels 2..k and the tables that follow from it
+static void build_dense(int k, DevLut *L)
+{
+    const uint32_t all = (1u << (k - 1)) - 1u;
+    std::vector<uint32_t> ord;
+    for (int h = 1; h <= k; h++) {
+        // by the complements, so that runs of sets without a colour are runs of
+        // complements that share it; level 2 keeps the order of S_1
+        revolving_door(k - 1, k - h, ord);
+        for (size_t i = 0; i < ord.size(); i++) {
+            const uint32_t D = all & ~ord[i];
+            L->setpos[h][D] = (uint8_t)(h == 2 ? L->colex_s[D] : i);
+        }
+        L->plane[h] = (L->W[h] + 7) / 8 * 8;
+    }
+    for (int h = 2; h <= k; h++)
+        for (int hp = 1; hp < h; hp++) {
+            const int n = binom(k - 1, h - 1) * binom(h - 1, hp - 1);
+            for (int i = L->term_base[h][hp]; i < L->term_base[h][hp] + n; i++) {
+                const uint32_t D = L->mask_s[hp - 1][L->term_x[i]];
+                L->xterm[i] = (uint16_t)(L->setpos[hp][D] * L->r[hp] | L->term_s[i] << 9);
+            }
+        }
+    for (int h = 2; h <= k; h++) {
+        const int nD = L->bk1[h - 1];
+        for (int o = 0; o < L->W[h]; o++) {
+            const int t = o / nD, dc = o - t * nD, hp = L->dec_hp[h][t];
+            const int pos = L->setpos[h][L->mask_s[h - 1][dc]] * L->r[h] + t;
+            const uint32_t at = L->out_off[h];
+            L->xpos[at + o] = (uint16_t)pos;
+            L->xord[at + pos] = (uint16_t)o;
+            L->outd[at + pos] = (L->out[at + o] & ~(uint64_t)0xffffu) | (uint64_t)(L->xoff[hp] + L->dec_a[h][t]);
+        }
+    }
+    for (int h = 2; h < k; h++)
+        for (int c = 0; c < k; c++)
+            for (int q = 0; q < L->bk1[h]; q++) {
+                const uint32_t C = expand_in(L->mask_s[h][q], c);
+                uint64_t w = 0;
+                for (int cu = 0; cu < SCC_KMAX; cu++) {
+                    const uint64_t b = cu < k && (C >> cu & 1u) ? L->setpos[h][compress_out(C & ~(1u << cu), cu)] : 0xffu;
+                    w |= b << (8 * cu);
+                }
+                L->gsel[h][c][q] = w;
+            }
 }
 
 // ---------------------------------------------------------------------------

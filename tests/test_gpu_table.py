@@ -344,3 +344,40 @@ def test_combine_bytes_match_their_definition(k, n, m):
         want = int(per_v[zero].sum()) if h == k else int(per_v.sum())
         assert cb[h] == want, h
     assert tb == int(10 * lens[k].sum() + 32 * g.n)
+
+
+def _hub_graph(hubs, leaves, deg, seed):
+    """`hubs` vertices adjacent to every leaf, and random edges of mean degree `deg` among the leaves."""
+    rng = np.random.default_rng(seed)
+    e = [np.stack([np.full(leaves, h), hubs + np.arange(leaves)], 1) for h in range(hubs)]
+    e.append(rng.integers(hubs, hubs + leaves, (leaves * deg // 2, 2)))
+    return gg.csr_from_edges(hubs + leaves, np.concatenate(e).astype(np.int64))
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("k,leaves,rooting", [(8, 1 << 15, O.ROOT_ZERO), (7, 1 << 16, O.ROOT_ALL)])
+def test_dense_levels_beyond_64_bits(k, leaves, rooting):
+    # most counts of every level are non-zero (dense records), the hubs' level
+    # sums pass 2^64 at level 6 and their counts at the last two levels, and every
+    # leaf borders a hub, so its sums need 128 bits there: rows one per wave and
+    # several to a wave, hub rows in blocks of the running sums, and hub rows
+    # taken whole; then the same table in the variable-length layout
+    S = scc()
+    g = _hub_graph(3, leaves, 8 if k == 8 else 6, seed=3)
+    colors = gg.colors(g.n, k, seed=5)
+    ot = O.Table(g, colors, k, rooting)
+    ov, op = ot.sample(1000, seed=3)
+    print("oracle table built and sampled", flush=True)
+    dg = S.DeviceGraph.from_graph(g)
+    for mode, hub_degree, width, vlc in [(0, 0, 0, False), (2, 1 << 20, 2, False), (1, 64, 1, False), (0, 0, 0, True)]:
+        gt = S.Table(dg, colors, k, rooting=rooting, gather_mode=mode, hub_degree=hub_degree, width_test=width, vlc=vlc)
+        info = gt.info()
+        assert info.wide_vertices[k - 1] > 0 and info.sorted_sum_rows >> (k - 1) & 1
+        assert_tables_equal(gt, ot, k, f"hubs mode {mode} hub>{hub_degree} width {width} vlc {vlc}")
+        gv, gp = gt.sample(1000, seed=3)
+        assert np.array_equal(gv.cpu().numpy(), ov) and np.array_equal(gp.cpu().numpy(), op), (mode, hub_degree, vlc)
+        off, key, lo, hi = ot.export_level(k - 1)
+        for v in (0, 1, 2, g.n - 1):
+            for e in range(int(off[v]), int(off[v + 1]), 37):
+                assert gt.occ(v, int(key[e])) == int(lo[e]) + (int(hi[e]) << 64)
+        print(f"mode {mode} hub>{hub_degree} width {width} vlc {vlc} equal", flush=True)
