@@ -381,3 +381,36 @@ def test_dense_levels_beyond_64_bits(k, leaves, rooting):
             for e in range(int(off[v]), int(off[v + 1]), 37):
                 assert gt.occ(v, int(key[e])) == int(lo[e]) + (int(hi[e]) << 64)
         print(f"mode {mode} hub>{hub_degree} width {width} vlc {vlc} equal", flush=True)
+
+
+@pytest.mark.parametrize("n,m", [(12, 30), (300, 2000), (4000, 3000)])
+def test_asymmetric_arcs_are_found(n, m):
+    # the symmetry check searches the arcs towards the vertex that comes first by
+    # (degree, id) and counts the others: one arc dropped, one moved to another
+    # head, and two moved so that the counts balance, towards both ends, at entries
+    # spread over the blocks; rows of no entry between them
+    S = scc()
+    g = gg.erdos_renyi(n, m, seed=n)
+    colors = gg.colors(n, 4, seed=1)
+    S.Table(S.DeviceGraph.from_graph(g), colors, 4)   # as it is: valid
+    rng = np.random.default_rng(m)
+    src = np.repeat(np.arange(n), np.diff(g.row_ptr))
+    arcs = set(zip(src.tolist(), g.col_idx.tolist()))
+
+    def refused(pairs):
+        e = np.array(sorted(pairs), np.int64)
+        rp = np.concatenate([[0], np.cumsum(np.bincount(e[:, 0], minlength=n))]).astype(np.int64)
+        with pytest.raises(S.SccError) as err:
+            S.Table(S.DeviceGraph(rp, e[:, 1].astype(np.int32)), colors, 4)
+        assert err.value.status == S.EINVAL
+
+    order = [sorted(arcs)[i] for i in rng.permutation(len(arcs))[:6]]
+    for v, u in order:
+        refused(arcs - {(v, u)})
+        w = next(w for w in rng.permutation(n).tolist() if w != v and (v, w) not in arcs)
+        refused(arcs - {(v, u)} | {(v, w)})
+        refused(arcs | {(v, w)})
+        # (v, u), (u, v) -> (v, w), (u, x): two arcs without a reverse, the same row lengths
+        x = next((x for x in rng.permutation(n).tolist() if x not in (u, v, w) and (u, x) not in arcs), None)
+        if x is not None:
+            refused(arcs - {(v, u), (u, v)} | {(v, w), (u, x)})
