@@ -5,20 +5,25 @@
 // order (vertices, record entries, colour sets, neighbours): the wave loads 64
 // items, forms their inclusive running sum with shuffles, and the first lane
 // whose running sum exceeds the drawn integer wins.
+//
+// What bounds it: each sample is a chain of dependent random loads, hidden by
+// eight waves per SIMD whose scalar and vector instructions take up about half of
+// the time (k = 8, per sample: 5000 vector instructions, 4000
+// scalar ones and 330 loads at first; 2540, 2990 and 123 now). So the draw reads
+// only what can be chosen: single-node T'' by counting colours with ballots, other
+// T'' at the neighbours whose colour is in C'' (queued 64 at a time), a T' of one
+// node without its stage 1, a vertex's row, colour, hub number and widths as one
+// pair of words kept while T' stays at it, a key's decomposition as one word; sums
+// below 2^64 are scanned in 64 bits. Kept small: rolled loops on rare paths took
+// the kernel's code from 100 KB to 26 KB and its spilled scalar registers from 326
+// to 45. 5*10^6 samples at k = 8 (2*10^6 vertices, 3*10^7 edges) 67.4 -> 39.2 ms;
+// 10^5 of one shape at k = 7 from variable-length counts 1.72 -> 1.25 ms; 1000 at
+// k = 6 58 -> 43 us.
 #include <cstring>
 
 #include "sampler.hpp"
 
 namespace {
-
-
-
-__device__ inline int key_level(const DevLut &L, uint32_t key)
-{
-    int h = 1;
-    while (h < L.k && (int)key >= L.off[h + 1]) h++;
-    return h;
-}
 
 // first lane (in order) whose inclusive running sum exceeds `target`; -1 if none
 __device__ inline int first_exceeding(u128 incl, u128 target)
@@ -33,32 +38,25 @@ __device__ inline int first_exceeding(u128 incl, u128 target)
 // shared by all samples and stay in cache); below 4096 entries only 8 lanes
 // probe (8-way split), which keeps the per-search traffic to a few cache lines.
 template <typename F>
-__device__ inline int64_t wave_search(int64_t len, u128 target, F val)
+__device__ inline int32_t wave_search(int32_t n, u128 target, F val)
 {
-    const int lane = lane_id();
-    int64_t lo = 0;
+    const uint32_t lane = (uint32_t)lane_id();
+    uint32_t lo = 0, len = (uint32_t)n;
     while (len > WAVE) {
-        const int ways = len > 4096 ? WAVE : 8;
-        const int64_t step = (len + ways - 1) / ways;
-        const int64_t last = lo + len - 1;
+        const uint32_t sh = len > 4096 ? 6 : 3;
+        const uint32_t step = (len + (1u << sh) - 1) >> sh;
         bool p = false;
-        if (lane < ways) {
-            int64_t idx = lo + (int64_t)(lane + 1) * step - 1;
-            if (idx > last) idx = last;
-            p = val(idx) > target;
-        }
+        if (lane < 1u << sh) p = val(lo + min((lane + 1) * step, len) - 1) > target;
         const uint64_t bal = __ballot(p);
         if (!bal) return -1;                                 // target not below the last value
-        const int f = __ffsll((long long)bal) - 1;
-        const int64_t nlo = lo + (int64_t)f * step;
-        const int64_t nhi = min(last, lo + (int64_t)(f + 1) * step - 1);
-        lo = nlo;
-        len = nhi - nlo + 1;
+        const uint32_t first = (uint32_t)(__ffsll((long long)bal) - 1) * step;
+        lo += first;
+        len = min(step, len - first);
     }
     const bool p = lane < len && val(lo + lane) > target;
     const uint64_t bal = __ballot(p);
     if (!bal) return -1;
-    return lo + (__ffsll((long long)bal) - 1);
+    return (int32_t)lo + (__ffsll((long long)bal) - 1);
 }
 
 // The draws of one sample, computed together: lane l holds the Philox block of
@@ -78,6 +76,25 @@ __device__ inline DrawCache draw_cache(uint64_t seed, uint64_t stream, uint64_t 
 }
 
 
+// the first two outputs of Philox4x64-10 (philox4x64_10) for counter (c0, c1, 0, 0)
+__device__ inline u128 philox_rolled(uint64_t c0, uint64_t c1, uint64_t k0, uint64_t k1)
+{
+    const uint64_t M0 = 0xD2E7470EE14C6C93ULL, M1 = 0xCA5A826395121157ULL;
+    const uint64_t W0 = 0x9E3779B97F4A7C15ULL, W1 = 0xBB67AE8584CAA73BULL;
+    uint64_t c2 = 0, c3 = 0;
+#pragma unroll 1
+    for (int r = 0; r < 10; r++) {
+        const u128 p0 = (u128)M0 * c0, p1 = (u128)M1 * c2;
+        c0 = hi64(p1) ^ c1 ^ k0;
+        c1 = lo64(p1);
+        c2 = hi64(p0) ^ c3 ^ k1;
+        c3 = lo64(p0);
+        k0 += W0;
+        k1 += W1;
+    }
+    return mk128(c0, c1);
+}
+
 // value of lane src (src uniform), as a scalar
 __device__ inline uint32_t readlane32(uint32_t x, int src) { return (uint32_t)__builtin_amdgcn_readlane((int)x, src); }
 __device__ inline u128 readlane128(u128 x, int src) { return mk128(readlane64(lo64(x), src), readlane64(hi64(x), src)); }
@@ -86,21 +103,30 @@ __device__ inline u128 draw_cached(const DrawCache &D, u128 N, uint64_t seed, ui
                                    uint32_t draw)
 {
     if (N <= 1) return 0;
-    if (draw >= 16) return draw_below(N, seed, stream, idx, draw);
-    const int bits = bitlen128(N - 1);
-    const u128 mask = bits >= 128 ? ~(u128)0 : (((u128)1 << bits) - 1);
-    for (uint32_t att = 0; att < 4; att++) {
-        const int src = (int)(draw + 16 * att);
-        const u128 x = mk128(readlane64(D.lo, src), readlane64(D.hi, src)) & mask;
-        if (x < N) return x;
+    // mask of the bit length of N - 1
+    const u128 m = N - 1;
+    const bool wide = hi64(m) != 0;
+    const uint64_t mlo = wide ? ~0ull : ~0ull >> __clzll((long long)lo64(m));
+    const uint64_t mhi = wide ? ~0ull >> __clzll((long long)hi64(m)) : 0ull;
+    if (draw < 16) {
+        // every lane tests its block; the draw's first attempt that is below N
+        const uint64_t xl = D.lo & mlo, xh = D.hi & mhi;
+        const bool ok = wide ? mk128(xl, xh) <= m : xl <= lo64(m);
+        const uint64_t bal = __ballot(ok) >> draw & 0x0001000100010001ull;
+        if (bal) {
+            const int src = (int)draw + __ffsll((long long)bal) - 1;
+            return mk128(readlane64(xl, src), wide ? readlane64(xh, src) : 0ull);
+        }
     }
-    for (uint32_t att = 4; att < 4096u; att++) {
-        uint64_t c[4] = {idx, ((uint64_t)draw << 32) | att, 0, 0};
-        philox4x64_10(c, seed, stream);
-        const u128 x = mk128(c[0], c[1]) & mask;
-        if (x < N) return x;
+    // (rolled: this is inlined at every draw, and the kernel's code has to stay
+    // within the instruction cache)
+#pragma unroll 1
+    for (uint32_t att = draw < 16 ? 4 : 0; att < 4096u; att++) {
+        const u128 y = philox_rolled(idx, ((uint64_t)draw << 32) | att, seed, stream);
+        const u128 x = mk128(lo64(y) & mlo, hi64(y) & mhi);
+        if (x <= m) return x;
     }
-    return N - 1;
+    return m;
 }
 
 // count of (T, C) with the given key at x (level h >= 1), x of colour cx
@@ -135,16 +161,6 @@ __device__ inline u128 own_count_c(const SampleArgs &A, int h, int64_t x, int cx
     r.p = L.pool + LOC_OFF(l);
     return r.cnt(pos);
 }
-__device__ inline u128 own_count(const SampleArgs &A, int h, int64_t x, uint32_t key)
-{
-    return own_count_c(A, h, x, A.g.colors[x], key);
-}
-// colour of the head of edge e (u = col_idx[e])
-__device__ inline int edge_colour(const SampleArgs &A, int64_t e, int32_t u)
-{
-    return A.ecol ? A.ecol[e] : A.g.colors[u];
-}
-
 // LDS of one wave's sample: the vertices found so far with their parents, and
 // the stack of pending decompositions (key, position of its root, count)
 struct SampleLds {
@@ -153,21 +169,127 @@ struct SampleLds {
     uint32_t st_key[2 * SCC_KMAX];
     int st_pos[2 * SCC_KMAX];
     u128 st_cnt[2 * SCC_KMAX];
+    uint32_t queue[2 * WAVE];   // neighbours whose colour is in C'', by offset in the row
 };
+
+// the small tables of a draw, copied once per workgroup: set positions in dense
+// records, colex ranks of (k-1)- and k-bit sets
+struct DrawTab {
+    uint8_t setpos[(SCC_KMAX + 1) * 128];
+    uint8_t colex_s[128];
+    uint8_t colex_k[256];
+};
+__device__ inline void load_draw_tab(const DevLut &L, DrawTab &D)
+{
+    auto copy = [](const uint8_t *src, uint8_t *dst, int bytes) {
+        for (int i = threadIdx.x; i < bytes / 4; i += WAVE) ((uint32_t *)dst)[i] = ((const uint32_t *)src)[i];
+    };
+    static_assert(offsetof(DevLut, setpos) % 4 == 0 && offsetof(DevLut, colex_s) % 4 == 0 && offsetof(DevLut, colex_k) % 4 == 0,
+                  "copied by words");
+    copy(&L.setpos[0][0], D.setpos, sizeof D.setpos);
+    copy(L.colex_s, D.colex_s, sizeof D.colex_s);
+    copy(L.colex_k, D.colex_k, sizeof D.colex_k);
+    __syncthreads();
+}
+
+// The arguments read anew: the compiler otherwise loads every pointer of the block
+// once, before the draw's loops, and spends vector instructions on spilling and
+// reloading what the scalar registers cannot hold; a scalar load where it is used
+// costs less
+typedef const __attribute__((address_space(4))) SampleArgs SampleArgsC;
+__device__ inline const SampleArgs &fresh_args(SampleArgsC *p)
+{
+    uint64_t q = readfirst64((uint64_t)p);
+    asm volatile("" : "+s"(q));
+    return *(const SampleArgs *)(SampleArgsC *)q;
+}
+
+// a vertex of the draw, in scalar registers
+struct VInfo {
+    int64_t ra;          // row start
+    uint32_t deg;
+    int hub;             // hub number, or -1
+    int c;
+    uint32_t sw, xw;     // bit h: 128-bit sums S_h, 128-bit record of level h
+};
+__device__ inline VInfo vertex_info(const SampleArgs &A, int64_t x)
+{
+    VInfo r;
+    if (A.vinfo) {
+        const uint64_t w0 = readfirst64(A.vinfo[2 * x]), w1 = readfirst64(A.vinfo[2 * x + 1]);
+        r.ra = (int64_t)(w0 & 0xffffffffffull);
+        r.c = (int)(w0 >> 40 & 7u);
+        r.sw = (uint32_t)(w0 >> 44 & 0xffu);
+        r.xw = (uint32_t)(w0 >> 52 & 0x1ffu);
+        r.deg = (uint32_t)w1;
+        r.hub = (int)(w1 >> 32) - 1;
+        return r;
+    }
+    r.ra = A.g.row_ptr[x];
+    r.deg = (uint32_t)(A.g.row_ptr[x + 1] - r.ra);
+    r.c = A.g.colors[x];
+    r.hub = A.hub_index ? A.hub_index[x] : -1;
+    r.sw = r.xw = 0;
+    for (int h = 1; h < A.k; h++) {
+        if (A.M[h] && (h + 1 < A.k || !A.zero || r.c == 0) && hi64(A.M[h][x])) r.sw |= 1u << h;
+        if (h >= 2 && A.lev[h].P && A.lev[h].hi && LOC_WIDE(A.lev[h].loc[x])) r.xw |= 1u << h;
+    }
+    return r;
+}
+
+// first lane whose inclusive running sum exceeds target: the sums stay below 2^64
+// when `narrow`, and are then formed in 64 bits (half the lane moves and adds)
+struct Pick {
+    int lane;            // -1: none
+    u128 total;          // the wave's sum, where none
+};
+__device__ inline Pick pick_exceeding(u128 run, u128 c, u128 target, bool narrow)
+{
+    Pick p;
+    if (narrow) {
+        const uint64_t incl = lo64(run) + wave_incl_scan64(lo64(c));
+        const uint64_t bal = __ballot(incl > lo64(target));
+        p.lane = bal ? __ffsll((long long)bal) - 1 : -1;
+        p.total = p.lane < 0 ? (u128)last_lane64(incl) : (u128)0;
+    } else {
+        const u128 incl = run + wave_incl_scan128(c);
+        p.lane = first_exceeding(incl, target);
+        p.total = p.lane < 0 ? last_lane128(incl) : (u128)0;
+    }
+    return p;
+}
+
+// the lane of the (n+1)-th set bit of mask (n below its bit count)
+__device__ inline int nth_bit(uint64_t mask, uint32_t n)
+{
+    const int below = (int)__popcll(mask & lanemask_lt());
+    return __ffsll((long long)__ballot((mask >> lane_id() & 1ull) && (uint32_t)below == n)) - 1;
+}
+
+// count of T'' (rank b of level h, colour set C, key kpp) at neighbour u of colour
+// cu in C
+__device__ inline u128 head_count(const SampleArgs &A, const DrawTab &D, int h, int rr, int b, uint32_t C, uint32_t kpp,
+                                  int64_t u, int cu)
+{
+    const LevelView &V = A.lev[h];
+    if (!V.P) return own_count_c(A, h, u, cu, kpp);
+    const int pos = D.setpos[h * 128 + compress_out(C & ~(1u << cu), cu)] * rr + b;
+    return dense_cnt(V, u, pos);
+}
 
 // An uncoloured k-star (round skipping, Sec. 3.3): the centre v by its running
 // sum of binom(d_v, k-1) (draw 0), then the i-th leaf at position r uniform
 // below d_v - i (draw 1 + i) among the neighbours not taken yet, where a taken
 // position is refilled by the last remaining one. Every lane makes the same
 // draws; lane q < i holds the q-th refilled position and its current value.
-__device__ inline int sample_star(const SampleArgs &A, int64_t r)
+__device__ __attribute__((always_inline)) inline int sample_star(const SampleArgs &A, int64_t r)
 {
     const int lane = lane_id();
     const int k = A.k;
     const uint64_t idx = A.first + (uint64_t)r;
     const DrawCache D = draw_cache(A.seed, A.stream, idx);
     const u128 X = draw_cached(D, A.total, A.seed, A.stream, idx, 0);
-    const int64_t v = wave_search(A.g.n, X, [&](int64_t i) { return A.pre[i]; });
+    const int64_t v = wave_search((int32_t)A.g.n, X, [&](uint32_t i) { return A.pre[i]; });
     if (v < 0) return 4;
     const int64_t ra = A.g.row_ptr[v], d = A.g.row_ptr[v + 1] - ra;
     if (d < k - 1) return 4;
@@ -199,8 +321,9 @@ __device__ inline int sample_star(const SampleArgs &A, int64_t r)
 // entry draw fell off the record, 2: a decomposition draw failed, 4: the root
 // vertex (or shape) draw fell off its running sums); none is expected for a
 // consistent table.
-__device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
+__device__ __attribute__((always_inline)) inline int sample_one(SampleArgsC *args, int64_t r, SampleLds &W, const DrawTab &D)
 {
+    const SampleArgs &A = *(const SampleArgs *)args;
     if (A.mode == 2) return sample_star(A, r);
     int32_t *sv = W.sv;
     int8_t *sp_par = W.par;
@@ -211,7 +334,7 @@ __device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
     const int lane = lane_id();
     const int k = A.k;
     const uint64_t idx = A.first + (uint64_t)r;
-    const DrawCache D = draw_cache(A.seed, A.stream, idx);
+    const DrawCache DC = draw_cache(A.seed, A.stream, idx);
     int shape = A.shape;
     const u128 *pre = A.pre;
     u128 total = A.total;
@@ -219,18 +342,19 @@ __device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
     if (A.mode == 1) {
         // shape first: j with running sum of t_j (ascending) exceeding X0, then
         // shape j's draws numbered from 1
-        const u128 X0 = draw_cached(D, A.total, A.seed, A.stream, idx, 0);
+        const u128 X0 = draw_cached(DC, A.total, A.seed, A.stream, idx, 0);
         const u128 incl = wave_incl_scan128(lane < L.num_unr ? A.stj[lane] : (u128)0);
         const int j = first_exceeding(incl, X0);
         if (j < 0) return 4;
         shape = j;
         pre = A.spre[j];
         total = pre[A.g.n - 1];
+        total = mk128(readfirst64(lo64(total)), readfirst64(hi64(total)));
         doff = 1;
     }
     // (1) root: first vertex whose running sum exceeds X, then the entry of its record
-    const u128 X = draw_cached(D, total, A.seed, A.stream, idx, doff);
-    const int64_t v = wave_search(A.g.n, X, [&](int64_t i) { return pre[i]; });
+    const u128 X = draw_cached(DC, total, A.seed, A.stream, idx, doff);
+    const int64_t v = wave_search((int32_t)A.g.n, X, [&](uint32_t i) { return pre[i]; });
     if (v < 0) return 4;
     const u128 res = X - (v > 0 ? pre[v - 1] : (u128)0);
     const Rec rk = rec_of(A.lev[k], v);
@@ -244,17 +368,15 @@ __device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
         uint32_t key = 0;
         if (e < lenk) {
             key = rk.key(e);
-            const int t = (int)(key - L.off[k]) / L.bk[k];
-            if (shape < 0 || L.unr_of[t] == shape) c = rk.cnt(e);
+            if (shape < 0 || L.unr_of[(int)(key - L.off[k]) / L.bk[k]] == shape) c = rk.cnt(e);
         }
-        const u128 incl = run + wave_incl_scan128(c);
-        const int w = first_exceeding(incl, res);
-        if (w >= 0) {
-            rkey = readlane32(key, w);
-            rcnt = readlane128(c, w);
+        const Pick p = pick_exceeding(run, c, res, hi64(total) == 0);
+        if (p.lane >= 0) {
+            rkey = readlane32(key, p.lane);
+            rcnt = readlane128(c, p.lane);
             break;
         }
-        run = readlane128(incl, WAVE - 1);
+        run = p.total;
     }
     if (rkey == 0xffffffffu) return 1;
     if (lane == 0) {
@@ -262,10 +384,14 @@ __device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
         st_key[0] = rkey; st_pos[0] = 0; st_cnt[0] = rcnt;
     }
     __syncthreads();
-    int nv = 1, sp = 1, dec = 0;
+    int nv = 1, sp = 1, dec = 0, at = -1;
     bool fail = false;
+    int64_t x = 0;
+    VInfo vi{};
     // (2) decompose, LIFO: (T', C \ C'', x) is processed before (T'', C'', u)
     while (sp > 0 && !fail) {
+        const SampleArgs &A = fresh_args(args);
+        const DevLut &L = *A.L;
         sp--;
         // every lane reads the same LDS words: made scalar, so that the per-level
         // arrays below are addressed from scalar registers
@@ -273,124 +399,177 @@ __device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
         const int pos = __builtin_amdgcn_readfirstlane(st_pos[sp]);
         const u128 cT = mk128(readfirst64(lo64(st_cnt[sp])), readfirst64(hi64(st_cnt[sp])));
         __syncthreads();
-        const int h = key_level(L, key);
-        if (h == 1) continue;
-        const int rel = (int)key - L.off[h];
-        const int t = rel / L.bk[h];
-        const uint32_t C = L.mask_k[h][rel - t * L.bk[h]];
-        const int64_t x = __builtin_amdgcn_readfirstlane(sv[pos]);
-        const int cx = A.g.colors[x];
-        const int hp = L.dec_hp[h][t], hpp = h - hp, a = L.dec_a[h][t], b = L.dec_b[h][t];
-        const int beta = L.dec_beta[h][t];
-        const u128 Y = draw_cached(D, (u128)beta * cT, A.seed, A.stream, idx, doff + 1 + 2 * dec);
+        if (key < (uint32_t)k) continue;   // a single node
+        // the key's decomposition in one word; the vertex's facts stay from T' to T'
+        const uint64_t ki = readfirst64(L.kinfo[key]);
+        if (pos != at) {
+            at = pos;
+            x = __builtin_amdgcn_readfirstlane(sv[pos]);
+            vi = vertex_info(A, x);
+        }
+        const uint32_t C = (uint32_t)ki & 0xffu;
+        const int h = (int)(ki >> 8) & 15, hp = (int)(ki >> 12) & 15, hpp = h - hp, beta = (int)(ki >> 16) & 15;
+        const int a = (int)(ki >> 20) & 0xff, b = (int)(ki >> 28) & 0xff;
+        const uint32_t key1 = (uint32_t)(ki >> 36) & 0xfffu, key2 = (uint32_t)(ki >> 48) & 0xfffu;
+        const int cx = vi.c;
+        const u128 N1 = (u128)beta * cT;
         // stage 1: C'' among the |T''|-subsets of C \ {c_x}, ascending bitmask
         const uint32_t R = C & ~(1u << cx);
-        int ncand = 1;
-        for (int i = 1; i <= hpp; i++) ncand = ncand * (h - 1 - hpp + i) / i;
-        u128 w = 0, xprime = 0, sval = 0;
-        uint32_t cpp = 0;
-        int sidx = 0;
-        if (lane < ncand) {
-            // deposit the lane-th hpp-subset of the low h-1 positions onto R's bits
-            uint32_t pm = L.mask_s[hpp][lane], dep = 0, rr = R;
-            for (int q = 0; rr; q++) {
-                const uint32_t bit = rr & (~rr + 1u);
-                if (pm >> q & 1u) dep |= bit;
-                rr &= rr - 1u;
+        uint32_t Cpp = R;
+        int Sidx = 0;
+        u128 Xp = 1, Sv = N1;
+        if (hp == 1) {
+            // T' is the root alone: C'' = R, and beta c(T_C, x) is the neighbour sum itself
+            Sidx = b * L.bk1[hpp] + D.colex_s[compress_out(R, cx)];
+        } else {
+            const u128 Y = draw_cached(DC, N1, A.seed, A.stream, idx, doff + 1 + 2 * dec);
+            // (the lists of one set follow each other by size, and |T''| < |R| here)
+            const int sub0 = __builtin_amdgcn_readfirstlane(L.sub_at[R][hpp]);
+            const int ncand = __builtin_amdgcn_readfirstlane(L.sub_at[R][hpp + 1]) - sub0;
+            u128 w = 0, xprime = 0, sval = 0;
+            uint32_t cpp = 0;
+            int sidx = 0;
+            if (lane < ncand) {
+                cpp = L.subs[sub0 + lane];
+                const int ws = L.WS[hpp];
+                sidx = b * L.bk1[hpp] + D.colex_s[compress_out(cpp, cx)];
+                const uint64_t slo = (A.Slo[hpp] + (size_t)x * ws)[(uint32_t)sidx];
+                uint64_t shi = 0;
+                if (vi.sw >> hpp & 1u)
+                    shi = A.Shi[hpp][(A.Shrow[hpp] ? (size_t)A.Shrow[hpp][x] : (size_t)x) * ws + sidx];
+                const LevelView &V = A.lev[hp];
+                if (V.P) {
+                    const int po = D.setpos[hp * 128 + compress_out(C & ~cpp & ~(1u << cx), cx)] * L.r[hp] + a;
+                    const uint64_t lo = (V.pool + (size_t)x * V.P)[(uint32_t)po];
+                    uint64_t hi = 0;
+                    if (vi.xw >> hp & 1u) hi = V.hi[(size_t)LOC_OFF(V.loc[x]) * V.P + po];
+                    xprime = mk128(lo, hi);
+                } else {
+                    xprime = own_count_c(A, hp, x, cx, key1 + D.colex_k[C ^ cpp]);
+                }
+                sval = mk128(slo, shi);
+                w = xprime * sval;
             }
-            cpp = dep;
-            const uint32_t kprime = L.off[hp] + a * L.bk[hp] + L.colex_k[C ^ cpp];
-            xprime = own_count(A, hp, x, kprime);
-            const int ws = L.WS[hpp];
-            sidx = b * L.bk1[hpp] + L.colex_s[compress_out(cpp, cx)];
-            const uint64_t slo = A.Slo[hpp][(size_t)x * ws + sidx];
-            const uint64_t shi =
-                hi64(A.M[hpp][x]) ? A.Shi[hpp][(A.Shrow[hpp] ? (size_t)A.Shrow[hpp][x] : (size_t)x) * ws + sidx] : 0;
-            sval = mk128(slo, shi);
-            w = xprime * sval;
+            const Pick p1 = pick_exceeding(0, w, Y, hi64(N1) == 0);
+            if (p1.lane < 0) { fail = true; break; }
+            // the chosen candidate's values, read from its lane as scalars
+            Cpp = readlane32(cpp, p1.lane);
+            Sidx = (int)readlane32((uint32_t)sidx, p1.lane);
+            Xp = readlane128(xprime, p1.lane);
+            Sv = readlane128(sval, p1.lane);
         }
-        const u128 incl1 = wave_incl_scan128(w);
-        const int w1 = first_exceeding(incl1, Y);
-        if (w1 < 0) { fail = true; break; }
-        // the chosen candidate's values, read from its lane as scalars
-        const uint32_t Cpp = readlane32(cpp, w1);
-        const int Sidx = (int)readlane32((uint32_t)sidx, w1);
-        const u128 Xp = readlane128(xprime, w1);
-        const u128 Sv = readlane128(sval, w1);
         // stage 2: neighbour u of x with weight c(T''_{C''}, u), CSR order
-        const u128 Z = draw_cached(D, Sv, A.seed, A.stream, idx, doff + 2 + 2 * dec);
-        const uint32_t kpp = L.off[hpp] + b * L.bk[hpp] + L.colex_k[Cpp];
-        const int64_t ra = A.g.row_ptr[x], rb = A.g.row_ptr[x + 1];
-        int64_t u = -1;
-        u128 wu = 0;
-        const int hub = A.hub_index ? A.hub_index[x] : -1;
-        if (hub >= 0) {
+        const u128 Z = draw_cached(DC, Sv, A.seed, A.stream, idx, doff + 2 + 2 * dec);
+        const bool narrow = hi64(Sv) == 0;
+        const uint32_t kpp = key2 + D.colex_k[Cpp];
+        const int rr = L.r[hpp];
+        const int32_t *row = A.g.col_idx + vi.ra;
+        const uint8_t *rowc = A.ecol ? A.ecol + vi.ra : nullptr;
+        auto colour = [&](uint32_t e) { return rowc ? (int)rowc[e] : (int)A.g.colors[row[e]]; };
+        int32_t u = -1;
+        u128 wu = 1;
+        uint32_t e0 = 0, e1 = vi.deg;   // the row's neighbours still in question
+        u128 run2 = 0;
+        if (vi.hub >= 0) {
             // running sums over x's neighbours at the end of every block of HUB_BLOCK
             // neighbours, precomputed per (hub, level, entry): search the block, then
             // scan its neighbours from the running sum before it
-            const int64_t d = rb - ra, nb = (d + HUB_BLOCK - 1) / HUB_BLOCK;
-            const int64_t base = A.hub_poff[(size_t)hub * (SCC_KMAX + 1) + hpp];
+            const int32_t nb = (int32_t)((vi.deg + (uint32_t)HUB_BLOCK - 1) / (uint32_t)HUB_BLOCK);
+            const int64_t base = A.hub_poff[(size_t)vi.hub * (SCC_KMAX + 1) + hpp];
             const uint64_t *plo = A.hub_pre + base + (size_t)Sidx * nb;
-            const bool pw = hi64(A.M[hpp][x]) != 0;
+            const bool pw = vi.sw >> hpp & 1u;
             const uint64_t *phi = A.hub_pre + base + (size_t)L.WS[hpp] * nb + (size_t)Sidx * nb;
-            auto P = [&](int64_t j) { return mk128(plo[j], pw ? phi[j] : 0); };
-            const int64_t b = wave_search(nb, Z, P);
-            if (b >= 0) {
-                const int64_t e = ra + b * HUB_BLOCK + lane;
-                u128 c = 0;
-                int32_t uu = -1;
-                if (e < rb) {
-                    uu = A.g.col_idx[e];
-                    c = own_count_c(A, hpp, uu, edge_colour(A, e, uu), kpp);
+            auto P = [&](uint32_t j) { return mk128(plo[j], pw ? phi[j] : 0); };
+            const int32_t bq = wave_search(nb, Z, P);
+            if (bq < 0) { fail = true; break; }
+            if (bq > 0) {
+                const u128 before = P(bq - 1);
+                run2 = mk128(readfirst64(lo64(before)), readfirst64(hi64(before)));
+            }
+            e0 = (uint32_t)(bq * HUB_BLOCK);
+            e1 = min(e1, e0 + (uint32_t)HUB_BLOCK);
+        }
+        if (hpp == 1) {
+            // a single node of colour Cpp: the (Z - run2 + 1)-th neighbour of that colour,
+            // by counting colours, 4 x 64 neighbours per round
+            uint32_t left = (uint32_t)(Z - run2);
+            const int want = __ffs((int)Cpp) - 1;
+            for (uint32_t base = e0; base < e1 && u < 0; base += 4 * WAVE) {
+                int c[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const uint32_t e = base + j * WAVE + lane;
+                    c[j] = -1;
+                    if (e < e1) c[j] = colour(e);
                 }
-                const u128 incl = (b > 0 ? P(b - 1) : (u128)0) + wave_incl_scan128(c);
-                const int w2 = first_exceeding(incl, Z);
-                if (w2 >= 0) {
-                    u = (int32_t)readlane32((uint32_t)uu, w2);
-                    wu = readlane128(c, w2);
+#pragma unroll
+                for (int j = 0; j < 4; j++) {
+                    const uint64_t m = __ballot(c[j] == want);
+                    const uint32_t cnt = (uint32_t)__popcll(m);
+                    if (u < 0) {
+                        if (left < cnt) {
+                            const int w2 = nth_bit(m, left);
+                            u = __builtin_amdgcn_readfirstlane(row[base + (uint32_t)(j * WAVE + w2)]);
+                        } else {
+                            left -= cnt;
+                        }
+                    }
                 }
             }
         } else {
-            // CSR order, 2 x 64 neighbours per round: every lane issues the loads of
-            // its 2 neighbours (and their colours, stored per edge) before using any,
-            // then the 2 groups are scanned in order
-            u128 run2 = 0;
-            bool found = false;
-            for (int64_t base = ra; base < rb && !found; base += 2 * WAVE) {
-                int32_t uu[2];
-                int cu[2];
-                u128 c[2];
+            // the neighbours whose colour is in C'' (the others have no such count) are
+            // queued in CSR order, 4 x 64 colours read per round, and counted 64 at a time
+            uint32_t qn = 0;
+            for (uint32_t base = e0; u < 0 && (base < e1 || qn > 0);) {
+                if (base < e1 && qn < WAVE) {
+                    int c[4];
 #pragma unroll
-                for (int g4 = 0; g4 < 2; g4++) {
-                    const int64_t e = base + g4 * WAVE + lane;
-                    uu[g4] = e < rb ? A.g.col_idx[e] : -1;
-                    cu[g4] = e < rb && A.ecol ? A.ecol[e] : 0;
-                }
-#pragma unroll
-                for (int g4 = 0; g4 < 2; g4++)
-                    c[g4] = uu[g4] >= 0 ? own_count_c(A, hpp, uu[g4], A.ecol ? cu[g4] : A.g.colors[uu[g4]], kpp)
-                                        : (u128)0;
-#pragma unroll
-                for (int g4 = 0; g4 < 2; g4++) {
-                    if (found) break;
-                    const u128 incl = run2 + wave_incl_scan128(c[g4]);
-                    const int w2 = first_exceeding(incl, Z);
-                    if (w2 >= 0) {
-                        u = (int32_t)readlane32((uint32_t)uu[g4], w2);
-                        wu = readlane128(c[g4], w2);
-                        found = true;
-                    } else {
-                        run2 = readlane128(incl, WAVE - 1);
+                    for (int j = 0; j < 4; j++) {
+                        const uint32_t e = base + j * WAVE + lane;
+                        c[j] = 31;
+                        if (e < e1) c[j] = colour(e);
                     }
+                    // as many of the four as the queue (two waves long) surely holds
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        if (qn > WAVE || base >= e1) continue;
+                        const bool rel = Cpp >> c[j] & 1u;
+                        const uint64_t m = __ballot(rel);
+                        if (rel) W.queue[qn + (uint32_t)__popcll(m & lanemask_lt())] = base + lane;
+                        qn += (uint32_t)__popcll(m);
+                        base += WAVE;
+                    }
+                    __syncthreads();
+                    if (qn < WAVE && base < e1) continue;
                 }
+                const uint32_t take = min(qn, (uint32_t)WAVE);
+                int32_t uu = -1;
+                u128 c = 0;
+                if ((uint32_t)lane < take) {
+                    const uint32_t e = W.queue[lane];
+                    uu = row[e];
+                    c = head_count(A, D, hpp, rr, b, Cpp, kpp, uu, colour(e));
+                }
+                const Pick p2 = pick_exceeding(run2, c, Z, narrow);
+                if (p2.lane >= 0) {
+                    u = (int32_t)readlane32((uint32_t)uu, p2.lane);
+                    wu = readlane128(c, p2.lane);
+                    break;
+                }
+                run2 = p2.total;
+                const uint32_t rest = (uint32_t)lane < qn - take ? W.queue[take + lane] : 0u;
+                __syncthreads();
+                if ((uint32_t)lane < qn - take) W.queue[lane] = rest;
+                qn -= take;
+                __syncthreads();
             }
         }
         if (u < 0) { fail = true; break; }
         if (lane == 0) {
-            sv[nv] = (int32_t)u;
+            sv[nv] = u;
             sp_par[nv] = (int8_t)pos;
             st_key[sp] = kpp; st_pos[sp] = nv; st_cnt[sp] = wu;
-            st_key[sp + 1] = L.off[hp] + a * L.bk[hp] + L.colex_k[C ^ Cpp];
+            st_key[sp + 1] = key1 + D.colex_k[C ^ Cpp];
             st_pos[sp + 1] = pos; st_cnt[sp + 1] = Xp;
         }
         __syncthreads();
@@ -412,12 +591,19 @@ __device__ inline int sample_one(const SampleArgs &A, int64_t r, SampleLds &W)
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_sample(SampleArgs A)
 {
     __shared__ SampleLds W;
+    __shared__ DrawTab D;
+    load_draw_tab(*A.L, D);
+    // (the argument block where it lies, so that sample_one can read it anew)
+    SampleArgsC *args = (SampleArgsC *)__builtin_amdgcn_kernarg_segment_ptr();
     for (int64_t s = blockIdx.x; s < A.nsamp; s += gridDim.x) {
-        const int e = sample_one(A, s, W);
+        const int e = sample_one(args, s, W, D);
         if (e && lane_id() == 0) atomicOr(A.err, e);
         __syncthreads();
     }
 }
+// eight rounds of the waves that fit the chip: enough for the dispatcher to even
+// out the samples, with the tables copied once per workgroup
+constexpr int64_t SAMPLE_GRID = 1 << 16;
 
 // A serving step: rows of many requests (each with its own table, shape and
 // random stream), flattened; row s belongs to the first chunk whose running end
@@ -427,6 +613,8 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
                                                       const int64_t *cend, int nch, int64_t total, int *err)
 {
     __shared__ SampleLds W;
+    __shared__ DrawTab D;
+    const DevLut *tab = nullptr;
     for (int64_t s = blockIdx.x; s < total; s += gridDim.x) {
         int lo = 0, hi = nch - 1;
         while (lo < hi) {
@@ -435,8 +623,12 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
         }
         const ServeChunk C = ch[lo];
         const int64_t r = C.off + (s - (cend[lo] - C.count));
-        const SampleArgs &A = *(const SampleArgs *)((const __attribute__((address_space(4))) SampleArgs *)args + C.arg);
-        const int e = sample_one(A, r, W);
+        SampleArgsC *A = (SampleArgsC *)args + __builtin_amdgcn_readfirstlane(C.arg);
+        if (A->L != tab) {   // another table
+            tab = A->L;
+            load_draw_tab(*tab, D);
+        }
+        const int e = sample_one(A, r, W, D);
         if (e && lane_id() == 0) atomicOr(err, e);
         __syncthreads();
     }
@@ -719,6 +911,24 @@ __global__ void k_edge_colours(const int32_t *col_idx, const uint8_t *colors, in
         if (e0 + j < nnz) ecol[e0 + j] = colors[col_idx[e0 + j]];
 }
 
+// the sampler's word pair of every vertex (SampleArgs::vinfo)
+__global__ void k_vertex_info(SampleArgs A, uint64_t *out)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= A.g.n) return;
+    const int64_t ra = A.g.row_ptr[v];
+    const int c = A.g.colors[v];
+    uint64_t w0 = (uint64_t)ra | (uint64_t)c << 40;
+    for (int h = 1; h < A.k; h++) {
+        // (the level k-1 sums exist at colour-0 vertices only under zero-rooting)
+        if (A.M[h] && (h + 1 < A.k || !A.zero || c == 0) && hi64(A.M[h][v])) w0 |= 1ull << (44 + h);
+        if (h >= 2 && A.lev[h].P && A.lev[h].hi && LOC_WIDE(A.lev[h].loc[v])) w0 |= 1ull << (52 + h);
+    }
+    out[2 * v] = w0;
+    out[2 * v + 1] = (uint64_t)(uint32_t)(A.g.row_ptr[v + 1] - ra) |
+                     (uint64_t)(uint32_t)((A.hub_index ? A.hub_index[v] : -1) + 1) << 32;
+}
+
 scc_status enqueue_edge_colours(scc_table *T)
 {
     if (T->ecol || T->nnz_g == 0) return SCC_OK;
@@ -915,6 +1125,7 @@ static scc_status sampling_args(scc_table *T, int shape, SampleArgs *out)
     u128 total = 0;
     int mode = 0;
     const uint8_t *A_ecol = nullptr;
+    const uint64_t *A_vinfo = nullptr;
     if (bal && shape == T->hlut.star_unr) {
         mode = 2;
         pre = T->star_pre;
@@ -942,9 +1153,11 @@ static scc_status sampling_args(scc_table *T, int shape, SampleArgs *out)
         std::lock_guard<std::mutex> g(T->hub_mu);
         if (!T->hubpre_ready && !T->hub_host.empty()) return set_error(SCC_EINVAL, "the hub running sums are not built");
         A_ecol = T->ecol;
+        A_vinfo = T->vinfo;
     }
     SampleArgs A{};
     A.ecol = A_ecol;
+    A.vinfo = A_vinfo;
     A.mode = mode;
     A.spre = T->bal_spre;
     A.stj = T->bal_stj;
@@ -958,6 +1171,22 @@ static scc_status sampling_args(scc_table *T, int shape, SampleArgs *out)
     }
     A.pre = pre; A.total = total;
     *out = A;
+    return SCC_OK;
+}
+
+// the per-vertex words of the draw, once per table (after its hub running sums)
+static scc_status ensure_vertex_info(scc_table *T, SampleArgs *A)
+{
+    std::lock_guard<std::mutex> g(T->hub_mu);
+    if (!T->vinfo && T->n) {
+        uint64_t *vi = (uint64_t *)T->alloc((size_t)T->n * 16);
+        if (!vi) return set_error(SCC_ENOMEM, "vertex words (%lld bytes)", (long long)T->n * 16);
+        hipLaunchKernelGGL(k_vertex_info, dim3((unsigned)((T->n + 255) / 256)), dim3(256), 0, T->stream, *A, vi);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipStreamSynchronize(T->stream));
+        T->vinfo = vi;
+    }
+    A->vinfo = T->vinfo;
     return SCC_OK;
 }
 
@@ -979,8 +1208,9 @@ scc_status prepare_sampling(scc_table *T, int shape, SampleArgs *out)
     if (s) return s;
     s = ensure_hub_prefix(T);
     if (!s) s = ensure_edge_colours(T);
-    if (s) return s;
-    return sampling_args(T, shape, out);
+    if (!s) s = sampling_args(T, shape, out);
+    if (!s) s = ensure_vertex_info(T, out);
+    return s;
 }
 
 scc_status prepare_all_sampling(scc_table *T)
@@ -1021,7 +1251,7 @@ extern "C" scc_status scc_sample(const scc_table *tc, int32_t shape, int64_t n, 
     A.seed = seed; A.stream = stream_id; A.first = first_index;
     A.nsamp = n; A.verts = out_verts; A.par = out_parent; A.err = err;
     hipError_t e = hipMemsetAsync(err, 0, 4, st);
-    const int64_t grid = std::min<int64_t>(n, (int64_t)1 << 20);
+    const int64_t grid = std::min<int64_t>(n, SAMPLE_GRID);
     hipLaunchKernelGGL(k_sample, dim3((unsigned)grid), dim3(WAVE), 0, st, A);
     int herr = 0;
     if (e == hipSuccess) e = hipGetLastError();
@@ -1090,7 +1320,7 @@ extern "C" scc_status scc_sample_noalloc(const scc_table *tc, int32_t shape, int
     A.seed = seed; A.stream = stream_id; A.first = first_index;
     A.nsamp = n; A.verts = out_verts; A.par = out_parent; A.err = flags;
     hipLaunchKernelGGL(k_clear_flags, dim3(1), dim3(WAVE), 0, st, flags, 1);
-    const int64_t grid = std::min<int64_t>(n, (int64_t)1 << 20);
+    const int64_t grid = std::min<int64_t>(n, SAMPLE_GRID);
     hipLaunchKernelGGL(k_sample, dim3((unsigned)grid), dim3(WAVE), 0, st, A);
     int herr = 0;
     hipError_t e = hipGetLastError();

@@ -19,6 +19,10 @@ struct SampleArgs {
     const int32_t *hub_index;             // [n] hub number or -1
     const int64_t *hub_poff;              // [nhub * (k+1)]
     const uint64_t *hub_pre;
+    // per vertex two words, read as one line: row start (40 bits), colour (3, at 40),
+    // levels whose sums have high words (bit 44 + h), levels whose records do (bit
+    // 52 + h); degree (32 bits), hub number + 1 (32). Null: read from the arrays.
+    const uint64_t *vinfo;
     const uint8_t *ecol;                  // [nnz] colour of each edge's head, or null (read colors[])
     const u128 *pre;                      // running sums of admissible level-k totals
     u128 total;

@@ -88,6 +88,13 @@ struct DevLut {
     // setpos[h] of the q-th h-set C (colex, without c) in the records of colour-c_u
     // vertices, 0xff where c_u is not in C
     uint64_t gsel[SCC_KMAX + 1][SCC_KMAX][35];
+    // The sampler's decomposition of each key (T, C) in one word: C (8 bits), h (4),
+    // |T'| (4), beta_T (4), rank of T' (8), rank of T'' (8), the first keys of T'
+    // (12) and of T'' (12), to which a colour set's colex rank is added
+    uint64_t kinfo[2000];
+    // the m-subsets of colour set R in ascending order, at subs[sub_at[R][m]]
+    uint16_t sub_at[256][SCC_KMAX + 1];
+    uint8_t subs[6561];
 };
 
 // Host-side treelet algebra (treelets.cpp).

@@ -106,8 +106,7 @@ struct scc_table {
     // hub running sums: the neighbour draw reads it with the edge instead of
     // looking the neighbour's colour up at random
     uint8_t *ecol = nullptr;
-    // root draw: every ROOT_STRIDE-th running sum, for a two-level search
-    u128 *pre_coarse = nullptr;
+    uint64_t *vinfo = nullptr;       // [2n] the sampler's word pair per vertex (SampleArgs::vinfo)
 
     void *alloc(size_t bytes_)
     {

@@ -180,6 +180,7 @@ int tree_unrooted_id(int k, const uint32_t *adjmask)
 }
 
 static void build_dense(int k, DevLut *L);
+static void build_draw(int k, DevLut *L);
 
 void build_lut(int k, DevLut *L)
 {
@@ -304,6 +305,7 @@ void build_lut(int k, DevLut *L)
         }
     }
     build_dense(k, L);
+    build_draw(k, L);
 }
 
 // Order of the m-subsets of [n] in which consecutive ones differ by exchanging one
@@ -365,6 +367,28 @@ static void build_dense(int k, DevLut *L)
                 }
                 L->gsel[h][c][q] = w;
             }
+}
+
+// the sampler's tables: a word per key, and the subsets of every colour set by size
+static void build_draw(int k, DevLut *L)
+{
+    for (int h = 2; h <= k; h++)
+        for (int t = 0; t < L->r[h]; t++)
+            for (int ci = 0; ci < L->bk[h]; ci++) {
+                const int hp = L->dec_hp[h][t], hpp = h - hp, a = L->dec_a[h][t], b = L->dec_b[h][t];
+                L->kinfo[L->off[h] + t * L->bk[h] + ci] =
+                    (uint64_t)L->mask_k[h][ci] | (uint64_t)h << 8 | (uint64_t)hp << 12 |
+                    (uint64_t)L->dec_beta[h][t] << 16 | (uint64_t)a << 20 | (uint64_t)b << 28 |
+                    (uint64_t)(L->off[hp] + a * L->bk[hp]) << 36 | (uint64_t)(L->off[hpp] + b * L->bk[hpp]) << 48;
+            }
+    for (int c = 0; c < k; c++) L->kinfo[c] = (uint64_t)(1u << c) | 1ull << 8;   // level 1
+    int at = 0;
+    for (uint32_t R = 0; R < (1u << k); R++)
+        for (int m = 0; m <= __builtin_popcount(R); m++) {
+            L->sub_at[R][m] = (uint16_t)at;
+            for (uint32_t s = 0; s <= R; s++)
+                if (!(s & ~R) && __builtin_popcount(s) == m) L->subs[at++] = (uint8_t)s;
+        }
 }
 
 // ---------------------------------------------------------------------------

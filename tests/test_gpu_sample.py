@@ -202,3 +202,17 @@ def test_ags_round_histogram_edges(round_size):
         v, _ = gt.sample(round_size, seed=3, shape=int(r["round_shapes"][q]), first_index=q * round_size)
         want += np.bincount(gt.classify(v)[1].cpu().numpy(), minlength=want.size)
     assert np.array_equal(r["hits"], want)
+
+
+@pytest.mark.parametrize("deg", [63, 64, 65, 128, 129, 192, 256, 257, 700])
+@pytest.mark.parametrize("hub_degree", [0, 32])
+def test_neighbour_draw_row_edges(deg, hub_degree):
+    # the neighbour draw reads a row's colours 4 x 64 at a time, counts single nodes
+    # by ballots and queues the neighbours in the colours of T'' 64 at a time: rows around
+    # those sizes, scanned whole and (hub_degree = 32) by blocks of the running sums
+    rng = np.random.default_rng(deg)
+    e = [np.stack([np.zeros(deg, np.int64), 1 + np.arange(deg)], 1), rng.integers(1, deg + 1, (2 * deg, 2))]
+    g = gg.csr_from_edges(deg + 1, np.concatenate(e).astype(np.int64))
+    for k in (3, 6, 8):
+        gt, ot = build_pair(g, gg.colors(g.n, k, seed=k), k, rooting=O.ROOT_ALL, hub_degree=hub_degree)
+        assert_samples_equal(gt, ot, 400, seed=deg, stream=k, label=f"row of {deg}, k {k}")
