@@ -547,6 +547,8 @@ extern "C" void scc_release_caches(void)
     for (int k = 0; k <= SCC_KMAX; k++) {
         if (g_cls[k]) { (void)hipFree(g_cls[k]->lut); delete g_cls[k]; g_cls[k] = nullptr; }
     }
+    release_k_tables();
+    release_events();
 }
 
 void launch_serve_classify(const ServeClassArgs *args, const ServeChunk *ch, const int64_t *cend, int nch,
@@ -605,7 +607,7 @@ scc_status AgsState::init(const scc_table *T, int64_t cbar_, hipStream_t st)
     if (s) return s;
     codes = cd->codes;
     S = (int)codes.size();
-    NS = T->hlut.num_unr;
+    NS = T->hl[0].num_unr;
     cbar = cbar_;
     c.assign(S, 0); nj.assign(NS, 0); w.assign(S, 0.0); tjd.assign(NS, 0.0);
     cov.assign(S, 0); sig_ok.assign(S, 0); sig.assign(S, nullptr);

@@ -2073,14 +2073,16 @@ __global__ void __launch_bounds__(WAVE) k_combine_wide(CombineArgs A, const int 
 // high word, summed (the rows of the next gather that need 128-bit sums are at
 // least their neighbours): out[0..3]
 struct LevelStats { uint64_t nnz, wide, max_n, heavy; };
+// With loc, the locators of a dense level without 128-bit vertices too.
 __global__ void __launch_bounds__(256) k_level_stats(GraphView g, const uint32_t *meta, const u128 *N,
-                                                     unsigned long long *out)
+                                                     unsigned long long *out, uint64_t *loc)
 {
     __shared__ uint64_t part[4][256 / WAVE];
     uint64_t x[4] = {0, 0, 0, 0};
     for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < g.n; v += (int64_t)gridDim.x * blockDim.x) {
         const uint32_t m = meta[v];
         const u128 nv = N[v];
+        if (loc) loc[v] = make_loc(0, META_LEN(m), 0);
         x[0] += META_LEN(m);
         x[1] += META_WIDE(m);
         x[2] = max(x[2], hi64(nv) ? ~0ull : lo64(nv));
@@ -2127,15 +2129,6 @@ __global__ void __launch_bounds__(WAVE) k_dense_hi(const int32_t *rows, int W, i
 {
     const int64_t v = rows[blockIdx.x];
     for (int i = threadIdx.x; i < W; i += WAVE) hi[(size_t)blockIdx.x * P + i] = src[(size_t)v * P + i];
-}
-
-// record size in 64-bit words
-__global__ void k_words(int64_t n, const uint32_t *meta, uint64_t *words)
-{
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    uint32_t m = meta[v], len = META_LEN(m);
-    words[v] = len ? (uint64_t)REC_HDR + key_words(len) + (uint64_t)len * (META_WIDE(m) ? 2u : 1u) : 0;
 }
 
 // Packing: each vertex's slot is copied into the pool at its offset, in one
@@ -2494,15 +2487,30 @@ __device__ T block_incl_scan(T x, T *sh)
     return x + pre;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(SCAN_T) k_scan_sums(const T *in, int64_t n, T *bsum)
+// what is scanned: an array, record sizes from the record summaries, or stored
+// entries from the locators
+template <typename T> struct ScanArray {
+    const T *a;
+    __device__ T operator()(int64_t i) const { return a[i]; }
+};
+struct ScanMetaWords {
+    const uint32_t *meta;
+    __device__ uint64_t operator()(int64_t i) const { return rec_words(meta[i]); }
+};
+struct ScanLocLen {
+    const uint64_t *loc;   // null: level 1, one entry a vertex
+    __device__ uint64_t operator()(int64_t i) const { return loc ? LOC_LEN(loc[i]) : 1u; }
+};
+
+template <typename T, typename F>
+__global__ void __launch_bounds__(SCAN_T) k_scan_sums(F in, int64_t n, T *bsum)
 {
     __shared__ T sh[SCAN_T / WAVE];
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE;
     T s = 0;
     for (int i = 0; i < SCAN_I; i++) {
         int64_t idx = base + (int64_t)threadIdx.x * SCAN_I + i;
-        if (idx < n) s += in[idx];
+        if (idx < n) s += in(idx);
     }
     T incl = block_incl_scan<T>(s, sh);
     if (threadIdx.x == SCAN_T - 1) bsum[blockIdx.x] = incl;
@@ -2528,15 +2536,15 @@ __global__ void __launch_bounds__(SCAN_T) k_scan_top(T *bsum, int64_t nb)
     }
 }
 
-template <typename T>
-__global__ void __launch_bounds__(SCAN_T) k_scan_apply(const T *in, T *out, int64_t n, const T *bexcl)
+template <typename T, typename F>
+__global__ void __launch_bounds__(SCAN_T) k_scan_apply(F in, T *out, int64_t n, const T *bexcl)
 {
     __shared__ T sh[SCAN_T / WAVE];
     const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_I;
     T v[SCAN_I];
     T s = 0;
     for (int i = 0; i < SCAN_I; i++) {
-        v[i] = (base + i < n) ? in[base + i] : (T)0;
+        v[i] = (base + i < n) ? in(base + i) : (T)0;
         s += v[i];
     }
     T incl = block_incl_scan<T>(s, sh);
@@ -2544,6 +2552,36 @@ __global__ void __launch_bounds__(SCAN_T) k_scan_apply(const T *in, T *out, int6
     for (int i = 0; i < SCAN_I; i++) {
         run += v[i];
         if (base + i < n) out[base + i] = run;
+    }
+}
+
+// short arrays: one block, tile after tile (one launch of a few microseconds
+// instead of three, whose gaps are longer than their work)
+constexpr int64_t SCAN_SMALL = 4 * SCAN_TILE;
+template <typename T, typename F>
+__global__ void __launch_bounds__(SCAN_T) k_scan_small(F in, T *out, int64_t n)
+{
+    __shared__ T sh[SCAN_T / WAVE];
+    __shared__ T carry;
+    if (threadIdx.x == 0) carry = 0;
+    __syncthreads();
+    for (int64_t base = (int64_t)threadIdx.x * SCAN_I; base - (int64_t)threadIdx.x * SCAN_I < n; base += SCAN_TILE) {
+        T v[SCAN_I];
+        T s = 0;
+        for (int i = 0; i < SCAN_I; i++) {
+            v[i] = (base + i < n) ? in(base + i) : (T)0;
+            s += v[i];
+        }
+        const T incl = block_incl_scan<T>(s, sh);
+        const T c = carry;
+        T run = c + incl - s;
+        for (int i = 0; i < SCAN_I; i++) {
+            run += v[i];
+            if (base + i < n) out[base + i] = run;
+        }
+        __syncthreads();
+        if (threadIdx.x == SCAN_T - 1) carry = c + incl;
+        __syncthreads();
     }
 }
 
@@ -2643,18 +2681,24 @@ __global__ void __launch_bounds__(WAVE) k_mpack(const PackJobDev *Js)
     if (threadIdx.x == 0 && nwide) atomicAdd(&J.stats[1], (unsigned long long)nwide);
 }
 
-template <typename T>
-scc_status scan_incl(scc_table *T_, const T *in, T *out, int64_t n)
+template <typename T, typename F>
+scc_status scan_incl(scc_table *T_, F in, T *out, int64_t n)
 {
     if (n <= 0) return SCC_OK;
+    if (n <= SCAN_SMALL) {
+        hipLaunchKernelGGL((k_scan_small<T, F>), dim3(1), dim3(SCAN_T), 0, T_->stream, in, out, n);
+        hipError_t es = hipGetLastError();
+        if (es != hipSuccess) return set_error(SCC_EDEVICE, "scan: %s", hipGetErrorString(es));
+        return SCC_OK;
+    }
     const int64_t nb = (n + SCAN_TILE - 1) / SCAN_TILE;
     DevMem m = T_->mem;        // scratch ordered on the stream the scan runs on
     m.stream = T_->stream;
     T *bsum = (T *)m.get(nb * sizeof(T));
     if (!bsum) return set_error(SCC_ENOMEM, "scan scratch");
-    hipLaunchKernelGGL(k_scan_sums<T>, dim3((unsigned)nb), dim3(SCAN_T), 0, T_->stream, in, n, bsum);
+    hipLaunchKernelGGL((k_scan_sums<T, F>), dim3((unsigned)nb), dim3(SCAN_T), 0, T_->stream, in, n, bsum);
     hipLaunchKernelGGL(k_scan_top<T>, dim3(1), dim3(SCAN_T), 0, T_->stream, bsum, nb);
-    hipLaunchKernelGGL(k_scan_apply<T>, dim3((unsigned)nb), dim3(SCAN_T), 0, T_->stream, in, out, n, bsum);
+    hipLaunchKernelGGL((k_scan_apply<T, F>), dim3((unsigned)nb), dim3(SCAN_T), 0, T_->stream, in, out, n, bsum);
     m.put(bsum);   // stream-ordered release: reused only by later work on this stream
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(SCC_EDEVICE, "scan: %s", hipGetErrorString(e));
@@ -2677,9 +2721,10 @@ LevelSrc packed_src(const TableLevel &l)
 
 }  // namespace
 
-scc_status scan_u128(scc_table *T, const u128 *in, u128 *out, int64_t n) { return scan_incl<u128>(T, in, out, n); }
-scc_status scan_u64(scc_table *T, const uint64_t *in, uint64_t *out, int64_t n) { return scan_incl<uint64_t>(T, in, out, n); }
-scc_status scan_u32(scc_table *T, const uint32_t *in, uint32_t *out, int64_t n) { return scan_incl<uint32_t>(T, in, out, n); }
+scc_status scan_u128(scc_table *T, const u128 *in, u128 *out, int64_t n) { return scan_incl<u128>(T, ScanArray<u128>{in}, out, n); }
+scc_status scan_u64(scc_table *T, const uint64_t *in, uint64_t *out, int64_t n) { return scan_incl<uint64_t>(T, ScanArray<uint64_t>{in}, out, n); }
+scc_status scan_u32(scc_table *T, const uint32_t *in, uint32_t *out, int64_t n) { return scan_incl<uint32_t>(T, ScanArray<uint32_t>{in}, out, n); }
+scc_status scan_entries(scc_table *T, const uint64_t *loc, uint64_t *out, int64_t n) { return scan_incl<uint64_t>(T, ScanLocLen{loc}, out, n); }
 
 void launch_eta_shape(scc_table *T, int shape, u128 *eta)
 {
@@ -2819,9 +2864,133 @@ static void launch_combine(const CombineArgs &C, int phi, bool pos, int64_t n, c
     else pos ? go(launch_combine_as<SCC_KMAX - 1, true>) : go(launch_combine_as<SCC_KMAX - 1, false>);
 }
 
-static scc_status build_levels(scc_table *T)
+// The device summary: the totals, then a block of flags, counts and statistics for
+// each level (level 1's holds the validation's result and the row lists' counts)
+constexpr int DSUM_TJ = 2 * (SCC_KMAX + 1);     // u64 index of the 32 per-shape totals
+constexpr int DSUM_STAR = DSUM_TJ + 64;          // uncoloured k-stars (round skipping)
+constexpr int DSUM_SFLAG = DSUM_STAR + 2;        // nonzero: the star count overflowed
+constexpr int DSUM_WORDS = DSUM_SFLAG + 1;
+constexpr size_t DSUM_BYTES = (DSUM_WORDS * 8 + 127) / 128 * 128;
+struct LevelBlock {          // 128 bytes a level
+    int flags;               // 1: count overflow, 2: sum overflow, 4: listed wrongly; level 1: validation
+    int list0;               // 128-bit vertices with high words in sums only; level 1: unused
+    int wide_rows;           // gather rows that need 128 bits
+    int list2;               // 128-bit vertices whose own records have high words
+    uint64_t pool_words;     // level 1: the validation's balance
+    int list5, list6;        // 64-bit vertices / top-sums-only vertices listed
+    int hi_rows;             // rows of high words of a dense level
+    int pad;
+    int narrow_rows;         // gather rows in 64 bits
+    int row_counts[5];       // level 1: k_row_lists
+    LevelStats ls;
+    uint64_t pad2[4];
+};
+static_assert(sizeof(LevelBlock) == 128 && offsetof(LevelBlock, ls) == 64, "the kernels' view: ints by index");
+constexpr size_t SUMMARY_BYTES = DSUM_BYTES + (SCC_KMAX + 1) * sizeof(LevelBlock);
+static int *level_block(const scc_table *T, int h)
 {
-    const DevLut &HL = T->hlut;
+    return (int *)((char *)T->dsum + DSUM_BYTES + h * sizeof(LevelBlock));
+}
+
+// HIP events of finished builds, kept for later ones (creating and destroying some
+// forty a build took longer than the smallest builds' kernels): at most 256 per
+// device, destroyed by scc_release_caches
+namespace {
+std::mutex g_ev_mu;
+auto &g_ev = *new std::map<int, std::vector<hipEvent_t>>();
+constexpr size_t EVENTS_KEPT = 256;
+struct Events {
+    int dev = 0;
+    std::vector<hipEvent_t> all;
+    Events() { (void)hipGetDevice(&dev); }
+    hipEvent_t get()
+    {
+        hipEvent_t e = nullptr;
+        {
+            std::lock_guard<std::mutex> lk(g_ev_mu);
+            auto &v = g_ev[dev];
+            if (!v.empty()) {
+                e = v.back();
+                v.pop_back();
+            }
+        }
+        if (!e && hipEventCreate(&e) != hipSuccess) return nullptr;
+        all.push_back(e);
+        return e;
+    }
+    ~Events()
+    {
+        std::lock_guard<std::mutex> lk(g_ev_mu);
+        auto &v = g_ev[dev];
+        for (hipEvent_t e : all) {
+            if (v.size() < EVENTS_KEPT) v.push_back(e);
+            else (void)hipEventDestroy(e);
+        }
+    }
+};
+}  // namespace
+
+void release_events()
+{
+    std::lock_guard<std::mutex> lk(g_ev_mu);
+    for (auto &d : g_ev)
+        for (hipEvent_t e : d.second) (void)hipEventDestroy(e);
+    g_ev.clear();
+}
+
+// a device's compute units, asked for once
+static int compute_units()
+{
+    static std::mutex mu;
+    static std::map<int, int> known;
+    int dev = 0, n = 0;
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = known.find(dev);
+    if (it != known.end()) return it->second;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
+    known[dev] = n;
+    return n;
+}
+
+// what a finished level's block says
+static scc_status level_result(scc_table *T, int h, const LevelBlock &b)
+{
+    if (b.flags & 1) return set_error(SCC_EOVERFLOW, "a level-%d count needs more than %d bits", h, T->max_bits);
+    if (b.flags & 2) return set_error(SCC_EOVERFLOW, "a level-%d neighbour sum may exceed 128 bits", h);
+    if (b.flags & 4)
+        return set_error(SCC_EDEVICE, "level %d: a vertex listed for the top-level 128-bit combine has more high words", h);
+    T->wide_input_rows[h][0] = b.list0;
+    T->wide_input_rows[h][1] = b.list6;
+    T->wide_input_rows[h][2] = b.list2;
+    T->lev[h].nnz = (int64_t)b.ls.nnz;
+    T->lev[h].wide = (int64_t)b.ls.wide;
+    return SCC_OK;
+}
+
+// a level's neighbour sums (low words) and bounds, in one block
+static bool sums_block(scc_table *T, TableSums &S, int64_t n, int ws)
+{
+    const size_t m = ((size_t)n * 16 + 255) & ~(size_t)255;
+    char *p = (char *)T->alloc(m + (size_t)n * ws * 8 + 8);
+    S.M = (u128 *)p;
+    S.lo = (uint64_t *)(p + m);
+    return p != nullptr;
+}
+
+static scc_status validate_launch(int64_t n, int64_t nnz, const int64_t *row_ptr, const int32_t *col_idx,
+                                  const uint8_t *colors, int k, hipStream_t stream, int *err, unsigned long long *balance);
+static scc_status validate_result(int flags);
+static scc_status totals_launch(scc_table *T);
+static scc_status totals_result(scc_table *T, const uint64_t *h);
+// builds whose records would take at most this much are not slowed by waiting to learn
+// how much they do take
+constexpr size_t LEAN_BYTES = (size_t)256 << 20;
+
+// every level, then the totals
+static scc_status build_levels(scc_table *T, bool validate)
+{
+    const DevLut &HL = T->hl[0];
     const int k = T->k;
     const int64_t n = T->n;
     hipStream_t st = T->stream;
@@ -2836,74 +3005,78 @@ static scc_status build_levels(scc_table *T)
         if (HL.designated[q]) s_need[k - HL.dec_hp[k][q]] = true;
     const int hub_degree = T->hub_degree;
 
-    // [0] flags, [1] 128-bit vertices with high words in neighbour sums only,
-    // [2] wide gather rows, [3] 128-bit vertices whose own records have high
-    // words; bytes 16..23 receive a level's pool size, so that one read returns
-    // it with the flags. A high-word array released while its copy is still
-    // queued is safe: the allocator hooks free in the table's stream order
-    // (hipFree, without hooks, waits for the device).
-    // [0] flags; [1], [3] combine lists; [2] gather's wide rows; [4..5] pool size;
-    // [6], [7] combine lists; [8] rows of high words of a dense level; [10] gather's
-    // narrow rows; bytes 64..95 the level's LevelStats
-    int *err = (int *)T->mem.get(128);
-    std::vector<void *> scratch{err};
+    std::vector<void *> scratch;
     struct Guard {
         scc_table *T; std::vector<void *> *s;
         ~Guard() { for (void *p : *s) T->mem.put(p); }
     } guard{T, &scratch};
+    // (a high-word array released while its copy is still queued is safe: the
+    // allocator hooks free in the table's stream order; hipFree, without hooks,
+    // waits for the device)
     auto get = [&](size_t bytes) { void *p = T->mem.get(bytes); if (p) scratch.push_back(p); return p; };
-    if (!err) return set_error(SCC_ENOMEM, "flags");
-    int32_t *gwide = (int32_t *)get((size_t)n * 4 + 256);   // rows whose neighbour sums need 128 bits
-    if (!gwide) return set_error(SCC_ENOMEM, "wide rows");
+    // the per-vertex scratch in one block: record summaries, running sums, level sums
+    // of sparse levels, row lists (hubs, rows between the short ones and the hubs,
+    // colour-0 rows), the gather's wide rows, the combine's lists
+    auto part = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t p4 = part((size_t)n * 4 + 256), p8 = part((size_t)n * 8 + 256), p16 = part((size_t)n * 16 + 256);
+    char *at = (char *)get(7 * p4 + p8 + p16);
+    if (!at) return set_error(SCC_ENOMEM, "row lists and combine scratch");
+    auto take = [&](size_t b) { char *p = at; at += b; return (void *)p; };
+    u128 *Nsc = (u128 *)take(p16);
+    uint64_t *words = (uint64_t *)take(p8);
+    uint32_t *meta = (uint32_t *)take(p4);
+    int32_t *hubs = (int32_t *)take(p4), *mids = (int32_t *)take(p4), *zrows = (int32_t *)take(p4);
+    int32_t *gwide = (int32_t *)take(p4);   // rows whose neighbour sums need 128 bits
+    int *wide_list = (int *)take(p4);
+    // row lists of one level: the gather's 64-bit rows where its rows are sorted,
+    // then the combine's 64-bit vertices (width test per lane) or the grouped
+    // combine's vertices whose bound reaches 2^64
+    int32_t *narrow = (int32_t *)take(p4);
 
     // per-level start/end events (whole level, and its gather), read once at the end
     // and the start of its combine (which ends with the level)
+    Events events;
     hipEvent_t ev[SCC_KMAX + 1][2] = {}, gev[SCC_KMAX + 1][2] = {}, cev[SCC_KMAX + 1] = {};
-    struct EvGuard {
-        hipEvent_t (*a)[2], (*b)[2], *c;
-        ~EvGuard() {
-            for (int h = 0; h <= SCC_KMAX; h++) {
-                for (int j = 0; j < 2; j++) {
-                    if (a[h][j]) (void)hipEventDestroy(a[h][j]);
-                    if (b[h][j]) (void)hipEventDestroy(b[h][j]);
-                }
-                if (c[h]) (void)hipEventDestroy(c[h]);
-            }
-        }
-    } evg{ev, gev, cev};
     for (int h = 1; h <= k; h++) {
         for (int j = 0; j < 2; j++) {
-            HIP_TRY(hipEventCreate(&ev[h][j]));
-            HIP_TRY(hipEventCreate(&gev[h][j]));
+            ev[h][j] = events.get();
+            gev[h][j] = events.get();
         }
-        HIP_TRY(hipEventCreate(&cev[h]));
+        cev[h] = events.get();
+        if (!ev[h][0] || !ev[h][1] || !gev[h][0] || !gev[h][1] || !cev[h]) return set_error(SCC_EDEVICE, "events");
     }
 
     // hub rows and their neighbour chunks, and the rows between the grouped
     // low-degree ones and the hubs (the same for every level)
     int nhub = 0, nmid = 0, nzero = 0, max_deg = 0;
     int64_t low_rows = 0;
-    int32_t *hubs = nullptr, *mids = nullptr, *zrows = nullptr;
     int32_t *chunk_v = nullptr, *chunk_q = nullptr;
     int64_t *chunk_e = nullptr;
     int64_t nchunk = 0;
     bool fused = false;   // hub running sums built with the gather
-    if (n) {
-        hubs = (int32_t *)get((size_t)n * 4 + 8);
-        mids = (int32_t *)get((size_t)n * 4 + 8);
-        zrows = (int32_t *)get((size_t)n * 4 + 8);
-        if (!hubs || !mids || !zrows) return set_error(SCC_ENOMEM, "row lists");
-        HIP_TRY(hipMemsetAsync(err, 0, 32, st));
-        hipLaunchKernelGGL(k_row_lists, dim3((unsigned)((n + ROW_LIST_T - 1) / ROW_LIST_T)), dim3(ROW_LIST_T), 0, st, g,
-                           hub_degree, hubs, mids, zrows, err);
-        int cnt[5] = {0, 0, 0, 0, 0};
-        HIP_TRY(hipMemcpyAsync(cnt, err, sizeof cnt, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        nhub = cnt[0];
-        nmid = cnt[1];
-        low_rows = cnt[2];
-        nzero = cnt[3];
-        max_deg = cnt[4];
+    {
+        // the input's check and the row lists (which read only row_ptr inside its n + 1
+        // entries and the colours), then one wait for both
+        int *b1 = level_block(T, 1);
+        if (validate) {
+            scc_status s = validate_launch(n, T->nnz_g, T->row_ptr, T->col_idx, T->colors, k, st, b1,
+                                           (unsigned long long *)((char *)b1 + offsetof(LevelBlock, pool_words)));
+            if (s) return s;
+        }
+        if (n)
+            hipLaunchKernelGGL(k_row_lists, dim3((unsigned)((n + ROW_LIST_T - 1) / ROW_LIST_T)), dim3(ROW_LIST_T), 0, st, g,
+                               hub_degree, hubs, mids, zrows, (int *)((char *)b1 + offsetof(LevelBlock, row_counts)));
+        LevelBlock r{};
+        if (n) {
+            HIP_TRY(hipMemcpyAsync(&r, b1, sizeof r, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+        }
+        if (scc_status s = validate_result(r.flags | (r.pool_words ? 16 : 0))) return s;
+        nhub = r.row_counts[0];
+        nmid = r.row_counts[1];
+        low_rows = r.row_counts[2];
+        nzero = r.row_counts[3];
+        max_deg = r.row_counts[4];
     }
     if (scc_status se = enqueue_edge_colours(T)) return se;
     if (nhub) {
@@ -2966,9 +3139,7 @@ static scc_status build_levels(scc_table *T)
 
     // level 1 neighbour sums
     TableSums &S1 = T->S[1];
-    S1.lo = (uint64_t *)T->alloc((size_t)n * (k - 1) * 8 + 8);
-    S1.M = (u128 *)T->alloc((size_t)n * 16 + 16);
-    if (!S1.lo || !S1.M) return set_error(SCC_ENOMEM, "level-1 sums");
+    if (!sums_block(T, S1, n, k - 1)) return set_error(SCC_ENOMEM, "level-1 sums");
     HIP_TRY(hipEventRecord(ev[1][0], st));
     if (n)
         hipLaunchKernelGGL(k_gather1, dim3(grid_of((n + WAVE - 1) / WAVE)), dim3(WAVE), 0, st, g, T->ecol, k, S1.lo, S1.M,
@@ -2986,21 +3157,12 @@ static scc_status build_levels(scc_table *T)
     HIP_TRY(hipEventRecord(ev[1][1], st));
     T->gather_bytes[1] = (double)n * 8.0 + (double)T->nnz_g * 5.0 + (double)n * (k - 1) * 8.0;
 
-    uint64_t *words = (uint64_t *)get((size_t)n * 8 + 256);
-    uint32_t *meta = (uint32_t *)get((size_t)n * 4 + 256);
-    u128 *Nsc = (u128 *)get((size_t)n * 16 + 256);
-    int *wide_list = (int *)get((size_t)n * 4 + 256);
-    // row lists of one level: the gather's 64-bit rows where its rows are sorted,
-    // then the combine's 64-bit vertices (width test per lane) or the grouped
-    // combine's vertices whose bound reaches 2^64
-    int32_t *narrow = (int32_t *)get((size_t)n * 4 + 256);
-    if (!words || !meta || !Nsc || !wide_list || !narrow) return set_error(SCC_ENOMEM, "combine scratch");
     // the slots of a level with sparse records, grown to the widest one met so far
     uint16_t *slot_key = nullptr;
     uint64_t *slot_lo = nullptr, *slot_hi = nullptr;
     int slot_w = 0;
-    auto slots = [&](int W) -> bool {
-        if (W <= slot_w) return true;
+    auto slots = [&](int W, bool high) -> bool {
+        if (W <= slot_w && (slot_hi || !high)) return true;
         for (void *p : {(void *)slot_key, (void *)slot_lo, (void *)slot_hi}) {
             scratch.erase(std::remove(scratch.begin(), scratch.end(), p), scratch.end());
             T->mem.put(p);   // stream-ordered
@@ -3008,8 +3170,8 @@ static scc_status build_levels(scc_table *T)
         slot_w = W;
         slot_key = (uint16_t *)get((size_t)n * W * 2 + 256);
         slot_lo = (uint64_t *)get((size_t)n * W * 8 + 256);
-        slot_hi = (uint64_t *)get((size_t)n * W * 8 + 256);
-        return slot_key && slot_lo && slot_hi;
+        slot_hi = high ? (uint64_t *)get((size_t)n * W * 8 + 256) : nullptr;
+        return slot_key && slot_lo && (slot_hi || !high);
     };
 
     int64_t heavy_prev = 0;   // sum of degrees of the vertices whose previous-level N has a high word
@@ -3023,20 +3185,36 @@ static scc_status build_levels(scc_table *T)
     // gather reads a third as much; below, memory decides. Level 2 (one line a
     // vertex) is always dense.
     double density = 1.0;
+    // Nothing to decide on the way: where every bound follows from the largest degree
+    // and stays below 2^64, no vertex can need high words or overflow, and where all
+    // levels dense and the level-k records at their largest are small, memory does not
+    // matter. Then no level waits for the host (of the 0.68 ms of a k = 4 build of
+    // 2000 vertices the kernels took 0.2), and the counts are read with the totals.
+    bool lean = T->width_test != SCC_WIDTH_PER_LANE && n > 0;
+    {
+        size_t bytes = (size_t)n * HL.W[k] * 24;
+        for (int h = 2; h < k; h++) bytes += (size_t)n * HL.plane[h] * 8;
+        u128 a_n[SCC_KMAX + 1] = {0, 1}, a_m[SCC_KMAX + 1] = {0, (u128)max_deg};
+        for (int h = 2; h <= k; h++) {
+            for (int hp = 1; hp < h; hp++) a_n[h] = sat_add(a_n[h], sat_mul(a_n[hp], a_m[h - hp]));
+            a_m[h] = sat_mul(a_n[h], (u128)max_deg);
+        }
+        lean = lean && bytes <= LEAN_BYTES && hi64(a_m[k]) == 0;
+        for (int h = 2; lean && h <= k; h++) max_n[h] = a_n[h];
+    }
     for (int h = 2; h <= k; h++) {
         const bool last = h == k;
+        int *err = level_block(T, h);   // (its ints by index, as the kernels see them: LevelBlock)
         int64_t top_wide_rows = 0;   // rows of the sums gathered now whose high words exist
         HIP_TRY(hipEventRecord(ev[h][0], st));
-        HIP_TRY(hipMemsetAsync(err, 0, 128, st));   // flags, the level's counts of listed rows, its statistics
         const int hs = h - 1;   // neighbour sums needed now
         max_m[hs] = sat_mul(max_n[hs], (u128)max_deg);
         if (hs >= 2 && s_need[hs] && T->lev[hs].P) {
             TableSums &Sx = T->S[hs];
             const TableLevel &Lx = T->lev[hs];
             const size_t row_bytes = (size_t)HL.WS[hs] * 8;
-            Sx.M = (u128 *)T->alloc((size_t)n * 16 + 16);
-            Sx.lo = (uint64_t *)T->alloc((size_t)n * row_bytes + 8);
-            if (!Sx.M || !Sx.lo) return set_error(SCC_ENOMEM, "neighbour sums level %d (%zu bytes)", hs, (size_t)n * row_bytes);
+            if (!sums_block(T, Sx, n, HL.WS[hs]))
+                return set_error(SCC_ENOMEM, "neighbour sums level %d (%zu bytes)", hs, (size_t)n * row_bytes);
             DGatherArgs G{};
             G.g = g; G.ecol = T->ecol; G.L = T->dlut;
             G.hs = hs; G.rr = HL.r[hs]; G.P = Lx.P; G.WS = HL.WS[hs]; G.nq = HL.bk1[hs];
@@ -3170,8 +3348,6 @@ static scc_status build_levels(scc_table *T)
         }
         // combine into slots: a vertex needing 128 bits waits for the second kernel
         TableLevel &Lv = T->lev[h];
-        Lv.loc = (uint64_t *)T->alloc((size_t)n * 8 + 8);
-        if (!Lv.loc) return set_error(SCC_ENOMEM, "level %d locators", h);
         const bool skipped = bal && h == k - 1;
         const bool dense = !skipped && h < k && density >= 0.5;
         // high words of a dense level before its 128-bit vertices are counted, a row per vertex
@@ -3179,15 +3355,24 @@ static scc_status build_levels(scc_table *T)
         struct PutHi { scc_table *T; uint64_t *&p; ~PutHi() { T->mem.put(p); } } put_hi{T, dense_hi};
         u128 max_u = 0;   // bounds every vertex's U of this level
         for (int hp = 1; hp < h; hp++) max_u = sat_add(max_u, sat_mul(max_n[hp], max_m[h - hp]));
+        if (!dense) {
+            Lv.loc = (uint64_t *)T->alloc((size_t)n * 8 + 8);
+            if (!Lv.loc) return set_error(SCC_ENOMEM, "level %d locators", h);
+        }
         if (dense) {
+            // records, level sums and locators in one block
             Lv.P = HL.plane[h];
-            Lv.pool = (uint64_t *)T->alloc((size_t)n * Lv.P * 8 + 64);
-            Lv.N = (u128 *)T->alloc((size_t)n * 16 + 16);
+            const size_t rec = part((size_t)n * Lv.P * 8 + 64);
+            Lv.block_bytes = rec + p16 + p8;
+            char *blk = (char *)T->alloc(Lv.block_bytes);
             if (hi64(max_u)) dense_hi = (uint64_t *)T->mem.get((size_t)n * Lv.P * 8 + 64);
-            if (!Lv.pool || !Lv.N || (hi64(max_u) && !dense_hi))
+            if (!blk || (hi64(max_u) && !dense_hi))
                 return set_error(SCC_ENOMEM, "level %d records (%lld bytes)", h, (long long)n * Lv.P * 8);
+            Lv.pool = (uint64_t *)blk;
+            Lv.N = (u128 *)(blk + rec);
+            Lv.loc = (uint64_t *)(blk + rec + p16);
         } else if (!skipped) {
-            if (!slots(HL.W[h])) return set_error(SCC_ENOMEM, "combine scratch (%lld bytes)", (long long)n * HL.W[h] * 18);
+            if (!slots(HL.W[h], hi64(max_u) != 0)) return set_error(SCC_ENOMEM, "combine scratch (%lld bytes)", (long long)n * HL.W[h] * 18);
             // sized by the level's width alone: allocated while the GPU still works
             Lv.BW = (HL.W[h] + 63) / 64;
             Lv.bm = (uint64_t *)T->alloc((size_t)n * Lv.BW * 8 + 8);
@@ -3269,24 +3454,26 @@ static scc_status build_levels(scc_table *T)
                     hipLaunchKernelGGL(kg, grid, dim3(WAVE), lds_g, st, C, zl ? zrows : nullptr, nr, narrow, err + 1);
                 }
                 // the vertices whose bound reaches 2^64, one per wave
-                int nf = 0;
-                HIP_TRY(hipMemcpyAsync(&nf, err + 6, 4, hipMemcpyDeviceToHost, st));
-                HIP_TRY(hipStreamSynchronize(st));
-                launch_combine(C, phi, pos, n, narrow, nf, lds, st, wide_list, err + 1);
+                if (hi64(max_u)) {
+                    int nf = 0;
+                    HIP_TRY(hipMemcpyAsync(&nf, err + 6, 4, hipMemcpyDeviceToHost, st));
+                    HIP_TRY(hipStreamSynchronize(st));
+                    launch_combine(C, phi, pos, n, narrow, nf, lds, st, wide_list, err + 1);
+                }
             } else if (h == 2 && !zl && !C.bal)
                 hipLaunchKernelGGL(k_combine_level2, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C);
             else if (h == 3 && !zl && !C.bal)
                 hipLaunchKernelGGL(k_combine_level3, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C, wide_list,
                                    err + 1);
             else launch_combine(C, phi, pos, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
+            if (hi64(max_u)) {
             // the 128-bit vertices (at k = 8 most of level 7, nearly all with high
             // words in neighbour sums only) stride over as many waves as each
             // kernel's LDS staging lets the chip hold
-            int dev = 0, ncu = 0, per_s = 0, per_own = 0;
+            int per_s = 0, per_own = 0;
+            const int ncu = compute_units();
             const size_t ltw = (size_t)level_term_words(k, h) * 8;   // the level's term descriptors
             const size_t lds_s = (size_t)(HL.xoff[h] + 2 * HL.soff[h]) * 8 + ltw, lds_o = 2 * lds + ltw;
-            HIP_TRY(hipGetDevice(&dev));
-            HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
             const auto kw_s = pos ? k_combine_wide<false, false, true> : k_combine_wide<false, false, false>;
             const auto kw_o = pos ? k_combine_wide<true, true, true> : k_combine_wide<true, true, false>;
             const auto kw_t = pos ? k_combine_wide<false, true, true> : k_combine_wide<false, true, false>;
@@ -3308,38 +3495,30 @@ static scc_status build_levels(scc_table *T)
                 hipLaunchKernelGGL(kw_t, dim3((unsigned)gt), dim3(WAVE), lds_t, st, Ct,
                                    (const int *)narrow, err + 7);
             }
+            }
         }
         if (n)
             hipLaunchKernelGGL(k_level_stats, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0, st, g,
-                               meta, C.Nout, (unsigned long long *)(err + 16));
+                               meta, C.Nout, (unsigned long long *)(err + 16), dense && !dense_hi ? Lv.loc : nullptr);
         if (!dense) {
-            // record sizes and offsets; the pool size, the statistics and the error flags in one read
-            if (n) hipLaunchKernelGGL(k_words, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, meta, words);
-            scc_status sst = scan_incl<uint64_t>(T, words, words, n);
+            // record sizes and offsets
+            scc_status sst = scan_incl<uint64_t>(T, ScanMetaWords{meta}, words, n);
             if (sst) return sst;
             if (n) HIP_TRY(hipMemcpyAsync(err + 4, words + (n - 1), 8, hipMemcpyDeviceToDevice, st));
-        } else if (n && !dense_hi) {
-            hipLaunchKernelGGL(k_dense_loc, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, meta, 0, err + 8,
-                               (int32_t *)nullptr, Lv.loc);
         }
-        struct { int f[4]; uint64_t total; int g[2]; int u[8]; LevelStats ls; } hr{};   // the layout of err
-        static_assert(sizeof hr == 96, "the layout of err");
-        HIP_TRY(hipMemcpyAsync(&hr, err, sizeof hr, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        const int *herr = hr.f;
-        const uint64_t total = n ? hr.total : 0;
-        if (herr[0] & 1) return set_error(SCC_EOVERFLOW, "a level-%d count needs more than %d bits", h, T->max_bits);
-        if (herr[0] & 2) return set_error(SCC_EOVERFLOW, "a level-%d neighbour sum may exceed 128 bits", h);
-        if (herr[0] & 4)
-            return set_error(SCC_EDEVICE, "level %d: a vertex listed for the top-level 128-bit combine has more high words", h);
-        heavy_prev = (int64_t)hr.ls.heavy;
-        T->wide_input_rows[h][0] = herr[1];
-        T->wide_input_rows[h][1] = hr.g[1];
-        T->wide_input_rows[h][2] = herr[3];
-        Lv.nnz = (int64_t)hr.ls.nnz;
-        Lv.wide = (int64_t)hr.ls.wide;
-        max_n[h] = hr.ls.max_n == ~0ull ? ~(u128)0 : (u128)hr.ls.max_n;
-        density = n ? (double)Lv.nnz / ((double)n * HL.W[h]) : 1.0;
+        LevelBlock hr{};
+        if (!lean) {
+            // the pool size, the statistics and the error flags in one read
+            HIP_TRY(hipMemcpyAsync(&hr, err, sizeof hr, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            if (scc_status s = level_result(T, h, hr)) return s;
+            heavy_prev = (int64_t)hr.ls.heavy;
+            max_n[h] = hr.ls.max_n == ~0ull ? ~(u128)0 : (u128)hr.ls.max_n;
+            density = n ? (double)Lv.nnz / ((double)n * HL.W[h]) : 1.0;
+        }
+        // (lean: the largest the records can be, every shape at every root in 64 bits)
+        const uint64_t total = !n ? 0 : !lean ? hr.pool_words
+                             : (uint64_t)(C.zero_only ? nzero : n) * (REC_HDR + key_words((uint32_t)HL.W[h]) + (uint32_t)HL.W[h]);
         if (dense) {
             Lv.pool_words = (uint64_t)n * Lv.P;
             if (dense_hi) {
@@ -3366,7 +3545,8 @@ static scc_status build_levels(scc_table *T)
             continue;
         }
         Lv.pool_words = total;
-        Lv.pool = (uint64_t *)T->alloc((size_t)total * 8 + 64);
+        Lv.block_bytes = (size_t)total * 8 + 64;
+        Lv.pool = (uint64_t *)T->alloc(Lv.block_bytes);
         if (!Lv.pool) return set_error(SCC_ENOMEM, "level %d pool (%llu words)", h, (unsigned long long)total);
         if (n) {
             PackView P{n, HL.W[h], Lv.BW, HL.nkeys, meta, words, slot_key, slot_lo, slot_hi, Nsc, Lv.pool, Lv.loc,
@@ -3385,10 +3565,25 @@ static scc_status build_levels(scc_table *T)
         T->hub_count_pre = nhub;
         T->hubpre_ready = true;
     }
-    // every level's duration (the stream is drained by the totals that follow)
-    HIP_TRY(hipEventSynchronize(ev[k][1]));
+    // the totals, and one read of the device summary
+    hipEvent_t tev[2] = {events.get(), events.get()};
+    if (!tev[0] || !tev[1]) return set_error(SCC_EDEVICE, "events");
+    HIP_TRY(hipEventRecord(tev[0], st));
+    if (scc_status s = totals_launch(T)) return s;
+    HIP_TRY(hipEventRecord(tev[1], st));
+    char sum[SUMMARY_BYTES];
+    HIP_TRY(hipMemcpyAsync(sum, T->dsum, sizeof sum, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    for (int h = 2; lean && h <= k; h++) {
+        if (bal && h == k - 1) continue;
+        LevelBlock hr;
+        memcpy(&hr, sum + DSUM_BYTES + h * sizeof hr, sizeof hr);
+        if (scc_status s = level_result(T, h, hr)) return s;
+        if (h == k) T->lev[k].pool_words = hr.pool_words;
+    }
+    if (scc_status s = totals_result(T, (const uint64_t *)sum)) return s;
+    float ms = 0;
     for (int h = 1; h <= k; h++) {
-        float ms = 0;
         HIP_TRY(hipEventElapsedTime(&ms, ev[h][0], ev[h][1]));
         T->level_ms[h] = ms;
         if (h == 1) T->gather_ms[1] = ms;
@@ -3401,6 +3596,8 @@ static scc_status build_levels(scc_table *T)
             T->gather_ms[h] = ms;
         }
     }
+    HIP_TRY(hipEventElapsedTime(&ms, tev[0], tev[1]));
+    T->totals_ms = ms;
     return SCC_OK;
 }
 
@@ -3420,7 +3617,7 @@ static scc_status gather_stats(scc_table *T)
         HIP_TRY(hipMemsetAsync(acc, 0, 8, st));
         const bool rz = T->rooting == SCC_ROOT_ZERO && hs == T->k - 1;
         if (n) hipLaunchKernelGGL(k_gather_bytes, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, g,
-                                  view(T->lev[hs]), T->S[hs].M, T->hlut.WS[hs], rz ? 1 : 0, acc);
+                                  view(T->lev[hs]), T->S[hs].M, T->hl[0].WS[hs], rz ? 1 : 0, acc);
         unsigned long long b = 0;
         HIP_TRY(hipMemcpyAsync(&b, acc, 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
@@ -3432,7 +3629,7 @@ static scc_status gather_stats(scc_table *T)
     A.g = g; A.k = T->k; A.zero = T->rooting == SCC_ROOT_ZERO;
     for (int h = 2; h <= T->k; h++) A.lev[h] = view(T->lev[h]);
     for (int h = 1; h < T->k; h++) {
-        A.WS[h] = h == 1 ? T->k - 1 : T->hlut.WS[h];
+        A.WS[h] = h == 1 ? T->k - 1 : T->hl[0].WS[h];
         A.s_built[h] = T->S[h].lo != nullptr;
         A.hrow[h] = T->S[h].hrow;
     }
@@ -3450,11 +3647,6 @@ static scc_status gather_stats(scc_table *T)
 
 // Level-k totals, launch half: eta and its running sums, the per-shape totals
 // and the root total land in the device summary; nothing waits for the device.
-constexpr int DSUM_TJ = 2 * (SCC_KMAX + 1);     // u64 index of the 32 per-shape totals
-constexpr int DSUM_TOT = DSUM_TJ + 64;           // u64 index of the root total
-constexpr int DSUM_STAR = DSUM_TOT + 2;          // uncoloured k-stars (round skipping)
-constexpr int DSUM_SFLAG = DSUM_STAR + 2;        // nonzero: the star count overflowed
-constexpr int DSUM_WORDS = DSUM_SFLAG + 1;
 
 static scc_status totals_launch(scc_table *T)
 {
@@ -3463,8 +3655,8 @@ static scc_status totals_launch(scc_table *T)
     hipStream_t st = T->stream;
     GraphView g{n, T->row_ptr, T->col_idx, T->colors};
     const bool zero = T->rooting == SCC_ROOT_ZERO;
-    T->eta = (u128 *)T->alloc((size_t)n * 16 + 16);
-    T->pre = (u128 *)T->alloc((size_t)n * 16 + 16);
+    T->eta = (u128 *)T->alloc((size_t)n * 32 + 32);   // eta, then its running sums
+    T->pre = T->eta ? T->eta + n + 1 : nullptr;
     const int64_t nb = std::max<int64_t>(1, std::min<int64_t>((n + TOT_WAVES - 1) / TOT_WAVES, 8192));
     u128 *part = (u128 *)T->mem.get((size_t)nb * 32 * 16);
     if (!T->eta || !T->pre || !part) { T->mem.put(part); return set_error(SCC_ENOMEM, "totals"); }
@@ -3472,12 +3664,11 @@ static scc_status totals_launch(scc_table *T)
     if (n)
         hipLaunchKernelGGL(k_totals, dim3((unsigned)nb), dim3(TOT_WAVES * WAVE), 0, st, g, T->dlut, view(T->lev[k]),
                            zero ? 1 : 0, T->eta, part);
-    hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)T->hlut.num_unr), dim3(256), 0, st, part, (int)(n ? nb : 0),
-                       T->hlut.num_unr, tjd);
+    hipLaunchKernelGGL(k_reduce_parts, dim3((unsigned)T->hl[0].num_unr), dim3(256), 0, st, part, (int)(n ? nb : 0),
+                       T->hl[0].num_unr, tjd);
     T->mem.put(part);   // stream-ordered
     scc_status s = scan_u128(T, T->eta, T->pre, n);
     if (s) return s;
-    if (n) HIP_TRY(hipMemcpyAsync(T->dsum + DSUM_TOT, T->pre + (n - 1), 16, hipMemcpyDeviceToDevice, st));
     if (T->rooting == SCC_ROOT_BALANCED) {
         // stars: per-vertex counts, their running sums (the direct star sampler's
         // centre draw) and the total
@@ -3497,13 +3688,9 @@ static scc_status totals_launch(scc_table *T)
     return SCC_OK;
 }
 
-// finish half: one read of the device summary (waits for the table's stream)
-static scc_status totals_finish(scc_table *T)
+// finish half, from a host copy of the device summary
+static scc_status totals_result(scc_table *T, const uint64_t *h)
 {
-    uint64_t h[DSUM_WORDS];
-    hipError_t e = hipMemcpyAsync(h, T->dsum, sizeof h, hipMemcpyDeviceToHost, T->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(T->stream);
-    if (e != hipSuccess) return set_error(SCC_EDEVICE, "totals: %s", hipGetErrorString(e));
     const int k = T->k;
     const bool zero = T->rooting == SCC_ROOT_ZERO;
     for (int lv = 2; lv <= k && !T->level_stats; lv++) {
@@ -3511,7 +3698,8 @@ static scc_status totals_finish(scc_table *T)
         T->lev[lv].wide = (int64_t)h[2 * lv + 1];
     }
     T->lev[1].nnz = T->n;
-    const u128 tot = T->n ? mk128(h[DSUM_TOT], h[DSUM_TOT + 1]) : (u128)0;
+    u128 tot = 0;   // the sum of eta: every level-k count belongs to one shape
+    for (int j = 0; j < T->hl[0].num_unr; j++) tot += mk128(h[DSUM_TJ + 2 * j], h[DSUM_TJ + 2 * j + 1]);
     T->root_total = tot;
     if (T->rooting == SCC_ROOT_BALANCED) {
         // every copy of a non-star shape is counted once per node of its
@@ -3519,9 +3707,9 @@ static scc_status totals_finish(scc_table *T)
         if (h[DSUM_SFLAG]) return set_error(SCC_EOVERFLOW, "the number of %d-stars needs more than 128 bits", k);
         T->stars = T->n ? mk128(h[DSUM_STAR], h[DSUM_STAR + 1]) : (u128)0;
         u128 t = 0;
-        for (int j = 0; j < T->hlut.num_unr; j++) {
+        for (int j = 0; j < T->hl[0].num_unr; j++) {
             const u128 tj = mk128(h[DSUM_TJ + 2 * j], h[DSUM_TJ + 2 * j + 1]);
-            const int orb = T->hlut.bal_orbit[j];
+            const int orb = T->hl[0].bal_orbit[j];
             if (orb == 0) {
                 if (tj) return set_error(SCC_EINVAL, "internal: counts of the star at level %d", k);
                 T->tj[j] = 0;
@@ -3534,7 +3722,7 @@ static scc_status totals_finish(scc_table *T)
         T->t = t;
         return SCC_OK;
     }
-    for (int j = 0; j < T->hlut.num_unr; j++) {
+    for (int j = 0; j < T->hl[0].num_unr; j++) {
         const u128 tj = mk128(h[DSUM_TJ + 2 * j], h[DSUM_TJ + 2 * j + 1]);
         T->tj[j] = zero ? tj : tj / (u128)k;
     }
@@ -3542,23 +3730,14 @@ static scc_status totals_finish(scc_table *T)
     return SCC_OK;
 }
 
-static scc_status build_totals(scc_table *T)
+// the same, read now (waits for the table's stream)
+static scc_status totals_finish(scc_table *T)
 {
-    hipEvent_t e[2] = {};
-    struct G { hipEvent_t *e; ~G() { for (int i = 0; i < 2; i++) if (e[i]) (void)hipEventDestroy(e[i]); } } gd{e};
-    HIP_TRY(hipEventCreate(&e[0]));
-    HIP_TRY(hipEventCreate(&e[1]));
-    HIP_TRY(hipEventRecord(e[0], T->stream));
-    scc_status s = totals_launch(T);
-    if (s) return s;
-    HIP_TRY(hipEventRecord(e[1], T->stream));
-    s = totals_finish(T);
-    if (s) return s;
-    float ms = 0;
-    HIP_TRY(hipEventSynchronize(e[1]));
-    HIP_TRY(hipEventElapsedTime(&ms, e[0], e[1]));
-    T->totals_ms = ms;
-    return SCC_OK;
+    uint64_t h[DSUM_WORDS];
+    hipError_t e = hipMemcpyAsync(h, T->dsum, sizeof h, hipMemcpyDeviceToHost, T->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(T->stream);
+    if (e != hipSuccess) return set_error(SCC_EDEVICE, "totals: %s", hipGetErrorString(e));
+    return totals_result(T, h);
 }
 
 // A dense level rewritten with sparse records and bitmaps, in T's memory.
@@ -3579,8 +3758,9 @@ static scc_status sparse_from_dense(scc_table *T, int h)
     TableLevel to;
     to.nnz = Lv.nnz; to.wide = Lv.wide;
     to.pool_words = total;
-    to.BW = (T->hlut.W[h] + 63) / 64;
-    to.pool = (uint64_t *)T->alloc((size_t)total * 8 + 64);
+    to.BW = (T->hl[0].W[h] + 63) / 64;
+    to.block_bytes = (size_t)total * 8 + 64;
+    to.pool = (uint64_t *)T->alloc(to.block_bytes);
     to.loc = (uint64_t *)T->alloc((size_t)n * 8 + 8);
     to.bm = (uint64_t *)T->alloc((size_t)n * to.BW * 8 + 8);
     if (!to.pool || !to.loc || !to.bm) return set_error(SCC_ENOMEM, "level %d sparse records (%llu words)", h,
@@ -3589,11 +3769,8 @@ static scc_status sparse_from_dense(scc_table *T, int h)
                               words, to.pool, to.loc, to.bm, to.BW);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));
-    const size_t plane = (size_t)Lv.P * 8;
-    T->release(Lv.pool, (size_t)n * plane + 64);
+    T->release(Lv.pool, Lv.block_bytes);
     if (Lv.hi) T->release(Lv.hi, (Lv.pool_words - (uint64_t)n * Lv.P) * 8 + 64);
-    T->release(Lv.N, (size_t)n * 16 + 16);
-    T->release(Lv.loc, (size_t)n * 8 + 8);
     Lv = to;
     return SCC_OK;
 }
@@ -3630,7 +3807,7 @@ static scc_status compact_levels(scc_table *T)
         if (n) hipLaunchKernelGGL(k_vlc_write, dim3(grid), dim3(WAVE), 0, st, n, view(Lv), words, pool, loc);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipStreamSynchronize(st));
-        T->release(Lv.pool, (size_t)Lv.pool_words * 8 + 64);
+        T->release(Lv.pool, Lv.block_bytes);
         T->release(Lv.loc, (size_t)n * 8 + 8);
         Lv.pool = pool;
         Lv.loc = loc;
@@ -3641,14 +3818,38 @@ static scc_status compact_levels(scc_table *T)
     return SCC_OK;
 }
 
-static scc_status make_key_maps(scc_table *T)
+KTables::~KTables()
 {
-    const DevLut &L = T->hlut;
-    const int k = T->k;
-    // the maps live in the table's host copy, so that their upload needs no wait here
+    (void)hipFree(lut);        // (waits for the device: nothing reads them any more)
+    (void)hipFree(key_sidx);
+}
+
+static std::mutex g_kt_mu;
+// (device, k); not destroyed at exit, when the runtime may be gone
+static auto &g_kt = *new std::map<std::pair<int, int>, std::shared_ptr<const KTables>>();
+
+void release_k_tables()
+{
+    std::lock_guard<std::mutex> lk(g_kt_mu);
+    g_kt.clear();
+}
+
+scc_status k_tables(int k, hipStream_t st, std::shared_ptr<const KTables> *out)
+{
+    int dev = 0;
+    HIP_TRY(hipGetDevice(&dev));
+    std::lock_guard<std::mutex> lk(g_kt_mu);
+    auto it = g_kt.find({dev, k});
+    if (it != g_kt.end()) {
+        *out = it->second;
+        return SCC_OK;
+    }
+    auto K = std::make_shared<KTables>();
+    build_lut(k, &K->host);
+    const DevLut &L = K->host;
     const size_t nk = (size_t)k * L.nkeys;
-    T->key_maps_host.assign(3 * nk, (int16_t)-1);
-    int16_t *sidx = T->key_maps_host.data(), *xidx = sidx + nk, *xpos = xidx + nk;
+    std::vector<int16_t> maps(3 * nk, (int16_t)-1);
+    int16_t *sidx = maps.data(), *xidx = sidx + nk, *xpos = xidx + nk;
     for (int h = 1; h <= k; h++)
         for (int t = 0; t < L.r[h]; t++)
             for (int ci = 0; ci < L.bk[h]; ci++) {
@@ -3665,15 +3866,30 @@ static scc_status make_key_maps(scc_table *T)
                     }
                 }
             }
-    T->key_sidx = (int16_t *)T->alloc(3 * nk * 2);
-    T->key_xidx = T->key_sidx ? T->key_sidx + nk : nullptr;
-    T->key_xpos = T->key_sidx ? T->key_xidx + nk : nullptr;
-    T->dlut = (DevLut *)T->alloc(sizeof(DevLut));
-    T->dsum = (uint64_t *)T->alloc(DSUM_WORDS * 8);
-    if (!T->key_sidx || !T->dlut || !T->dsum) return set_error(SCC_ENOMEM, "lookup tables");
-    HIP_TRY(hipMemsetAsync(T->dsum, 0, DSUM_WORDS * 8, T->stream));
-    HIP_TRY(hipMemcpyAsync(T->key_sidx, sidx, 3 * nk * 2, hipMemcpyHostToDevice, T->stream));
-    HIP_TRY(hipMemcpyAsync(T->dlut, &T->hlut, sizeof(DevLut), hipMemcpyHostToDevice, T->stream));
+    if (hipMalloc((void **)&K->lut, sizeof(DevLut)) != hipSuccess ||
+        hipMalloc((void **)&K->key_sidx, 3 * nk * 2) != hipSuccess)
+        return set_error(SCC_ENOMEM, "lookup tables");
+    K->key_xidx = K->key_sidx + nk;
+    K->key_xpos = K->key_xidx + nk;
+    HIP_TRY(hipMemcpyAsync(K->lut, &K->host, sizeof(DevLut), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(K->key_sidx, maps.data(), 3 * nk * 2, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));   // complete for every stream that uses them from now on
+    g_kt[{dev, k}] = K;
+    *out = K;
+    return SCC_OK;
+}
+
+// the lookup tables and the (cleared) device summary
+static scc_status set_up(scc_table *T)
+{
+    scc_status s = k_tables(T->k, T->stream, &T->kt);
+    if (s) return s;
+    T->hl = &T->kt->host;
+    T->dlut = T->kt->lut;
+    T->key_sidx = T->kt->key_sidx; T->key_xidx = T->kt->key_xidx; T->key_xpos = T->kt->key_xpos;
+    T->dsum = (uint64_t *)T->alloc(SUMMARY_BYTES);
+    if (!T->dsum) return set_error(SCC_ENOMEM, "device summary");
+    HIP_TRY(hipMemsetAsync(T->dsum, 0, SUMMARY_BYTES, T->stream));
     return SCC_OK;
 }
 
@@ -3699,28 +3915,23 @@ static scc_status attach_graph(scc_table *T, const scc_csr *g, const uint8_t *co
 }
 
 // Checks a CSR and its colours on the device (Sec. 1.3: a simple undirected
-// graph; Sec. 2: colours in [0, k)): EINVAL on any violation.
-scc_status validate_csr(int64_t n, int64_t nnz, const int64_t *row_ptr, const int32_t *col_idx,
-                        const uint8_t *colors, int k, hipStream_t stream, DevMem &mem)
+// graph; Sec. 2: colours in [0, k)): EINVAL on any violation. Launch half: the
+// flags and the arcs' balance are added to *err and *balance (cleared before).
+static scc_status validate_launch(int64_t n, int64_t nnz, const int64_t *row_ptr, const int32_t *col_idx,
+                                  const uint8_t *colors, int k, hipStream_t stream, int *err, unsigned long long *balance)
 {
     if (n == 0) return nnz == 0 ? SCC_OK : set_error(SCC_EINVAL, "invalid input (an empty graph with nnz = %lld)", (long long)nnz);
-    int *err = (int *)mem.get(16);
-    if (!err) return set_error(SCC_ENOMEM, "validate");
-    struct { int flags, pad; unsigned long long balance; } h{};
-    hipError_t e = hipMemsetAsync(err, 0, 16, stream);
-    if (e == hipSuccess) {
-        GraphView gv{n, row_ptr, col_idx, colors};
-        const int64_t m = std::max(n, nnz);
-        hipLaunchKernelGGL(k_validate_rows, dim3((unsigned)((n + 1 + 255) / 256)), dim3(256), 0, stream, row_ptr, n,
-                           nnz, err);
-        hipLaunchKernelGGL(k_validate_edges, dim3((unsigned)((m + VAL_PER - 1) / VAL_PER)), dim3(VAL_T), 0, stream, gv,
-                           nnz, k, err, (unsigned long long *)(err + 2));
-        e = hipMemcpyAsync(&h, err, 16, hipMemcpyDeviceToHost, stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    }
-    const int herr = h.flags | (h.balance ? 16 : 0);
-    mem.put(err);
-    if (e != hipSuccess) return set_error(SCC_EDEVICE, "validate: %s", hipGetErrorString(e));
+    GraphView gv{n, row_ptr, col_idx, colors};
+    const int64_t m = std::max(n, nnz);
+    hipLaunchKernelGGL(k_validate_rows, dim3((unsigned)((n + 1 + 255) / 256)), dim3(256), 0, stream, row_ptr, n, nnz, err);
+    hipLaunchKernelGGL(k_validate_edges, dim3((unsigned)((m + VAL_PER - 1) / VAL_PER)), dim3(VAL_T), 0, stream, gv, nnz, k,
+                       err, balance);
+    HIP_TRY(hipGetLastError());
+    return SCC_OK;
+}
+
+static scc_status validate_result(int herr)
+{
     if (herr)
         return set_error(SCC_EINVAL, "invalid input (%s%s%s%s%s%s)", herr & 1 ? "colour >= k " : "",
                          herr & 2 ? "row_ptr not increasing from 0 within [0, nnz] " : "",
@@ -3728,6 +3939,21 @@ scc_status validate_csr(int64_t n, int64_t nnz, const int64_t *row_ptr, const in
                          herr & 8 ? "row not strictly increasing " : "", herr & 16 ? "asymmetric edge " : "",
                          herr & 32 ? "row_ptr[n] != nnz" : "");
     return SCC_OK;
+}
+
+scc_status validate_csr(int64_t n, int64_t nnz, const int64_t *row_ptr, const int32_t *col_idx,
+                        const uint8_t *colors, int k, hipStream_t stream, DevMem &mem)
+{
+    int *err = (int *)mem.get(16);
+    if (!err) return set_error(SCC_ENOMEM, "validate");
+    struct Put { DevMem &m; int *p; ~Put() { m.put(p); } } put{mem, err};
+    struct { int flags, pad; unsigned long long balance; } h{};
+    HIP_TRY(hipMemsetAsync(err, 0, 16, stream));
+    scc_status s = validate_launch(n, nnz, row_ptr, col_idx, colors, k, stream, err, (unsigned long long *)(err + 2));
+    if (s) return s;
+    HIP_TRY(hipMemcpyAsync(&h, err, 16, hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    return validate_result(h.flags | (h.balance ? 16 : 0));
 }
 
 static scc_status validate_graph(scc_table *T)
@@ -3761,11 +3987,9 @@ extern "C" scc_status scc_build_table(const scc_csr *g, const uint8_t *colors, i
     T->gather_mode = o.gather_mode;
     T->width_test = o.width_test;
     scc_status s = attach_graph(T, g, colors);
-    if (!s && !o.no_validate) s = validate_graph(T);
-    if (!s) s = make_key_maps(T);
+    if (!s) s = set_up(T);
     T->level_stats = true;
-    if (!s) s = build_levels(T);
-    if (!s) s = build_totals(T);
+    if (!s) s = build_levels(T, !o.no_validate);
     if (!s && o.vlc) s = compact_levels(T);
     if (s) { delete T; return s; }
     *out = T;
@@ -3803,7 +4027,7 @@ extern "C" scc_status scc_table_info_get(const scc_table *t, scc_table_info *out
 {
     if (!t || !out) return set_error(SCC_EINVAL, "NULL argument");
     memset(out, 0, sizeof *out);
-    out->n = t->n; out->k = t->k; out->rooting = t->rooting; out->num_unrooted = t->hlut.num_unr;
+    out->n = t->n; out->k = t->k; out->rooting = t->rooting; out->num_unrooted = t->hl[0].num_unr;
     for (int h = 1; h <= t->k; h++) {
         out->nnz[h] = t->lev[h].nnz;
         out->wide_vertices[h] = t->lev[h].wide;
@@ -3818,7 +4042,7 @@ extern "C" scc_status scc_table_info_get(const scc_table *t, scc_table_info *out
     out->num_hubs = t->nhub;
     out->bytes = t->bytes;
     out->t[0] = lo64(t->t); out->t[1] = hi64(t->t);
-    for (int j = 0; j < t->hlut.num_unr; j++) { out->tj[j][0] = lo64(t->tj[j]); out->tj[j][1] = hi64(t->tj[j]); }
+    for (int j = 0; j < t->hl[0].num_unr; j++) { out->tj[j][0] = lo64(t->tj[j]); out->tj[j][1] = hi64(t->tj[j]); }
     out->stars[0] = lo64(t->stars); out->stars[1] = hi64(t->stars);
     for (int h = 2; h <= t->k; h++) out->record_bytes += (int64_t)t->lev[h].pool_words * 8;
     out->vlc = t->vlc ? 1 : 0;
@@ -4100,7 +4324,6 @@ static scc_table *new_table(const scc_csr *g, const uint8_t *colors, int k, cons
     T->mem.alloc = o.alloc; T->mem.stream = T->stream;
     T->hub_degree = o.hub_degree > 0 ? o.hub_degree : 1024;
     T->hub_chunk = 256;
-    build_lut(k, &T->hlut);
     return T;
 }
 
@@ -4182,7 +4405,7 @@ static scc_status batch_launch(std::vector<BatchInstHost> &H, int tile, int hub_
     std::vector<BInst> inst(ni);
     for (int i = 0; i < ni; i++) {
         scc_table *T = H[i].T;
-        const DevLut &HL = T->hlut;
+        const DevLut &HL = T->hl[0];
         const int k = T->k;
         const bool zero = T->rooting == SCC_ROOT_ZERO;
         BInst &B = inst[i];
@@ -4249,7 +4472,7 @@ static scc_status batch_launch(std::vector<BatchInstHost> &H, int tile, int hub_
     size_t lds = 0;
     int64_t hi_stride = 0;
     for (int i = 0; i < ni; i++) {
-        const DevLut &HL = H[i].T->hlut;
+        const DevLut &HL = H[i].T->hl[0];
         for (int h = 2; h <= H[i].T->k; h++) {
             lds = std::max(lds, (size_t)(HL.xoff[h] + HL.soff[h]) * 8);
             hi_stride = std::max<int64_t>(hi_stride, HL.xoff[h] + HL.soff[h]);
@@ -4317,14 +4540,19 @@ static hipStream_t aux_stream(int dev, int slot)
     return s;
 }
 
+constexpr int64_t PLAIN_NNZ = (int64_t)1 << 21;
+// host threads that build by the level kernels (the 32 graphs: 1, 2, 3 and 4 threads
+// 23.1, 12.4, 10.5 and 14.3 ms; 20 graphs of up to 96 000 entries 9.2, 4.1, 4.4, 7.5)
+constexpr int PLAIN_BUILDERS = 2;
+
 // The batch scheduler: instances with at least plain_nnz CSR entries are built
 // by the level kernels (exactly as scc_build_table builds them), the others
 // together in one persistent launch. When there are both, the persistent launch
 // runs from a second host thread on a second stream while the level kernels
-// run. The level-kernel instances are taken from a shared queue by two host
-// threads on two streams when the two largest of them would fit in free device
-// memory together at 1 KiB per CSR entry (one build's kernels then cover the
-// other's host waits), else by one. Tables built on a scheduler stream are
+// run. The level-kernel instances are taken from a shared queue by PLAIN_BUILDERS host
+// threads, each on a stream of its own, as far as the largest of them would fit in
+// free device memory together at 1 KiB per CSR entry (one build's kernels then cover
+// the other's host waits). Tables built on a scheduler stream are
 // handed back on the caller's stream.
 extern "C" scc_status scc_build_batch(const scc_instance *inst, int n_inst, const scc_build_opts *opt,
                                       const scc_batch_opts *bopt, scc_table **out, scc_batch_report *rep)
@@ -4333,7 +4561,7 @@ extern "C" scc_status scc_build_batch(const scc_instance *inst, int n_inst, cons
     for (int i = 0; i < n_inst; i++) out[i] = nullptr;
     scc_batch_opts bo{};
     if (bopt) bo = *bopt;
-    const int64_t plain_nnz = bo.plain_nnz > 0 ? bo.plain_nnz : (bo.plain_nnz < 0 ? INT64_MAX : ((int64_t)1 << 21));
+    const int64_t plain_nnz = bo.plain_nnz > 0 ? bo.plain_nnz : (bo.plain_nnz < 0 ? INT64_MAX : PLAIN_NNZ);
     std::vector<int> plain, pers;
     for (int i = 0; i < n_inst; i++) (inst[i].g.nnz >= plain_nnz ? plain : pers).push_back(i);
     scc_batch_report R{};
@@ -4377,8 +4605,7 @@ extern "C" scc_status scc_build_batch(const scc_instance *inst, int n_inst, cons
         }
     };
     auto t0 = std::chrono::steady_clock::now();
-    scc_status s = SCC_OK, s2 = SCC_OK;
-    std::string err2;
+    scc_status s = SCC_OK;
     std::atomic<size_t> next{0};
     // builds queued level-kernel instances until the queue is empty or one fails
     auto build_plain = [&](hipStream_t st, bool second, scc_status &res, std::string *err) {
@@ -4397,48 +4624,58 @@ extern "C" scc_status scc_build_batch(const scc_instance *inst, int n_inst, cons
             }
         }
     };
-    hipStream_t st2 = nullptr;
-    if (plain.size() >= 2) {
-        int64_t a = 0, b = 0;   // the two largest level-kernel instances
-        for (int i : plain) {
-            const int64_t z = inst[i].g.nnz;
-            if (z > a) { b = a; a = z; } else if (z > b) b = z;
+    // as many builders as fit in memory together (the largest instances at 1 KiB per
+    // CSR entry), the caller's thread among them
+    struct Builder {
+        hipStream_t st = nullptr;
+        scc_status res = SCC_OK;
+        std::string err;
+        std::thread th;
+    };
+    std::vector<std::unique_ptr<Builder>> builders;
+    int dev = 0;
+    size_t fr = 0, tot = 0;
+    if (plain.size() >= 2 && hipGetDevice(&dev) == hipSuccess && hipMemGetInfo(&fr, &tot) == hipSuccess) {
+        std::vector<int64_t> z;
+        for (int i : plain) z.push_back(inst[i].g.nnz);
+        std::sort(z.rbegin(), z.rend());
+        int64_t sum = z[0];
+        for (size_t q = 1; q < z.size() && (int)builders.size() + 1 < PLAIN_BUILDERS; q++) {
+            sum += z[q];
+            if ((double)fr <= 1024.0 * (double)sum) break;
+            const hipStream_t as = aux_stream(dev, (int)builders.size() + 1);
+            if (!as) break;
+            builders.push_back(std::make_unique<Builder>());
+            builders.back()->st = as;
         }
-        size_t fr = 0, tot = 0;
-        int dev = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipMemGetInfo(&fr, &tot) == hipSuccess &&
-            (double)fr > 1024.0 * (double)(a + b))
-            st2 = aux_stream(dev, 1);
     }
-    std::thread plain2;
-    if (st2) {
-        int dev = 0;
-        HIP_TRY(hipGetDevice(&dev));
-        plain2 = std::thread([&, dev] {
+    for (auto &bp : builders) {
+        Builder *B = bp.get();
+        B->th = std::thread([&, B] {
             if (hipSetDevice(dev) != hipSuccess) {
-                s2 = SCC_EDEVICE;
-                err2 = "hipSetDevice failed in the batch scheduler's thread";
+                B->res = SCC_EDEVICE;
+                B->err = "hipSetDevice failed in the batch scheduler's thread";
                 next = plain.size();
                 return;
             }
-            build_plain(st2, true, s2, &err2);
+            build_plain(B->st, true, B->res, &B->err);
+            if (!B->res && hipStreamSynchronize(B->st) != hipSuccess) {
+                B->res = SCC_EDEVICE;
+                B->err = "synchronising the batch scheduler's stream";
+            }
         });
     }
     build_plain(nullptr, false, s, nullptr);
-    if (plain2.joinable()) {
-        plain2.join();
-        if (!s2 && hipStreamSynchronize(st2) != hipSuccess) {
-            s2 = SCC_EDEVICE;
-            err2 = "synchronising the batch scheduler's second stream";
-        }
-        for (int i : plain)   // finished on the second stream: hand over to the caller's
-            if (out[i] && out[i]->stream == st2) {
+    for (auto &B : builders) {
+        B->th.join();
+        for (int i : plain)   // finished on a scheduler stream: hand over to the caller's
+            if (out[i] && out[i]->stream == B->st) {
                 out[i]->stream = caller;
                 out[i]->mem.stream = caller;
             }
-        if (!s && s2) {
-            s = s2;
-            set_error(s2, "%s", err2.c_str());
+        if (!s && B->res) {
+            s = B->res;
+            set_error(s, "%s", B->err.c_str());
         }
     }
     const double plain_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -4501,9 +4738,9 @@ static scc_status batch_persistent(const scc_instance *inst, int n_inst, const s
         scc_status s = attach_graph(T, &I.g, I.colors);
         if (!s && !o.no_validate) s = validate_graph(T);
         if (s) return fail(s);
-        s = make_key_maps(T);
+        s = set_up(T);
         if (s) return fail(s);
-        const DevLut &HL = T->hlut;
+        const DevLut &HL = T->hl[0];
         const int64_t n = T->n;
         // the neighbour sums of every level in one allocation owned by the table, the
         // slots of every level in another (parts on 256-byte boundaries)
@@ -4607,7 +4844,7 @@ static scc_status batch_persistent(const scc_instance *inst, int n_inst, const s
         if (!words || !bsum) return fail(set_error(SCC_ENOMEM, "pack scratch"));
         for (int h = 2; h <= T->k; h++) {
             PackJobDev J{};
-            J.n = n; J.W = T->hlut.W[h]; J.BW = (J.W + 63) / 64; J.nkeys = T->hlut.nkeys;
+            J.n = n; J.W = T->hl[0].W[h]; J.BW = (J.W + 63) / 64; J.nkeys = T->hl[0].nkeys;
             J.meta = H[i].meta[h]; J.words = words + (size_t)n * (h - 2); J.bsum = bsum + (size_t)nb * (h - 2);
             J.skey = H[i].skey[h]; J.slo = H[i].slo[h]; J.shi = H[i].shi[h]; J.N = H[i].N[h];
             J.key_xidx = T->key_xidx; J.colors = T->colors;
@@ -4636,7 +4873,7 @@ static scc_status batch_persistent(const scc_instance *inst, int n_inst, const s
             size_t pool_w = 0, bm_w = 0;
             for (int h = 2; h <= T->k; h++) {
                 pool_w += (size_t)htot[j + h - 2] + 8;
-                bm_w += (size_t)n * ((T->hlut.W[h] + 63) / 64);
+                bm_w += (size_t)n * ((T->hl[0].W[h] + 63) / 64);
             }
             uint64_t *pool = (uint64_t *)T->alloc(pool_w * 8 + 64);
             uint64_t *loc = (uint64_t *)T->alloc((size_t)n * 8 * (T->k - 1) + 64);

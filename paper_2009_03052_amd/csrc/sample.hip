@@ -833,13 +833,6 @@ __global__ void k_occ(GraphView g, const DevLut *Lp, LevelView lev_h, int h, int
     *out = record_lookup(lev_h, v, (uint32_t)key);
 }
 
-__global__ void k_len(int64_t n, const uint64_t *loc, int h1, const uint8_t *colors, uint64_t *len)
-{
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    len[v] = h1 ? 1 : LOC_LEN(loc[v]);
-}
-
 __global__ void __launch_bounds__(WAVE) k_export(int64_t n, LevelView Lv, const DevLut *Lp, int h, const uint8_t *colors,
                                                  const uint64_t *incl, int64_t *off, uint16_t *key,
                                                  uint64_t *lo, uint64_t *hi)
@@ -965,7 +958,7 @@ static scc_status ensure_hub_prefix(scc_table *T)
     hipStream_t st = T->stream;
     if (nh == 0 || k < 2) { T->hubpre_ready = true; return SCC_OK; }
     if (T->vlc) return set_error(SCC_EINVAL, "internal: hub running sums after the variable-length re-encoding");
-    const DevLut &HL = T->hlut;
+    const DevLut &HL = T->hl[0];
     HubPreArgs A{};
     A.g = GraphView{T->n, T->row_ptr, T->col_idx, T->colors};
     A.L = T->dlut; A.k = k; A.nkeys = HL.nkeys; A.zero = T->rooting == SCC_ROOT_ZERO;
@@ -1093,10 +1086,10 @@ scc_status table_prefix(scc_table *T, int shape, const u128 **pre, u128 *total)
 // device arrays of the shape-first draw (built once per table).
 static scc_status ensure_shape_first(scc_table *T)
 {
-    const int nu = T->hlut.num_unr;
+    const int nu = T->hl[0].num_unr;
     std::vector<const u128 *> ptr(32, nullptr);
     for (int j = 0; j < nu; j++) {
-        if (T->hlut.bal_rank[j] < 0 || T->tj[j] == 0) continue;
+        if (T->hl[0].bal_rank[j] < 0 || T->tj[j] == 0) continue;
         u128 tot;
         scc_status s = table_prefix(T, j, &ptr[j], &tot);
         if (s) return s;
@@ -1107,7 +1100,7 @@ static scc_status ensure_shape_first(scc_table *T)
     u128 *dt = (u128 *)T->alloc(32 * sizeof(u128));
     if (!dp || !dt) return set_error(SCC_ENOMEM, "shape-first tables");
     std::vector<u128> tj(32, 0);
-    for (int j = 0; j < nu; j++) tj[j] = T->hlut.bal_rank[j] >= 0 ? T->tj[j] : 0;
+    for (int j = 0; j < nu; j++) tj[j] = T->hl[0].bal_rank[j] >= 0 ? T->tj[j] : 0;
     HIP_TRY(hipMemcpyAsync(dp, ptr.data(), 32 * sizeof(u128 *), hipMemcpyHostToDevice, T->stream));
     HIP_TRY(hipMemcpyAsync(dt, tj.data(), 32 * sizeof(u128), hipMemcpyHostToDevice, T->stream));
     HIP_TRY(hipStreamSynchronize(T->stream));
@@ -1126,7 +1119,7 @@ static scc_status sampling_args(scc_table *T, int shape, SampleArgs *out)
     int mode = 0;
     const uint8_t *A_ecol = nullptr;
     const uint64_t *A_vinfo = nullptr;
-    if (bal && shape == T->hlut.star_unr) {
+    if (bal && shape == T->hl[0].star_unr) {
         mode = 2;
         pre = T->star_pre;
         total = T->stars;
@@ -1161,7 +1154,7 @@ static scc_status sampling_args(scc_table *T, int shape, SampleArgs *out)
     A.mode = mode;
     A.spre = T->bal_spre;
     A.stj = T->bal_stj;
-    A.key_xidx = T->key_xidx; A.key_xpos = T->key_xpos; A.nkeys = T->hlut.nkeys;
+    A.key_xidx = T->key_xidx; A.key_xpos = T->key_xpos; A.nkeys = T->hl[0].nkeys;
     if (T->hub_count_pre) { A.hub_index = T->hub_index; A.hub_poff = T->hub_poff; A.hub_pre = T->hub_pre; }
     A.g = GraphView{T->n, T->row_ptr, T->col_idx, T->colors};
     A.L = T->dlut; A.k = T->k; A.shape = shape; A.zero = T->rooting == SCC_ROOT_ZERO;
@@ -1194,7 +1187,7 @@ scc_status prepare_sampling(scc_table *T, int shape, SampleArgs *out)
 {
     const bool bal = T->rooting == SCC_ROOT_BALANCED;
     scc_status s = SCC_OK;
-    if (bal && shape == T->hlut.star_unr) {
+    if (bal && shape == T->hl[0].star_unr) {
         if (T->stars == 0) return set_error(SCC_EEMPTY, "no %d-star to sample", T->k);
     } else if (bal && shape < 0) {
         if (T->t == 0) return set_error(SCC_EEMPTY, "no colourful %d-treelet to sample", T->k);
@@ -1216,7 +1209,7 @@ scc_status prepare_sampling(scc_table *T, int shape, SampleArgs *out)
 scc_status prepare_all_sampling(scc_table *T)
 {
     SampleArgs A;
-    for (int shape = -1; shape < T->hlut.num_unr; shape++) {
+    for (int shape = -1; shape < T->hl[0].num_unr; shape++) {
         if (sample_weight(T, shape) == 0) continue;
         scc_status s = prepare_sampling(T, shape, &A);
         if (s && s != SCC_EEMPTY) return s;
@@ -1239,7 +1232,7 @@ extern "C" scc_status scc_sample(const scc_table *tc, int32_t shape, int64_t n, 
     scc_table *T = const_cast<scc_table *>(tc);
     if (!T) return set_error(SCC_EINVAL, "table NULL");
     if (n < 0) return set_error(SCC_EINVAL, "n < 0");
-    if (shape < -1 || shape >= T->hlut.num_unr) return set_error(SCC_EINVAL, "shape %d out of range", shape);
+    if (shape < -1 || shape >= T->hl[0].num_unr) return set_error(SCC_EINVAL, "shape %d out of range", shape);
     if (n == 0) return SCC_OK;
     if (!out_verts || !out_parent) return set_error(SCC_EINVAL, "output NULL");
     SampleArgs A;
@@ -1307,7 +1300,7 @@ extern "C" scc_status scc_sample_noalloc(const scc_table *tc, int32_t shape, int
     scc_table *T = const_cast<scc_table *>(tc);
     if (!T) return set_error(SCC_EINVAL, "table NULL");
     if (n < 0) return set_error(SCC_EINVAL, "n < 0");
-    if (shape < -1 || shape >= T->hlut.num_unr) return set_error(SCC_EINVAL, "shape %d out of range", shape);
+    if (shape < -1 || shape >= T->hl[0].num_unr) return set_error(SCC_EINVAL, "shape %d out of range", shape);
     if (n == 0) return SCC_OK;
     if (!out_verts || !out_parent) return set_error(SCC_EINVAL, "output NULL");
     SampleArgs A;
@@ -1335,10 +1328,10 @@ extern "C" scc_status scc_occ(const scc_table *T, int64_t v, int32_t key, uint64
 {
     if (!T || !out) return set_error(SCC_EINVAL, "NULL argument");
     if (v < 0 || v >= T->n) return set_error(SCC_EINVAL, "vertex out of range");
-    if (key >= T->hlut.nkeys || key < -1) return set_error(SCC_EINVAL, "key out of range");
+    if (key >= T->hl[0].nkeys || key < -1) return set_error(SCC_EINVAL, "key out of range");
     int h = 1;
     if (key >= 0)
-        while (h < T->k && key >= T->hlut.off[h + 1]) h++;
+        while (h < T->k && key >= T->hl[0].off[h + 1]) h++;
     u128 *d = (u128 *)const_cast<scc_table *>(T)->mem.get(16);
     if (!d) return set_error(SCC_ENOMEM, "occ");
     GraphView g{T->n, T->row_ptr, T->col_idx, T->colors};
@@ -1372,10 +1365,9 @@ extern "C" scc_status scc_export_level(const scc_table *tc, int h, int64_t *nnz_
     }
     uint64_t *len = (uint64_t *)T->mem.get((size_t)n * 8);
     if (!len) return set_error(SCC_ENOMEM, "export scratch");
-    hipLaunchKernelGGL(k_len, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, T->lev[h].loc, h == 1, T->colors, len);
     hipStream_t keep = T->stream;
     T->stream = st;
-    scc_status s = scan_u64(T, len, len, n);
+    scc_status s = scan_entries(T, h == 1 ? nullptr : T->lev[h].loc, len, n);
     T->stream = keep;
     if (s) { T->mem.put(len); return s; }
     hipLaunchKernelGGL(k_export, dim3((unsigned)n), dim3(WAVE), 0, st, n, lview(T->lev[h]), T->dlut, h, T->colors, len,

@@ -423,8 +423,8 @@ extern "C" scc_status scc_server_create(const scc_server_opts *opts, scc_server 
         S->tables.push_back(T);
         scc_status s = prepare_all_sampling(T);
         if (s) return fail(s);
-        std::vector<SampleArgs> b(T->hlut.num_unr + 1);
-        for (int shape = -1; shape < T->hlut.num_unr; shape++) {
+        std::vector<SampleArgs> b(T->hl[0].num_unr + 1);
+        for (int shape = -1; shape < T->hl[0].num_unr; shape++) {
             SampleArgs A{};
             if (sample_weight(T, shape) > 0) {
                 s = prepare_sampling(T, shape, &A);
@@ -511,7 +511,7 @@ extern "C" scc_status scc_server_submit(scc_server *S, const scc_request *q, int
     if (q->n < 1) return set_error(SCC_EINVAL, "n < 1");
     const scc_table *T = S->tables[q->table];
     if (q->kind == SCC_REQ_SAMPLE) {
-        if (q->shape < -1 || q->shape >= T->hlut.num_unr) return set_error(SCC_EINVAL, "shape %d out of range", q->shape);
+        if (q->shape < -1 || q->shape >= T->hl[0].num_unr) return set_error(SCC_EINVAL, "shape %d out of range", q->shape);
         if (sample_weight(T, q->shape) == 0)
             return set_error(SCC_EEMPTY, "no colourful %d-treelet of this shape", T->k);
     } else if (q->kind == SCC_REQ_AGS_ROUND) {

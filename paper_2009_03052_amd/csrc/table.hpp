@@ -2,6 +2,7 @@
 #pragma once
 
 #include <map>
+#include <memory>
 #include <mutex>
 
 #include "device.hpp"
@@ -12,6 +13,7 @@ constexpr int64_t HUB_BLOCK = 64;
 struct TableLevel {
     uint64_t *pool = nullptr;   // packed records
     uint64_t pool_words = 0;
+    size_t block_bytes = 0;     // the pool's allocation (dense: with the level sums and locators behind it)
     uint64_t *loc = nullptr;    // [n] record locators
     int64_t nnz = 0;
     int64_t wide = 0;
@@ -36,6 +38,17 @@ struct TableSums {
     u128 *M = nullptr;          // [n] sum over neighbours of N_h
 };
 
+// The lookup tables of one k on one device, shared by every table of that k while
+// any of them (or the process's cache, until scc_release_caches) holds them.
+struct KTables {
+    DevLut host;
+    DevLut *lut = nullptr;           // device copy of host
+    int16_t *key_sidx = nullptr;     // [k * nkeys] neighbour-sum index of a key seen from colour c, or -1
+    int16_t *key_xidx = nullptr;     // [k * nkeys] own-count index of a key at a colour-c vertex, or -1
+    int16_t *key_xpos = nullptr;     // [k * nkeys] its position in a dense record, or -1
+    ~KTables();
+};
+
 struct scc_table {
     int k = 0, rooting = SCC_ROOT_ZERO, max_bits = 128;
     int64_t n = 0, nnz_g = 0;
@@ -44,11 +57,10 @@ struct scc_table {
     const uint8_t *colors = nullptr;
     hipStream_t stream = nullptr;
     DevMem mem;
-    DevLut hlut;
-    DevLut *dlut = nullptr;          // device copy of hlut
-    int16_t *key_sidx = nullptr;     // [k * nkeys] neighbour-sum index of a key seen from colour c, or -1
-    int16_t *key_xidx = nullptr;     // [k * nkeys] own-count index of a key at a colour-c vertex, or -1
-    int16_t *key_xpos = nullptr;     // [k * nkeys] its position in a dense record, or -1
+    std::shared_ptr<const KTables> kt;
+    const DevLut *hl = nullptr;      // kt's tables: host, device, key maps
+    const DevLut *dlut = nullptr;
+    const int16_t *key_sidx = nullptr, *key_xidx = nullptr, *key_xpos = nullptr;
     TableLevel lev[SCC_KMAX + 1];
     TableSums S[SCC_KMAX + 1];
     u128 *eta = nullptr;             // [n] admissible level-k total per vertex (all shapes)
@@ -90,7 +102,6 @@ struct scc_table {
     bool vlc = false;                // levels re-encoded with variable-length counts after the build
     int nhub = 0;
     bool stats_done = false;
-    std::vector<int16_t> key_maps_host;   // host copy of key_sidx, key_xidx, key_xpos (source of their upload)
     std::vector<int32_t> hub_host;   // hub vertices (ascending) and their row bounds
     std::vector<int64_t> hub_rows_host;
     // per-hub running sums over neighbours of every neighbour-sum entry, for the
@@ -139,12 +150,18 @@ struct scc_table {
     }
 };
 
+// The lookup tables of k on the current device, made on first use (waits for the
+// stream), and the end of the cache's hold on all of them.
+scc_status k_tables(int k, hipStream_t st, std::shared_ptr<const KTables> *out);
+void release_k_tables();
+void release_events();
+
 // What a sampling call of this shape draws from (shape -1: t; under round
 // skipping the star draws from the uncoloured stars); 0 means nothing to sample.
 inline u128 sample_weight(const scc_table *T, int shape)
 {
     if (shape < 0) return T->t;
-    if (T->rooting == SCC_ROOT_BALANCED && shape == T->hlut.star_unr) return T->stars;
+    if (T->rooting == SCC_ROOT_BALANCED && shape == T->hl[0].star_unr) return T->stars;
     return T->tj[shape];
 }
 
@@ -156,6 +173,8 @@ scc_status table_prefix(scc_table *T, int shape, const u128 **pre, u128 *total);
 scc_status scan_u128(scc_table *T, const u128 *in, u128 *out, int64_t n);
 scc_status scan_u64(scc_table *T, const uint64_t *in, uint64_t *out, int64_t n);
 scc_status scan_u32(scc_table *T, const uint32_t *in, uint32_t *out, int64_t n);
+// running sum of the stored entries of a level's records (loc null: one a vertex)
+scc_status scan_entries(scc_table *T, const uint64_t *loc, uint64_t *out, int64_t n);
 // the colour of every edge's head, unless the table has it (enqueued on T's stream)
 scc_status enqueue_edge_colours(scc_table *T);
 // admissible level-k totals of one unrooted shape per vertex (enqueued on T's stream)
