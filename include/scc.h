@@ -461,7 +461,7 @@ typedef struct {
                           0 = tuned or the compiler's own (about five waves per SIMD) */
     int64_t plain_nnz; /* instances with at least this many CSR entries are built by the
                           level kernels, one after another, before the persistent launch
-                          (which holds the others); 0 = 2^21, negative = none */
+                          (which holds the others); 0 = 2^13, negative = none */
 } scc_batch_opts;
 
 typedef struct {
@@ -486,7 +486,7 @@ typedef struct {
  * build of Sec. 3.4 assigns vertices to a thread pool; here vertex tiles of
  * every instance and level are work items of one resident grid, ordered so
  * that an item only waits for earlier ones. Instances with at least
- * bopt->plain_nnz CSR entries (large enough to fill the GPU alone) are built by
+ * bopt->plain_nnz CSR entries (2^13 by default) are built by
  * the level kernels of scc_build_table instead, on the caller's stream; when
  * there are both kinds the persistent launch runs meanwhile from a second host
  * thread on a library-owned second stream, and its tables are synchronised

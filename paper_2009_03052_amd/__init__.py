@@ -483,7 +483,7 @@ def build_batch(instances, rooting: int = ROOT_ZERO, max_bits: int = 128, tile: 
                 autotune: bool = False, stream=None, use_torch_allocator: bool = True, waves: int = 0,
                 validate: bool = True, plain_nnz: int = 0):
     """``scc_build_batch``: instances is a list of (DeviceGraph, colours, k).
-    Instances with at least ``plain_nnz`` CSR entries (0: 2^21; -1: none) are built by
+    Instances with at least ``plain_nnz`` CSR entries (0: 2^13; -1: none) are built by
     the level kernels, the others in one persistent launch. Returns ([Table], report dict)."""
     n = len(instances)
     arr = (_Instance * n)()

@@ -4540,7 +4540,11 @@ static hipStream_t aux_stream(int dev, int slot)
     return s;
 }
 
-constexpr int64_t PLAIN_NNZ = (int64_t)1 << 21;
+// Which builds of a batch the persistent launch takes: those of fewer CSR entries.
+// Measured (k = 5..7, all in one launch / all by the level kernels): 200 graphs of
+// 2000 entries 25.6 / 36.7 ms, 100 of 4000 15.0 / 18.6, 64 of 8000 11.0 / 12.1, 40 of
+// 16 000 8.2 / 7.7; 8 of 4000 2.9 / 2.0; 32 of 10 800 to 1 570 000 36.6 / 14.0.
+constexpr int64_t PLAIN_NNZ = (int64_t)1 << 13;
 // host threads that build by the level kernels (the 32 graphs: 1, 2, 3 and 4 threads
 // 23.1, 12.4, 10.5 and 14.3 ms; 20 graphs of up to 96 000 entries 9.2, 4.1, 4.4, 7.5)
 constexpr int PLAIN_BUILDERS = 2;

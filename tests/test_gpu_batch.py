@@ -168,3 +168,27 @@ def test_batch_scheduler_error_in_either_half(bad):
     # the library is still usable afterwards
     tabs, rep = S.build_batch([x for j, x in enumerate(dev) if j != i], plain_nnz=5000)
     assert rep["plain_instances"] == len(big) - (1 if bad == "plain" else 0)
+
+
+@pytest.mark.parametrize("plain_nnz", [-1, 0, 1])
+def test_batch_routes_with_wide_counts_and_edges(plain_nnz):
+    # the three routes (all in the persistent launch, by size, all by the level kernels
+    # from two host threads) on graphs around the scheduler's size, empty ones, and a
+    # star whose counts pass 2^64
+    S = scc()
+    leaves = 1 << 16
+    edges = [(0, i) for i in range(1, leaves + 1)] + [(i, i + 1) for i in range(1, 200)]
+    inst = [(gg.csr_from_edges(leaves + 1, np.array(edges, np.int64)),
+             np.concatenate([[0], (np.arange(leaves) % 5) + 1]).astype(np.uint8), 6)]
+    for i, m in enumerate([4095, 4096, 4097, 12]):
+        g = gg.erdos_renyi(1000, m, seed=i)
+        inst.append((g, gg.colors(g.n, 4 + i, seed=i), 4 + i))
+    inst.append((gg.csr_from_edges(5, np.zeros((0, 2), np.int64)), gg.colors(5, 5, seed=1), 5))
+    tabs, rep = S.build_batch([(S.DeviceGraph.from_graph(g), c, k) for g, c, k in inst], plain_nnz=plain_nnz)
+    limit = {-1: 1 << 60, 0: 1 << 13, 1: 1}[plain_nnz]
+    assert rep["plain_instances"] == sum(g.nnz >= limit for g, _, _ in inst)
+    for (g, c, k), bt in zip(inst, tabs):
+        ot = O.Table(g, c, k)
+        assert_tables_equal(bt, ot, k, f"route {plain_nnz} n={g.n} k={k}")
+        if ot.totals()[0]:
+            assert np.array_equal(bt.sample(100, seed=2)[0].cpu().numpy(), ot.sample(100, seed=2)[0])
