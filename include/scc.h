@@ -194,8 +194,8 @@ typedef struct {
                                   64- and 128-bit ones (one per lane) before the gather: where a row
                                   may need 128 bits (levels kept with dense records), or many rows
                                   border a vertex whose level-h sum does */
-    int grouped_combine;       /* bit h: level h was combined four vertices per wave (at most
-                                  64 outputs per vertex) */
+    int grouped_combine;       /* bit h: level h was combined several vertices per wave where
+                                  the rows fill the GPU (at most 64 outputs per vertex) */
 } scc_table_info;
 
 /* Table summary (host struct; no device work). */

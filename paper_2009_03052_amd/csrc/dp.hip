@@ -1381,12 +1381,11 @@ __device__ inline u128 mul_64x128(uint64_t x, u128 s) { return (u128)x * lo64(s)
 // s_hi0 on (the sums below have none); with own counts in 64 bits, an output
 // whose T'' block lies below s_hi0 takes 64 x 64-bit products. tx_lds: the
 // level's term descriptors copied to LDS (level_term_words), else read from L.
-// POS: own counts are staged by dense position (outd, xterm), else by output
-// index (out, term_xs). A level with dense records takes its outputs in position
-// order and stores every one, zeros included.
-template <bool POS> __device__ inline int term_xi(uint32_t xs) { return (int)(POS ? xs & 0x1ffu : xs & 0xffu); }
-template <bool POS> __device__ inline int term_si(uint32_t xs) { return (int)(POS ? xs >> 9 : xs >> 8); }
-template <int ILP, bool POS>
+// A level with dense records takes its outputs in position order and stores every
+// one, zeros included.
+__device__ inline int term_xi(uint32_t xs) { return (int)(xs & 0xffu); }
+__device__ inline int term_si(uint32_t xs) { return (int)(xs >> 8); }
+template <int ILP>
 __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, const uint64_t *Xlo,
                                        const uint64_t *Slo, const uint64_t *Xhi, const uint64_t *Shi, bool owide,
                                        bool wide, int s_hi0, const uint16_t *tx_lds)
@@ -1404,15 +1403,10 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
     uint16_t *sk = A.slot_key + (size_t)v * A.W;
     uint64_t *sl = A.slot_lo + (size_t)v * stride;
     uint64_t *sh = owide ? A.slot_hi + (size_t)v * stride : nullptr;
-    // own counts by position and outputs by index, or the reverse, occur only where
-    // some levels of a table are dense and some are not
-    const uint64_t *outs = POS ? L.outd : L.out;
-    const bool reorder = A.P ? !POS : (POS && h < L.k);
-    const uint16_t *ord = A.P ? L.xord : L.xpos;
     for (int o0 = 0; o0 < Wh; o0 += WAVE) {
         const int o = o0 + lane;
         u128 val = 0;
-        const uint64_t d = o < Wh ? outs[ob + (reorder ? ord[ob + o] : o)] : 0ull;
+        const uint64_t d = o < Wh ? L.out[ob + (A.P ? L.xord[ob + o] : o)] : 0ull;
         if (o < Wh && !(A.bal && !(d >> 63))) {
             const int xb = (int)(d & 0xffffu), sb = (int)((d >> 16) & 0xffffu), tb = (int)((d >> 32) & 0xffffu);
             const int nsplit = (int)((d >> 48) & 0xffu);
@@ -1420,7 +1414,7 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
             // terms four at a time: the four descriptors, then all their LDS
             // operands, are requested before any product, so that the loads of
             // a group overlap instead of one latency per term
-            const uint16_t *txs = tx_lds ? tx_lds + (tb - L.term_base[h][1]) : (POS ? L.xterm : L.term_xs) + tb;
+            const uint16_t *txs = tx_lds ? tx_lds + (tb - L.term_base[h][1]) : L.term_xs + tb;
             const int n4 = ILP >= 4 ? (nsplit & ~3) : 0;
             if (!owide) {
                 uint64_t a64 = 0;
@@ -1430,13 +1424,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
 #pragma unroll
                     for (int j = 0; j < 4; j++) xs[j] = txs[i + j];
 #pragma unroll
-                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + term_xi<POS>(xs[j])]; sv[j] = Slo[sb + term_si<POS>(xs[j])]; }
+                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + term_xi(xs[j])]; sv[j] = Slo[sb + term_si(xs[j])]; }
 #pragma unroll
                     for (int j = 0; j < 4; j++) a64 += xv[j] * sv[j];
                 }
                 for (int i = n4; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    a64 += Xlo[xb + term_xi<POS>(xs)] * Slo[sb + term_si<POS>(xs)];
+                    a64 += Xlo[xb + term_xi(xs)] * Slo[sb + term_si(xs)];
                 }
                 acc = a64;
             } else if (!wide || (!Xhi && sb < s_hi0)) {
@@ -1446,13 +1440,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
 #pragma unroll
                     for (int j = 0; j < 4; j++) xs[j] = txs[i + j];
 #pragma unroll
-                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + term_xi<POS>(xs[j])]; sv[j] = Slo[sb + term_si<POS>(xs[j])]; }
+                    for (int j = 0; j < 4; j++) { xv[j] = Xlo[xb + term_xi(xs[j])]; sv[j] = Slo[sb + term_si(xs[j])]; }
 #pragma unroll
                     for (int j = 0; j < 4; j++) acc += (u128)xv[j] * sv[j];
                 }
                 for (int i = n4; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    acc += (u128)Xlo[xb + term_xi<POS>(xs)] * Slo[sb + term_si<POS>(xs)];
+                    acc += (u128)Xlo[xb + term_xi(xs)] * Slo[sb + term_si(xs)];
                 }
             } else if (!Xhi) {
                 // own counts in 64 bits, neighbour sums in 128
@@ -1463,8 +1457,8 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
                     for (int j = 0; j < 4; j++) xs[j] = txs[i + j];
 #pragma unroll
                     for (int j = 0; j < 4; j++) {
-                        const int si = sb + term_si<POS>(xs[j]);
-                        xv[j] = Xlo[xb + term_xi<POS>(xs[j])];
+                        const int si = sb + term_si(xs[j]);
+                        xv[j] = Xlo[xb + term_xi(xs[j])];
                         sl[j] = Slo[si];
                         sh2[j] = Shi[si - s_hi0];
                     }
@@ -1473,13 +1467,13 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
                 }
                 for (int i = n4; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    const int xi = xb + term_xi<POS>(xs), si = sb + term_si<POS>(xs);
+                    const int xi = xb + term_xi(xs), si = sb + term_si(xs);
                     acc += mul_64x128(Xlo[xi], mk128(Slo[si], Shi[si - s_hi0]));
                 }
             } else {
                 for (int i = 0; i < nsplit; i++) {
                     const uint32_t xs = txs[i];
-                    const int xi = xb + term_xi<POS>(xs), si = sb + term_si<POS>(xs);
+                    const int xi = xb + term_xi(xs), si = sb + term_si(xs);
                     u128 x = mk128(Xlo[xi], Xhi[xi]), s = mk128(Slo[si], Shi[si]);
                     acc += x * s;
                 }
@@ -1524,8 +1518,9 @@ __device__ inline void combine_outputs(const CombineArgs &A, int64_t v, int cv, 
 // registers. The loads count in vmcnt like any other; wait before reading dst.
 __device__ inline void lds_dma_words(const uint64_t *src, uint64_t *dst, int nwords)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x % WAVE;
     const int nd = 2 * nwords;
+#pragma unroll 1
     for (int b = 0; b < nd; b += WAVE)
         if (b + lane < nd)
             __builtin_amdgcn_global_load_lds(
@@ -1547,10 +1542,7 @@ __device__ inline void wait_vm_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // DMA: the neighbour sums reach lo_area (LDS) by direct-to-LDS loads; HI_LDS:
 // hi_area is LDS too, so their high words may go the same way (the batched
 // worker's hi_area is global scratch: filled by ordinary stores)
-// POS: every own level has dense records, staged by position: one run of direct
-// loads per level, like the neighbour sums, with no keys to read and no index to
-// look up first
-template <bool SLOTS, int PMAX, bool DMA, bool HI_LDS = false, bool POS = false>
+template <bool SLOTS, int PMAX, bool DMA, bool HI_LDS = false>
 __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64_t *lo_area, uint64_t *hi_area,
                                          int *wide_list, int *wide_count, bool own_hi = true,
                                          const uint16_t *tx_lds = nullptr)
@@ -1578,9 +1570,6 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     auto dma_sums = [&]() {
         for (int hs = 1; hs <= phi; hs++)
             if (A.Slo[hs]) lds_dma_words(A.Slo[hs] + (size_t)v * L.WS[hs], Slo + L.soff[hs], L.WS[hs]);
-        if (POS)
-            for (int q = 2; q <= phi; q++)
-                lds_dma_words(A.lev[q].P.pool + (size_t)v * A.lev[q].P.P, Xlo + L.xoff[q], L.W[q]);
     };
     const bool late = DMA && !hi_area && A.late_dma;
     if (DMA && !late) dma_sums();
@@ -1599,7 +1588,7 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
                 if (SLOTS) { metap = A.lev[q].meta; Np = A.lev[q].N; }
                 else {
                     locp = A.lev[q].P.loc; poolp = A.lev[q].P.pool;
-                    if (POS || A.lev[q].P.P) Np = A.lev[q].P.N;
+                    if (A.lev[q].P.P) Np = A.lev[q].P.N;
                     else if (A.lev[q].P.BW == 1) bmp = A.lev[q].P.bm;
                 }
             }
@@ -1616,9 +1605,7 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
         if (!DMA && q <= phi && A.Slo[q] && lane < L.WS[q]) sw[q] = A.Slo[q][(size_t)v * L.WS[q] + lane];
     }
     u128 Nq = 0;
-    if (POS) {
-        if (Np) Nq = Np[v];
-    } else if (h_len<SLOTS>(hd)) {
+    if (h_len<SLOTS>(hd)) {
         if (SLOTS || Np) Nq = Np[v];
         else { const uint64_t *rp = poolp + LOC_OFF(hd); Nq = mk128(rp[0], rp[1]); }
     }
@@ -1628,7 +1615,7 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     for (int q = 2; q <= PMAX; q++) {
         ek[q] = 0;
         el[q] = 0;
-        if (!POS && q <= phi) {
+        if (q <= phi) {
             const RecView<SLOTS> r = h_rec<SLOTS>(A.lev[q], readlane64(hd, q));
             if (!SLOTS && A.lev[q].P.P) {
                 if (lane < L.W[q]) el[q] = A.lev[q].P.pool[(size_t)v * A.lev[q].P.P + lane];
@@ -1682,11 +1669,10 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     }
     if (late) dma_sums();
     const bool stage_xhi = wide && Xhi;
-    if (!POS)
-        for (int i = lane; i < XT; i += WAVE) {
-            Xlo[i] = 0;
-            if (stage_xhi) Xhi[i] = 0;
-        }
+    for (int i = lane; i < XT; i += WAVE) {
+        Xlo[i] = 0;
+        if (stage_xhi) Xhi[i] = 0;
+    }
     if (!DMA) {
 #pragma unroll
         for (int q = 1; q <= PMAX; q++)
@@ -1708,21 +1694,11 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
         }
     }
     __syncthreads();
-    if (lane == 0) {   // level 1: the single node, coloured c_v
-        Xlo[L.xoff[1]] = 1;
-        if (POS && stage_xhi) Xhi[L.xoff[1]] = 0;
-    }
-    if (POS && stage_xhi)
-        for (int q = 2; q <= phi; q++) {
-            const LevelView &V = A.lev[q].P;
-            const uint64_t l = readlane64(hd, q);
-            if (LOC_WIDE(l)) lds_dma_words(V.hi + (size_t)LOC_OFF(l) * V.P, Xhi + L.xoff[q], L.W[q]);
-            else for (int i = lane; i < L.W[q]; i += WAVE) Xhi[L.xoff[q] + i] = 0;
-        }
+    if (lane == 0) Xlo[L.xoff[1]] = 1;   // level 1: the single node, coloured c_v
     const int16_t *xidx = A.key_xidx + (size_t)cv * L.nkeys;
 #pragma unroll
     for (int q = 2; q <= PMAX; q++) {
-        if (POS || q > phi) continue;
+        if (q > phi) continue;
         if (!SLOTS && A.lev[q].P.P) {
             // a dense level beside one that is not: from position order to index order
             const LevelView &V = A.lev[q].P;
@@ -1770,26 +1746,26 @@ __device__ inline void combine_vertex_pf(const CombineArgs &A, int64_t v, uint64
     }
     if (DMA) wait_vm_all();
     __syncthreads();
-    combine_outputs<SLOTS ? 1 : 4, POS>(A, v, cv, Xlo, Slo, stage_xhi ? Xhi : nullptr, Shi, owide, wide, s_hi0, tx_lds);
+    combine_outputs<SLOTS ? 1 : 4>(A, v, cv, Xlo, Slo, stage_xhi ? Xhi : nullptr, Shi, owide, wide, s_hi0, tx_lds);
 }
 
 // one workgroup per vertex, low words in LDS; vertices that need 128 bits are
 // listed for k_combine_wide
 // eight waves per SIMD (one register below the compiler's own choice): the
 // combine waits on memory, and the extra waves measured 9 % faster
-template <int PMAX, bool POS>
+template <int PMAX>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_combine(CombineArgs A, int *wide_list, int *wide_count)
 {
     extern __shared__ uint64_t sm[];
-    if ((int64_t)blockIdx.x < A.g.n) combine_vertex_pf<false, PMAX, true, false, POS>(A, blockIdx.x, sm, nullptr, wide_list, wide_count);
+    if ((int64_t)blockIdx.x < A.g.n) combine_vertex_pf<false, PMAX, true>(A, blockIdx.x, sm, nullptr, wide_list, wide_count);
 }
 
 // the listed vertices only (level k under zero-rooting: the colour-0 vertices)
-template <int PMAX, bool POS>
+template <int PMAX>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_combine_list(CombineArgs A, const int32_t *rows, int *wide_list, int *wide_count)
 {
     extern __shared__ uint64_t sm[];
-    combine_vertex_pf<false, PMAX, true, false, POS>(A, __builtin_amdgcn_readfirstlane(rows[blockIdx.x]), sm, nullptr, wide_list, wide_count);
+    combine_vertex_pf<false, PMAX, true>(A, __builtin_amdgcn_readfirstlane(rows[blockIdx.x]), sm, nullptr, wide_list, wide_count);
 }
 
 // The combine of a level with at most 64 outputs per vertex, four vertices per
@@ -1801,7 +1777,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
 // combine_vertex_pf: slot, meta, N and the level's single bitmap word.
 constexpr int CGL = 16;   // lanes per vertex of the grouped combine
 __device__ inline uint64_t grp_shfl64(uint64_t x, int src) { return shfl64(x, (lane_id() & ~(CGL - 1)) + src); }
-template <int PMAX, bool POS>
+template <int PMAX>
 __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8))) k_combine_group(CombineArgs A, const int32_t *rows, int64_t nrows, int32_t *fallback, int *count)
 {
     extern __shared__ uint64_t sm[];
@@ -1827,10 +1803,10 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
             mp = A.M[q];
             if (q >= 2) {
                 locp = A.lev[q].P.loc; poolp = A.lev[q].P.pool;
-                if (POS || A.lev[q].P.P) Np = A.lev[q].P.N;
+                if (A.lev[q].P.P) Np = A.lev[q].P.N;
             }
         }
-    const uint64_t hd = !POS && act && locp ? locp[v] : 0ull;
+    const uint64_t hd = act && locp ? locp[v] : 0ull;
     const u128 Mq = act && mp ? mp[v] : (u128)0;
     u128 Nq = 0;
     if (Np) { if (act) Nq = Np[v]; }
@@ -1855,14 +1831,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
     if (isfb) fallback[fbase + __popcll(fb & lanemask_lt())] = (int32_t)v;
     // staging: own counts X (zeroed, then the records) and neighbour sums S
     if (run) {
-        if (POS) {
-            for (int q = 2; q <= phi; q++) {
-                const uint64_t *gx = A.lev[q].P.pool + (size_t)v * A.lev[q].P.P;
-                for (int j = s; j < L.W[q]; j += CGL) Xlo[L.xoff[q] + j] = gx[j];
-            }
-        } else {
-            for (int j = s; j < XT; j += CGL) Xlo[j] = 0;
-        }
+        for (int j = s; j < XT; j += CGL) Xlo[j] = 0;
         for (int hs = 1; hs <= phi; hs++) {
             if (!A.Slo[hs]) continue;
             const int ws = L.WS[hs];
@@ -1876,7 +1845,7 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
 #pragma unroll
     for (int q = 2; q <= PMAX; q++) {
         const uint64_t hq = grp_shfl64(hd, q);
-        if (POS || !run || q > phi) continue;
+        if (!run || q > phi) continue;
         if (A.lev[q].P.P) {   // a dense level beside one that is not
             const uint64_t *gx = A.lev[q].P.pool + (size_t)v * A.lev[q].P.P;
             for (int j = s; j < L.W[q]; j += CGL) Xlo[L.xoff[q] + L.xord[L.out_off[q] + j]] = gx[j];
@@ -1907,23 +1876,20 @@ __global__ void __launch_bounds__(WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)
     const uint16_t *okey = L.out_key[cv] + ob;
     uint16_t *sk = A.slot_key + (size_t)v * A.W;
     uint64_t *sl = A.slot_lo + (size_t)v * (A.P ? A.P : A.W);
-    const uint64_t *outs = POS ? L.outd : L.out;   // as in combine_outputs
-    const bool reorder = A.P ? !POS : (POS && h < L.k);
-    const uint16_t *ord = A.P ? L.xord : L.xpos;
     uint32_t cnt = 0;
     uint64_t nsum = 0, bmw = 0;
     for (int o0 = 0; o0 < Wh; o0 += CGL) {
         const int o = o0 + s;
         uint64_t val = 0;
-        const uint64_t d = run && o < Wh ? outs[ob + (reorder ? ord[ob + o] : o)] : 0ull;
+        const uint64_t d = run && o < Wh ? L.out[ob + (A.P ? L.xord[ob + o] : o)] : 0ull;
         if (run && o < Wh && !(A.bal && !(d >> 63))) {
             const int xb = (int)(d & 0xffffu), sb = (int)((d >> 16) & 0xffffu), tb = (int)((d >> 32) & 0xffffu);
             const int nsplit = (int)((d >> 48) & 0xffu);
-            const uint16_t *txs = (POS ? L.xterm : L.term_xs) + tb;
+            const uint16_t *txs = L.term_xs + tb;
             uint64_t a64 = 0;
             for (int t = 0; t < nsplit; t++) {
                 const uint32_t xs = txs[t];
-                a64 += Xlo[xb + term_xi<POS>(xs)] * Slo[sb + term_si<POS>(xs)];
+                a64 += Xlo[xb + term_xi(xs)] * Slo[sb + term_si(xs)];
             }
             const uint32_t beta = (uint32_t)((d >> 56) & 0x7fu);
             val = beta == 1 ? a64 : div_exact_small64(a64, beta);
@@ -2047,7 +2013,7 @@ __host__ __device__ inline int level_term_words(int k, int h)
 
 // persistent over the listed vertices: the LDS holds the level's term
 // descriptors (copied once), then each vertex's staging areas
-template <bool OWN, bool BACK, bool POS>
+template <bool OWN, bool BACK>
 __global__ void __launch_bounds__(WAVE) k_combine_wide(CombineArgs A, const int *wide_list, const int *wide_count)
 {
     extern __shared__ uint64_t sm[];
@@ -2056,15 +2022,396 @@ __global__ void __launch_bounds__(WAVE) k_combine_wide(CombineArgs A, const int 
     const DevLut &L = *A.L;
     const int tw = level_term_words(L.k, A.h);
     uint16_t *tx = (uint16_t *)sm;
-    const uint16_t *src = (POS ? L.xterm : L.term_xs) + L.term_base[A.h][1];
+    const uint16_t *src = L.term_xs + L.term_base[A.h][1];
     for (int i = threadIdx.x; i < tw * 4; i += WAVE) tx[i] = src[i];
     uint64_t *lo = sm + tw;
     const int lo_words = L.xoff[A.h] + L.soff[A.h];
     __syncthreads();
     for (int i = blockIdx.x; i < cnt; i += gridDim.x) {
         const int v = __builtin_amdgcn_readfirstlane(BACK ? wide_list[A.g.n - 1 - i] : wide_list[i]);
-        combine_vertex_pf<false, SCC_KMAX - 1, true, true, POS>(A, v, lo, lo + lo_words, nullptr, nullptr, OWN, tx);
+        combine_vertex_pf<false, SCC_KMAX - 1, true, true>(A, v, lo, lo + lo_words, nullptr, nullptr, OWN, tx);
         __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Combine of vertices whose own levels all have dense records
+// ---------------------------------------------------------------------------
+// Bound by HBM: the own records and sums read, the new records written. With a
+// wave per vertex (combine_vertex_pf) the combines of a k = 8 build took 117 ms for
+// 4 million vertices, three times that: each wave read the descriptors and terms of
+// its outputs again, waited alone for every step of its chain of loads, and ran each
+// round of 64 outputs as long as its longest one (level 7: 120 products a lane for
+// 30). Here the waves stay; a workgroup keeps the level's descriptors and terms in
+// LDS, the outputs go by descending number of splits (level 7: 40 products a lane;
+// the counts are stored by position, scattered within the record), the next vertices'
+// bounds are on their way while these are evaluated, and a wave takes GV vertices at
+// once where their counts and sums are few: consecutive vertices' rows are one run of
+// each array. 4 million vertices, k = 8: level 3 4.7 to 0.8 ms, 4 7.8 to 2.7, 5 12.7 to
+// 7.6, 6 25.9 to 11.4, 7 53.4 to 25.2 (floors 0.5, 1.9, 4.9, 10 and 17), 8 13.3 to 9.1;
+// 2 million, k = 7, balanced: 15.5 to 4.9 ms for levels 3 to 5 and 7.
+struct DCombine {
+    const int32_t *rows;       // the vertices, or null for 0 .. nrows - 1
+    int nrows;
+    const int *count;          // the device's count of rows (null: nrows)
+    int back;                  // rows are listed from the end of the list
+    int check;                 // bounds may reach 2^64 (or max_bits)
+    int table_words;           // the workgroup's tables, in 64-bit words
+    int wave_words;            // a wave's staging area
+    int32_t *wide_list;        // vertices with 128-bit inputs (HI = 0)
+    int *wide_count;
+};
+constexpr int DC_WAVES = 4, DC_OCC = 4;   // waves a workgroup; a SIMD (registers)
+
+// Words of the tables: descriptors (8 bytes an output), strides (4 bytes), terms.
+__host__ __device__ inline int dcombine_table_words(int k, int h, int W)
+{
+    return W + (W + 1) / 2 + level_term_words(k, h);
+}
+// A wave's staging area for gv vertices: the word of X_1, X by level (rows of P
+// words), S by level, the outputs of a sparse level; and high words for S from some
+// level on (hi_words), preceded by those of X_1 and X where own.
+__host__ __device__ inline int dcombine_x_words(const DevLut &L, int phi, int gv)
+{
+    int w = 2;
+    for (int q = 2; q <= phi; q++) w += gv * L.plane[q];
+    return w;
+}
+
+// GV vertices a wave; HI = 0: inputs in 64 bits (others are listed), 1: neighbour
+// sums with high words, 2: own counts too (GV = 1)
+template <int GV, int HI>
+__global__ void __launch_bounds__(DC_WAVES * WAVE) __attribute__((amdgpu_waves_per_eu(DC_OCC))) k_dcombine(CombineArgs A, DCombine R)
+{
+    extern __shared__ uint64_t sm[];
+    constexpr int GL = WAVE / GV;
+    const DevLut &L = *A.L;
+    const int h = A.h, Wh = L.W[h];
+    const int plo = A.bal ? 2 : 1, phi = A.bal ? h - 2 : h - 1;
+    const int nrows = R.count ? __builtin_amdgcn_readfirstlane(*R.count) : R.nrows;
+    const int nw = blockDim.x / WAVE;
+    if ((int)blockIdx.x * nw * GV >= nrows) return;
+
+    // the level's tables: first words of T' and T'' | term, splits, beta, position |
+    // strides of a vertex's row in the two blocks
+    uint32_t *dA = (uint32_t *)sm, *dB = dA + Wh, *dC = dB + Wh;
+    uint16_t *tx = (uint16_t *)(sm + Wh + (Wh + 1) / 2);
+    const int XW = dcombine_x_words(L, phi, GV);
+    {
+        const uint32_t ob = L.out_off[h];
+        for (int i = threadIdx.x; i < Wh; i += (int)blockDim.x) {
+            const int p = L.xsort[ob + i];
+            const uint64_t d = L.outd[ob + p];
+            const int xb = (int)(d & 0xffffu), sb = (int)((d >> 16) & 0xffffu);
+            int x = 0, xs = 0, s = 0, ss = 0, xo = 2, so = XW;
+            for (int q = 1; q <= phi; q++) {
+                if (q >= 2 && xb >= L.xoff[q] && xb < L.xoff[q + 1]) { x = xo + xb - L.xoff[q]; xs = L.plane[q]; }
+                if (sb >= L.soff[q] && sb < L.soff[q + 1]) { s = so + sb - L.soff[q]; ss = L.WS[q]; }
+                if (q >= 2) xo += GV * L.plane[q];
+                so += GV * L.WS[q];
+            }
+            const bool skip = A.bal && !(d >> 63);
+            const uint32_t t = (uint32_t)((d >> 32) & 0xffffu) - L.term_base[h][1];
+            const uint32_t to = A.P ? (uint32_t)p : L.xord[ob + p];   // sparse outputs go by key
+            dA[i] = (uint32_t)x | (uint32_t)s << 16;
+            dB[i] = skip ? to << 23 | 1u << 17
+                         : t | (uint32_t)((d >> 48) & 0x3fu) << 11 | (uint32_t)((d >> 56) & 0x3fu) << 17 | to << 23;
+            if (GV > 1) dC[i] = (uint32_t)xs | (uint32_t)ss << 16;
+        }
+        const uint16_t *src = L.xterm + L.term_base[h][1];
+        const int nt = level_term_words(L.k, h) * 4;
+        for (int i = threadIdx.x; i < nt; i += (int)blockDim.x) tx[i] = src[i];
+    }
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
+    const int u = lane / GL, s = lane % GL;
+    uint64_t *area = sm + R.table_words + (size_t)wave * R.wave_words;
+    if (lane < 2) area[lane] = lane == 0;   // X_1 (high words, where staged, begin with the 0)
+    const int SW = GV * L.soff[phi + 1];
+    uint64_t *olo = area + XW + SW;         // outputs of a sparse level, in order
+    uint64_t *ohi = olo + GV * Wh;
+    uint64_t *Xhi = HI == 2 ? area + XW + SW + (A.P ? 0 : 2 * Wh) : nullptr;
+    uint64_t *Shi = HI == 2 ? Xhi + XW : area + XW + SW + (A.P ? 0 : 2 * Wh);
+    __syncthreads();
+
+    // lane s = q of a vertex's group: M_q and, for own levels, N_q and the locator
+    const u128 *mp = nullptr, *Np = nullptr;
+    const uint64_t *locp = nullptr;
+#pragma unroll
+    for (int q = 1; q < SCC_KMAX; q++)
+        if (R.check && s == q && q <= phi) {
+            mp = A.M[q];
+            if (q >= 2) { Np = A.lev[q].P.N; locp = A.lev[q].P.loc; }
+        }
+    const int step = (int)gridDim.x * nw * GV;   // (at most the chip's waves)
+    // lane e: the e-th array to stage (own levels 2..phi, then sums 1..phi), its words
+    // per vertex and its place in the area
+    const uint64_t *arr = nullptr;
+    int arr_row = 0, arr_at = 0;
+    {
+        int at = 2;
+#pragma unroll 1
+        for (int e = 0; e < 2 * phi - 1; e++) {
+            const bool x = e < phi - 1;
+            const int q = x ? e + 2 : e - phi + 2, w = x ? L.plane[q] : L.WS[q];
+            if (lane == e) { arr = x ? A.lev[q].P.pool : A.Slo[q]; arr_row = w; arr_at = at; }
+            at += GV * w;
+        }
+    }
+    auto vertex = [&](int64_t i0) {
+        const int64_t i = i0 + u;
+        return i >= nrows ? -1 : !R.rows ? (int)i : R.back ? R.rows[A.g.n - 1 - i] : R.rows[i];
+    };
+    // the next round's words (fetched a round ahead) and the vertices of the one after it
+    const int first = ((int)blockIdx.x * nw + wave) * GV;
+    int v = vertex(first), vn = vertex((int64_t)first + step);
+    u128 Mq = 0, Nq = 0;
+    uint64_t hd = 0;
+    if (v >= 0) {
+        if (mp) Mq = mp[v];
+        if (Np) Nq = Np[v];
+        if (locp) hd = locp[v];
+    }
+    for (int64_t i0 = first; i0 < nrows; i0 += step) {
+        const int nv = (int)min((int64_t)GV, nrows - i0);
+        // staging: one run per level where the vertices are consecutive
+        {
+            const bool run1 = GV == 1 || !R.rows;
+            const int nrun = run1 ? 1 : nv, per = run1 ? nv : 1;
+            for (int r = 0; r < nrun; r++) {
+                const int64_t vr = __builtin_amdgcn_readlane(v, r * GL);
+#pragma unroll 1
+                for (int e = 0; e < 2 * phi - 1; e++) {
+                    const int w = __builtin_amdgcn_readlane(arr_row, e), at = __builtin_amdgcn_readlane(arr_at, e);
+                    const uint64_t *src = (const uint64_t *)readlane64((uint64_t)arr, e);
+                    if (src) lds_dma_words(src + (size_t)vr * w, area + at + r * w, per * w);
+                }
+            }
+        }
+        const int vc = v;
+        const u128 Mc = Mq, Nc = Nq;
+        const uint64_t hc = hd;
+        v = vn;
+        vn = vertex(i0 + 2 * step);
+        if (v >= 0) {
+            if (mp) Mq = mp[v];
+            if (Np) Nq = Np[v];
+            if (locp) hd = locp[v];
+        }
+        bool run = vc >= 0, owide = false;
+        int hs_hi = 1;
+        uint32_t own_wide = 0, sum_wide = 0;   // HI: bit q, level q has high words
+        if (R.check) {
+            // bound: lane hp contributes N_hp(v) M_{h-hp}(v) (level 1: N = 1)
+            const int g0 = lane & ~(GL - 1);
+            const u128 Mpair = shfl128(Mc, g0 + ((h - s) & (GL - 1)));
+            u128 U = run && s >= plo && s <= phi ? sat_mul(s == 1 ? (u128)1 : Nc, Mpair) : (u128)0;
+#pragma unroll
+            for (int off = 4; off >= 1; off >>= 1) U = sat_add(U, shfl128(U, lane ^ off));
+            if (GL > 8) U = shfl128(U, g0);   // levels 1..7: the sum of the group's first eight lanes
+            const uint64_t gm = (GL == 64 ? ~0ull : (1ull << GL) - 1ull) << g0;
+            const bool xw = (__ballot(run && s >= 2 && s <= phi && LOC_WIDE(hc)) & gm) != 0;
+            const uint64_t sw = (__ballot(run && s >= 1 && s <= phi && hi64(Mc) != 0) & gm) >> g0;
+            if (run && (U == ~(u128)0 || bitlen128(U) > A.max_bits)) {
+                if (s == 0) { atomicOr(A.err, 1); A.meta[vc] = 0; A.Nout[vc] = 0; }
+                run = false;
+            }
+            owide = hi64(U) != 0;
+            if (HI == 0) {
+                if (run && owide && (xw || sw)) {
+                    // own records with high words: from the back of the list
+                    // (wide_count[2]); neighbour sums alone: from its front
+                    if (s == 0) {
+                        if (xw) R.wide_list[A.g.n - 1 - atomicAdd(R.wide_count + 2, 1)] = vc;
+                        else R.wide_list[atomicAdd(R.wide_count, 1)] = vc;
+                    }
+                    run = false;
+                }
+            } else {
+                own_wide = (uint32_t)__ballot(run && s >= 2 && s <= phi && LOC_WIDE(hc));
+                sum_wide = (uint32_t)sw;
+                hs_hi = HI == 2 || !sum_wide ? 1 : __builtin_ctz(sum_wide);
+                if (HI == 1 && A.hi_cap > 0 && L.soff[phi + 1] - L.soff[hs_hi] > A.hi_cap) {
+                    // a launch sized for fewer high words than this vertex has (not
+                    // expected: the listing applies the same test)
+                    if (run && lane == 0) { atomicOr(A.err, 4); A.meta[vc] = 0; A.Nout[vc] = 0; }
+                    run = false;
+                }
+                if (run) {
+                    const int64_t vr = __builtin_amdgcn_readlane(vc, 0);
+                    if (HI == 2) {
+                        int at = 2;
+                        for (int q = 2; q <= phi; q++) {
+                            const int P = L.plane[q];
+                            const uint64_t l = readlane64(hc, q);
+                            if (own_wide >> q & 1) lds_dma_words(A.lev[q].P.hi + (size_t)LOC_OFF(l) * P, Xhi + at, P);
+                            else for (int i = lane; i < P; i += WAVE) Xhi[at + i] = 0;
+                            at += P;
+                        }
+                        if (lane < 2) Xhi[lane] = 0;
+                    }
+                    for (int q = hs_hi; q <= phi; q++) {
+                        if (!A.Slo[q]) continue;
+                        const int ws = L.WS[q];
+                        uint64_t *dst = Shi + (L.soff[q] - L.soff[hs_hi]);
+                        if (sum_wide >> q & 1) lds_dma_words(A.Shi[q] + hi_row(A.Shrow[q], vr) * ws, dst, ws);
+                        else for (int i = lane; i < ws; i += WAVE) dst[i] = 0;
+                    }
+                }
+            }
+        }
+        wait_vm_all();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+
+        const int s_hi0 = XW + L.soff[hs_hi];   // HI: S words from here on have high words
+        uint32_t cnt = 0;
+        u128 nsum = 0;
+        // MODE 0: all in 64 bits; 1: 64 x 64-bit products summed in 128; 2: neighbour
+        // sums in 128 from s_hi0 on; 3: both factors in 128
+        auto outputs = [&](auto mode) {
+            constexpr int MODE = decltype(mode)::value;
+#pragma unroll 1
+            for (int o0 = 0; o0 < Wh; o0 += GL) {
+                const int o = o0 + s;
+                if (!run || o >= Wh) continue;
+                const uint32_t a = dA[o], b = dB[o];
+                int xb = (int)(a & 0xffffu), sb = (int)(a >> 16);
+                if (GV > 1) {
+                    const uint32_t c = dC[o];
+                    xb += u * (int)(c & 0xffffu);
+                    sb += u * (int)(c >> 16);
+                }
+                const uint16_t *tp = tx + (b & 0x7ffu);
+                const int ns = (int)(b >> 11 & 0x3fu), beta = (int)(b >> 17 & 0x3fu), pos = (int)(b >> 23);
+                const uint64_t *X = area + xb, *S = area + sb;
+                u128 val;
+                if (MODE == 0) {
+                    uint64_t acc = 0;
+                    int i = 0;
+#pragma unroll 1
+                    for (; i + 4 <= ns; i += 4) {
+                        uint64_t x[4], y[4];
+#pragma unroll
+                        for (int j = 0; j < 4; j++) { const uint32_t t = tp[i + j]; x[j] = X[t & 0x1ffu]; y[j] = S[t >> 9]; }
+#pragma unroll
+                        for (int j = 0; j < 4; j++) acc += x[j] * y[j];
+                    }
+#pragma unroll 1
+                    for (; i < ns; i++) { const uint32_t t = tp[i]; acc += X[t & 0x1ffu] * S[t >> 9]; }
+                    val = beta == 1 ? acc : div_exact_small64(acc, (uint32_t)beta);
+                } else {
+                    u128 acc = 0;
+                    if (MODE == 1 || (MODE == 2 && sb < s_hi0)) {
+                        int i = 0;
+#pragma unroll 1
+                        for (; i + 4 <= ns; i += 4) {
+                            uint64_t x[4], y[4];
+#pragma unroll
+                            for (int j = 0; j < 4; j++) { const uint32_t t = tp[i + j]; x[j] = X[t & 0x1ffu]; y[j] = S[t >> 9]; }
+#pragma unroll
+                            for (int j = 0; j < 4; j++) acc += (u128)x[j] * y[j];
+                        }
+#pragma unroll 1
+                        for (; i < ns; i++) { const uint32_t t = tp[i]; acc += (u128)X[t & 0x1ffu] * S[t >> 9]; }
+                    } else if (MODE == 2) {
+                        const uint64_t *Y = Shi + (sb - s_hi0);
+                        int i = 0;
+#pragma unroll 1
+                        for (; i + 2 <= ns; i += 2) {
+                            uint64_t x[2], y[2], z[2];
+#pragma unroll
+                            for (int j = 0; j < 2; j++) {
+                                const uint32_t t = tp[i + j];
+                                x[j] = X[t & 0x1ffu]; y[j] = S[t >> 9]; z[j] = Y[t >> 9];
+                            }
+#pragma unroll
+                            for (int j = 0; j < 2; j++) acc += mul_64x128(x[j], mk128(y[j], z[j]));
+                        }
+#pragma unroll 1
+                        for (; i < ns; i++) { const uint32_t t = tp[i]; acc += mul_64x128(X[t & 0x1ffu], mk128(S[t >> 9], Y[t >> 9])); }
+                    } else {
+                        const uint64_t *Y = Shi + (sb - XW), *Z = Xhi + xb;
+                        int i = 0;
+#pragma unroll 1
+                        for (; i + 4 <= ns; i += 4) {
+                            uint64_t x[4], y[4], z[4], w[4];
+#pragma unroll
+                            for (int j = 0; j < 4; j++) {
+                                const uint32_t t = tp[i + j];
+                                x[j] = X[t & 0x1ffu]; w[j] = Z[t & 0x1ffu]; y[j] = S[t >> 9]; z[j] = Y[t >> 9];
+                            }
+#pragma unroll
+                            for (int j = 0; j < 4; j++) acc += mk128(x[j], w[j]) * mk128(y[j], z[j]);
+                        }
+#pragma unroll 1
+                        for (; i < ns; i++) {
+                            const uint32_t t = tp[i];
+                            acc += mk128(X[t & 0x1ffu], Z[t & 0x1ffu]) * mk128(S[t >> 9], Y[t >> 9]);
+                        }
+                    }
+                    // beta divides the sum exactly (Eq. (1) counts each copy beta times)
+                    val = beta == 1 ? acc : div_exact_small(acc, (uint32_t)beta);
+                }
+                if (A.P) {
+                    const size_t at = (size_t)vc * A.P + pos;
+                    A.slot_lo[at] = lo64(val);
+                    if (MODE && owide) A.slot_hi[at] = hi64(val);
+                } else {
+                    olo[u * Wh + pos] = lo64(val);
+                    if (MODE) ohi[u * Wh + pos] = hi64(val);
+                }
+                cnt += val != 0;
+                nsum += val;
+            }
+        };
+        const bool ow = HI > 0 || __any(run && owide);
+        if (HI == 2) outputs(std::integral_constant<int, 3>{});
+        else if (HI == 1) outputs(std::integral_constant<int, 2>{});
+        else if (ow) outputs(std::integral_constant<int, 1>{});
+        else outputs(std::integral_constant<int, 0>{});
+#pragma unroll
+        for (int off = GL / 2; off >= 1; off >>= 1) {
+            cnt += (uint32_t)__shfl((int)cnt, lane ^ off);
+            if (ow) nsum += shfl128(nsum, lane ^ off);
+            else nsum = lo64(nsum) + shfl64(lo64(nsum), lane ^ off);
+        }
+        if (run && s == 0) {
+            A.meta[vc] = cnt | (owide ? 0x80000000u : 0u);
+            A.Nout[vc] = nsum;
+        }
+        if (!A.P) {
+            // the non-zero outputs in ascending key order, and the presence bitmap
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const uint16_t *okey = L.out_key[run ? (int)A.g.colors[vc] : 0] + L.out_off[h];
+            uint16_t *sk = A.slot_key + (size_t)vc * A.W;
+            uint64_t *dl = A.slot_lo + (size_t)vc * A.W, *dh = A.slot_hi + (size_t)vc * A.W;
+            uint32_t at = 0;
+            uint64_t word = 0;
+#pragma unroll 1
+            for (int o0 = 0; o0 < Wh; o0 += GL) {
+                const int o = o0 + s;
+                const bool in = run && o < Wh;
+                const uint64_t lo = in ? olo[u * Wh + o] : 0ull, hi = in && ow ? ohi[u * Wh + o] : 0ull;
+                const bool nz = (lo | hi) != 0;
+                const uint64_t gm = (__ballot(nz) >> (lane & ~(GL - 1))) & (GL == 64 ? ~0ull : (1ull << GL) - 1ull);
+                if (nz) {
+                    const uint32_t e = at + (uint32_t)__popcll(gm & ((1ull << s) - 1ull));
+                    sk[e] = okey[o];
+                    dl[e] = lo;
+                    if (owide) dh[e] = hi;
+                }
+                at += (uint32_t)__popcll(gm);
+                word |= gm << (o0 & 63);
+                if (((o0 + GL) & 63) == 0 || o0 + GL >= Wh) {
+                    if (run && s == 0 && A.bm) A.bm[(size_t)vc * A.BW + (o0 >> 6)] = word;
+                    word = 0;
+                }
+            }
+        }
+        // every LDS read of this round is complete before the next round's loads land
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -2841,27 +3188,81 @@ __global__ void __launch_bounds__(256) k_combine_level3(CombineArgs A, int *wide
     A.Nout[v] = nsum;
 }
 
-template <int PMAX, bool POS>
+template <int PMAX>
 static void launch_combine_as(const CombineArgs &C, int64_t n, const int32_t *rows, int64_t nrows, size_t lds,
                               hipStream_t st, int *wide_list, int *wide_count)
 {
     if (rows) {
         if (nrows)
-            hipLaunchKernelGGL((k_combine_list<PMAX, POS>), dim3((unsigned)nrows), dim3(WAVE), lds, st, C, rows, wide_list,
+            hipLaunchKernelGGL(k_combine_list<PMAX>, dim3((unsigned)nrows), dim3(WAVE), lds, st, C, rows, wide_list,
                                wide_count);
     } else {
-        hipLaunchKernelGGL((k_combine<PMAX, POS>), dim3((unsigned)n), dim3(WAVE), lds, st, C, wide_list, wide_count);
+        hipLaunchKernelGGL(k_combine<PMAX>, dim3((unsigned)n), dim3(WAVE), lds, st, C, wide_list, wide_count);
     }
 }
 
 // phi: the highest own level and sum level that the combine reads
-static void launch_combine(const CombineArgs &C, int phi, bool pos, int64_t n, const int32_t *rows, int64_t nrows,
+static void launch_combine(const CombineArgs &C, int phi, int64_t n, const int32_t *rows, int64_t nrows,
                            size_t lds, hipStream_t st, int *wide_list, int *wide_count)
 {
     auto go = [&](auto f) { f(C, n, rows, nrows, lds, st, wide_list, wide_count); };
-    if (phi <= 3) pos ? go(launch_combine_as<3, true>) : go(launch_combine_as<3, false>);
-    else if (phi <= 5) pos ? go(launch_combine_as<5, true>) : go(launch_combine_as<5, false>);
-    else pos ? go(launch_combine_as<SCC_KMAX - 1, true>) : go(launch_combine_as<SCC_KMAX - 1, false>);
+    if (phi <= 3) go(launch_combine_as<3>);
+    else if (phi <= 5) go(launch_combine_as<5>);
+    else go(launch_combine_as<SCC_KMAX - 1>);
+}
+
+// a device's compute units, asked for once
+static int compute_units()
+{
+    static std::mutex mu;
+    static std::map<int, int> known;
+    int dev = 0, n = 0;
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = known.find(dev);
+    if (it != known.end()) return it->second;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
+    known[dev] = n;
+    return n;
+}
+
+// k_dcombine over R's rows: hi = 0 with inputs in 64 bits, 1 / 2 with high words of
+// the neighbour sums (hi_words of them) / of the own counts too. Vertices a wave: as
+// many as keep its staging within DC_STAGE words (16 waves a CU: 160 KB), fewer where
+// the rows would not fill the chip. Measured, vertices a wave: balanced level 7 of k = 7
+// 3.57 ms (1), 2.15 (2); level 6 of k = 7 0.80 (1), 0.58 (2); level 4 of k = 8 2.71 (4),
+// 3.44 (8, 12 waves a CU); level 5 of k = 8 7.6 (1), 7.5 (2), 8.9 (4). Waves a workgroup:
+// what puts most of them on a CU within 64 KB each.
+constexpr int DC_STAGE = 1200;
+static void launch_dcombine(const CombineArgs &C, const DevLut &L, DCombine R, int hi, int hi_words, hipStream_t st)
+{
+    if (!R.count && !R.nrows) return;
+    const int h = C.h, W = L.W[h], phi = C.bal ? h - 2 : h - 1, ncu = compute_units();
+    auto words = [&](int gv) {
+        int w = dcombine_x_words(L, phi, gv) + gv * L.soff[phi + 1];
+        if (!C.P) w += gv * W * (R.check ? 2 : 1);
+        if (hi) w += hi_words + (hi == 2 ? dcombine_x_words(L, phi, 1) : 0);
+        return (w + 1) & ~1;
+    };
+    int gv = 1;
+    if (!hi)
+        while (gv < 8 && words(2 * gv) <= DC_STAGE && R.nrows >= 2 * gv * ncu * 4 * DC_OCC) gv *= 2;
+    R.wave_words = words(gv);
+    R.table_words = (dcombine_table_words(L.k, h, W) + 1) & ~1;
+    int nw = 1, best = 0, per = 0;
+    size_t lds = 0;
+    for (int w = DC_WAVES; w >= 1; w--) {
+        const size_t b = ((size_t)R.table_words + (size_t)w * R.wave_words) * 8;
+        if (w > 1 && b > 65536) continue;
+        const int blocks = std::min(4 * DC_OCC / w, (int)(163840 / ((b + 2047) / 2048 * 2048)));
+        if (blocks * w > best) { best = blocks * w; nw = w; per = blocks; lds = b; }
+    }
+    const int64_t tile = (int64_t)nw * gv;
+    const int64_t rows = R.count ? C.g.n : R.nrows;
+    const dim3 grid((unsigned)std::min<int64_t>((rows + tile - 1) / tile, (int64_t)ncu * per)), block(nw * WAVE);
+    const auto kern = hi == 2 ? k_dcombine<1, 2> : hi == 1 ? k_dcombine<1, 1> : gv == 1 ? k_dcombine<1, 0>
+                    : gv == 2 ? k_dcombine<2, 0> : gv == 4 ? k_dcombine<4, 0> : k_dcombine<8, 0>;
+    hipLaunchKernelGGL(kern, grid, block, lds, st, C, R);
 }
 
 // The device summary: the totals, then a block of flags, counts and statistics for
@@ -2938,20 +3339,6 @@ void release_events()
     g_ev.clear();
 }
 
-// a device's compute units, asked for once
-static int compute_units()
-{
-    static std::mutex mu;
-    static std::map<int, int> known;
-    int dev = 0, n = 0;
-    (void)hipGetDevice(&dev);
-    std::lock_guard<std::mutex> lk(mu);
-    auto it = known.find(dev);
-    if (it != known.end()) return it->second;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
-    known[dev] = n;
-    return n;
-}
 
 // what a finished level's block says
 static scc_status level_result(scc_table *T, int h, const LevelBlock &b)
@@ -3415,6 +3802,7 @@ static scc_status build_levels(scc_table *T, bool validate)
             C.Nout = Lv.N;
         }
         const size_t lds = (size_t)(HL.xoff[h] + HL.soff[h]) * 8;
+        bool bits = (h == 2 || h == 3) && !C.zero_only && !C.bal;   // the bitmaps are left to k_pack
         if (n) {
             // level k under zero-rooting: only the colour-0 vertices have records
             const bool zl = C.zero_only != 0;
@@ -3423,8 +3811,13 @@ static scc_status build_levels(scc_table *T, bool validate)
                 HIP_TRY(hipMemsetAsync(Nsc, 0, (size_t)n * 16, st));
             }
             const int phi = C.bal ? h - 2 : h - 1;
-            bool pos = true;   // every own level read has dense records
+            // every own level read has dense records, and the outputs are stored by
+            // position or are few (level k's shapes: at most 115) and compacted in LDS
+            bool pos = dense || HL.W[h] <= 128;
             for (int q = 2; q <= phi; q++) pos = pos && T->lev[q].P > 0;
+            const bool wide = hi64(max_u) != 0;
+            DCombine R{zl ? zrows : nullptr, zl ? nzero : (int)n, nullptr, 0, wide || bitlen128(max_u) > T->max_bits, 0, 0,
+                       wide_list, err + 1};
             const bool classified = h >= 4 && (T->width_test == SCC_WIDTH_PER_LANE ||
                                                (T->width_test == SCC_WIDTH_AUTO && C.late_dma));
             // at most 64 outputs per vertex: four vertices per wave
@@ -3442,15 +3835,21 @@ static scc_status build_levels(scc_table *T, bool validate)
                 HIP_TRY(hipStreamSynchronize(st));
                 CombineArgs Cn = C;
                 Cn.late_dma = 0;
-                launch_combine(Cn, phi, pos, n, narrow, nn, lds, st, wide_list, err + 1);
+                R.rows = narrow;
+                R.nrows = nn;
+                if (pos) launch_dcombine(Cn, HL, R, 0, 0, st);
+                else launch_combine(Cn, phi, n, narrow, nn, lds, st, wide_list, err + 1);
+            } else if (pos && !(h == 2 && !zl && !C.bal)) {
+                if (grouped) T->grouped_combine |= 1 << h;
+                bits = false;
+                launch_dcombine(C, HL, R, 0, 0, st);
             } else if (grouped) {
                 T->grouped_combine |= 1 << h;
                 const int64_t nr = zl ? nzero : n;
                 const size_t lds_g = (size_t)(WAVE / CGL) * (HL.xoff[h] + HL.soff[h]) * 8;
                 if (nr) {
                     const dim3 grid((unsigned)((nr + WAVE / CGL - 1) / (WAVE / CGL)));
-                    const auto kg = phi <= 3 ? (pos ? k_combine_group<3, true> : k_combine_group<3, false>)
-                                             : (pos ? k_combine_group<5, true> : k_combine_group<5, false>);
+                    const auto kg = phi <= 3 ? k_combine_group<3> : k_combine_group<5>;
                     hipLaunchKernelGGL(kg, grid, dim3(WAVE), lds_g, st, C, zl ? zrows : nullptr, nr, narrow, err + 1);
                 }
                 // the vertices whose bound reaches 2^64, one per wave
@@ -3458,15 +3857,31 @@ static scc_status build_levels(scc_table *T, bool validate)
                     int nf = 0;
                     HIP_TRY(hipMemcpyAsync(&nf, err + 6, 4, hipMemcpyDeviceToHost, st));
                     HIP_TRY(hipStreamSynchronize(st));
-                    launch_combine(C, phi, pos, n, narrow, nf, lds, st, wide_list, err + 1);
+                    launch_combine(C, phi, n, narrow, nf, lds, st, wide_list, err + 1);
                 }
             } else if (h == 2 && !zl && !C.bal)
                 hipLaunchKernelGGL(k_combine_level2, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C);
             else if (h == 3 && !zl && !C.bal)
                 hipLaunchKernelGGL(k_combine_level3, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, C, wide_list,
                                    err + 1);
-            else launch_combine(C, phi, pos, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
-            if (hi64(max_u)) {
+            else launch_combine(C, phi, n, zl ? zrows : nullptr, nzero, lds, st, wide_list, err + 1);
+            if (wide && pos) {
+                // the vertices with 128-bit inputs
+                R.rows = wide_list;
+                R.count = err + 1;
+                launch_dcombine(C, HL, R, 1, HL.soff[phi + 1], st);
+                R.count = err + 3;
+                R.back = 1;
+                launch_dcombine(C, HL, R, 2, HL.soff[phi + 1], st);
+                if (classified) {
+                    // high words in the top-level sums only (listed at the back of narrow)
+                    CombineArgs Ct = C;
+                    Ct.hi_cap = HL.WS[phi];
+                    R.rows = narrow;
+                    R.count = err + 7;
+                    launch_dcombine(Ct, HL, R, 1, HL.WS[phi], st);
+                }
+            } else if (wide) {
             // the 128-bit vertices (at k = 8 most of level 7, nearly all with high
             // words in neighbour sums only) stride over as many waves as each
             // kernel's LDS staging lets the chip hold
@@ -3474,9 +3889,7 @@ static scc_status build_levels(scc_table *T, bool validate)
             const int ncu = compute_units();
             const size_t ltw = (size_t)level_term_words(k, h) * 8;   // the level's term descriptors
             const size_t lds_s = (size_t)(HL.xoff[h] + 2 * HL.soff[h]) * 8 + ltw, lds_o = 2 * lds + ltw;
-            const auto kw_s = pos ? k_combine_wide<false, false, true> : k_combine_wide<false, false, false>;
-            const auto kw_o = pos ? k_combine_wide<true, true, true> : k_combine_wide<true, true, false>;
-            const auto kw_t = pos ? k_combine_wide<false, true, true> : k_combine_wide<false, true, false>;
+            const auto kw_s = k_combine_wide<false, false>, kw_o = k_combine_wide<true, true>, kw_t = k_combine_wide<false, true>;
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_s, (const void *)kw_s, WAVE, lds_s));
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_own, (const void *)kw_o, WAVE, lds_o));
             const int64_t gs = std::min<int64_t>(n, std::max<int64_t>(1024, (int64_t)ncu * per_s));
@@ -3554,7 +3967,6 @@ static scc_status build_levels(scc_table *T, bool validate)
             // one group of four vertices per wave: the waves' dependent loads overlap.
             // The bitmaps come from the combine, except after the dedicated level-2
             // and level-3 kernels, which do not write them
-            const bool bits = (h == 2 || h == 3) && !C.zero_only && !C.bal;
             if (bits) hipLaunchKernelGGL(k_pack<true>, dim3((unsigned)((n + 3) / 4)), dim3(WAVE), 0, st, P);
             else hipLaunchKernelGGL(k_pack<false>, dim3((unsigned)((n + 3) / 4)), dim3(WAVE), 0, st, P);
         }

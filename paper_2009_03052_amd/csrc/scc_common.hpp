@@ -84,6 +84,9 @@ struct DevLut {
     // at position i, and terms (setpos of D') r_h' | (colex rank of D'') << 9
     uint64_t outd[1400];
     uint16_t xterm[2200];
+    // [out_off[h] + i] -> position, the outputs of level h by descending number of
+    // splits: lanes that evaluate consecutive ones run equally long
+    uint16_t xsort[1400];
     // the sums S_h seen from a colour-c vertex: byte c_u of gsel[h][c][q] is
     // setpos[h] of the q-th h-set C (colex, without c) in the records of colour-c_u
     // vertices, 0xff where c_u is not in C

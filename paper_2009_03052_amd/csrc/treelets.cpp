@@ -356,6 +356,12 @@ static void build_dense(int k, DevLut *L)
             L->outd[at + pos] = (L->out[at + o] & ~(uint64_t)0xffffu) | (uint64_t)(L->xoff[hp] + L->dec_a[h][t]);
         }
     }
+    for (int h = 2; h <= k; h++) {
+        const uint64_t *d = L->outd + L->out_off[h];
+        uint16_t *by = L->xsort + L->out_off[h];
+        for (int i = 0; i < L->W[h]; i++) by[i] = (uint16_t)i;
+        std::stable_sort(by, by + L->W[h], [d](uint16_t a, uint16_t b) { return (d[a] >> 48 & 0xffu) > (d[b] >> 48 & 0xffu); });
+    }
     for (int h = 2; h < k; h++)
         for (int c = 0; c < k; c++)
             for (int q = 0; q < L->bk1[h]; q++) {

@@ -383,6 +383,17 @@ def test_dense_levels_beyond_64_bits(k, leaves, rooting):
         print(f"mode {mode} hub>{hub_degree} width {width} vlc {vlc} equal", flush=True)
 
 
+@pytest.mark.parametrize("k,n,m,rooting", [(7, 33003, 130000, O.ROOT_BALANCED), (5, 16389, 100000, O.ROOT_ALL),
+                                           (8, 8195, 40000, O.ROOT_ZERO), (4, 5, 6, O.ROOT_ALL)])
+def test_combine_vertices_per_wave(k, n, m, rooting):
+    # 8, 4, 2 and 1 vertices a wave with a last wave that is not full, dense
+    # levels and the compacted level k
+    g = gg.erdos_renyi(n, m, seed=600 + k)
+    colors = gg.colors(g.n, k, seed=k)
+    gt, ot = build_pair(g, colors, k, rooting=rooting)
+    assert_tables_equal(gt, ot, k, f"k = {k}, n = {n}")
+
+
 @pytest.mark.parametrize("n,m", [(12, 30), (300, 2000), (4000, 3000)])
 def test_asymmetric_arcs_are_found(n, m):
     # the symmetry check searches the arcs towards the vertex that comes first by
