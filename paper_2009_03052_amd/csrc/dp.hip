@@ -900,14 +900,16 @@ __global__ void __launch_bounds__(WAVE) k_gather_hub(GatherArgs A, int chunk)
 // nothing is added through LDS. The entries whose sets hold c_v, of which a
 // record has h - 1 in every k - 1, are never read; the record's order keeps the
 // others in few runs of whole lines.
-// GW lanes hold a row's entries, R each (GW R >= WS); a wave has 64 / GW groups,
+// GW lanes hold a row's entries, R pairs each; a wave has 64 / GW groups,
 // which take a row each (short rows) or every (64/GW)-th neighbour of one row.
 // W128: some neighbour or row may need 128 bits.
-// The gather is bound by HBM reads. At k = 8 (Chung-Lu, 4*10^6 vertices, 6*10^7
-// edges) the sparse records of levels 2..7 took 1.26 TB of reads and 250 ms a build
-// (6.2 TB/s of requests), the dense ones take 110 ms; with what the combine and the
-// pack no longer do the build went from 418 to 237 ms (k = 6, 10^6 vertices, 10^7
-// edges: 10.4 to 8.1 ms; k = 7, 5*10^5 and 5*10^6: 13.3 to 9.3 ms).
+// The gather is bound by HBM reads: two or three waits for it a row, one after
+// another. At k = 8 (Chung-Lu, 4*10^6 vertices, 6*10^7 arcs) the sparse records of
+// levels 2..7 took 1.26 TB of reads and 250 ms a build, the dense ones take 95 ms; with
+// what the combine and the pack no longer do the build went from 418 to 237 ms (k = 6,
+// 10^6 vertices, 10^7 edges: 10.4 to 8.1 ms; k = 7, 5*10^5 and 5*10^6: 13.3 to 9.3 ms).
+// Whole lines copied to LDS, more neighbours in flight a wave, resident waves with
+// tables, sums stored in whole lines: none made levels 4 to 6 of k = 8 faster.
 // ---------------------------------------------------------------------------
 struct DGatherArgs {
     GraphView g;
@@ -928,28 +930,38 @@ struct DGatherArgs {
     int *err;
 };
 
-// This lane's entries of the row: i = gl + GW r is entry (set q, rank t); off the
-// row every byte of its selector is 0xff
+// This lane's entries of the row: pair i = gl + GW r holds entries (set q, ranks t and
+// t + 1), the second of a set's last pair only where r_h is even (two[r]); off the row
+// every byte of its selector is 0xff. A pair is one load of 16 bytes: the address unit
+// takes a cycle per lane whatever its width, and was busy 80 % of the time with a word
+// per lane (level 3 of k = 8, 4*10^6 vertices: 7.9 to 6.2 ms; levels 4 to 6 wait for HBM
+// and kept their time; k = 7's levels fit in half a wave, two rows at a time: level 4 of
+// 5*10^5 vertices 0.64 to 0.42 ms)
 template <int GW, int R> struct DLane {
     int q[R], t[R];
-    bool on[R];
+    bool on[R], two[R];
     __device__ DLane(const DGatherArgs &A)
     {
-        const int gl = lane_id() & (GW - 1);
+        const int gl = lane_id() & (GW - 1), pr = (A.rr + 1) / 2;
 #pragma unroll
         for (int r = 0; r < R; r++) {
             const int i = gl + GW * r;
-            on[r] = i < A.WS;
-            q[r] = on[r] ? i / A.rr : 0;
-            t[r] = i - q[r] * A.rr;
+            q[r] = i / pr;
+            on[r] = q[r] < A.nq;
+            q[r] = on[r] ? q[r] : 0;
+            t[r] = 2 * (i % pr);
+            two[r] = t[r] + 1 < A.rr;
         }
     }
 };
 
 template <int R> struct DAcc {
-    uint64_t lo[R], hi[R];
+    uint64_t lo[R][2], hi[R][2];
     u128 m;
 };
+// two words of a record at any of its words (after a set's last rank of an odd r_h the
+// second is not used; a record of such a level ends in padding)
+typedef uint64_t words2 __attribute__((ext_vector_type(2), aligned(8)));
 
 // Adds the group's edges start, start + stride, ... below end (the same trip in
 // every lane of the wave). U neighbours' words are requested before any is added.
@@ -957,7 +969,7 @@ template <int GW, int R, bool W128>
 __device__ inline void dgather_edges(const DGatherArgs &A, const DLane<GW, R> &D, int cv, int64_t start, int64_t end,
                                      int64_t stride, bool bound, DAcc<R> &acc)
 {
-    constexpr int U = R * (W128 ? 2 : 1) >= 4 ? 2 : 4;
+    constexpr int U = R * (W128 ? 2 : 1) >= 2 ? 2 : 4;
     const int lane = lane_id(), gl = lane & (GW - 1), gb = lane & ~(GW - 1);
     uint64_t tab[R];
 #pragma unroll
@@ -984,7 +996,7 @@ __device__ inline void dgather_edges(const DGatherArgs &A, const DLane<GW, R> &D
         const int mx = 64 - __clzll((long long)f);
         const int cnt = GW < 64 ? __popcll(am >> gb & ((1ull << (GW & 63)) - 1ull)) : mx;
         for (int n = 0; n < mx; n += U) {
-            uint64_t xl[U][R], xh[U][R];
+            words2 xl[U][R], xh[U][R];
 #pragma unroll
             for (int j = 0; j < U; j++) {
                 const int src = n + j;
@@ -1008,18 +1020,20 @@ __device__ inline void dgather_edges(const DGatherArgs &A, const DLane<GW, R> &D
                     xl[j][r] = 0;
                     xh[j][r] = 0;
                     if (in) {
-                        xl[j][r] = row[off];
-                        if (W128 && nh >= 0) xh[j][r] = A.hi[(size_t)nh * A.P + off];
+                        xl[j][r] = *(const words2 *)(row + off);
+                        if (W128 && nh >= 0) xh[j][r] = *(const words2 *)(A.hi + (size_t)nh * A.P + off);
                     }
                 }
             }
 #pragma unroll
             for (int j = 0; j < U; j++)
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    acc.lo[r] += xl[j][r];
-                    if (W128) acc.hi[r] += xh[j][r] + (acc.lo[r] < xl[j][r] ? 1u : 0u);
-                }
+                for (int r = 0; r < R; r++)
+#pragma unroll
+                    for (int i = 0; i < 2; i++) {
+                        acc.lo[r][i] += xl[j][r][i];
+                        if (W128) acc.hi[r][i] += xh[j][r][i] + (acc.lo[r][i] < xl[j][r][i] ? 1u : 0u);
+                    }
         }
     }
 }
@@ -1031,11 +1045,13 @@ __device__ inline void dgather_join(DAcc<R> &acc)
 #pragma unroll
     for (int s = GW; s < WAVE; s <<= 1)
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            const uint64_t x = shfl64(acc.lo[r], lane_id() ^ s);
-            acc.lo[r] += x;
-            if (W128) acc.hi[r] += shfl64(acc.hi[r], lane_id() ^ s) + (acc.lo[r] < x ? 1u : 0u);
-        }
+        for (int r = 0; r < R; r++)
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                const uint64_t x = shfl64(acc.lo[r][i], lane_id() ^ s);
+                acc.lo[r][i] += x;
+                if (W128) acc.hi[r][i] += shfl64(acc.hi[r][i], lane_id() ^ s) + (acc.lo[r][i] < x ? 1u : 0u);
+            }
 }
 
 template <int GW, int R, bool W128>
@@ -1044,11 +1060,13 @@ __device__ inline void dgather_store(const DGatherArgs &A, const DLane<GW, R> &D
     const int hr = W128 && A.hrow && mine ? A.hrow[v] : -1;
 #pragma unroll
     for (int r = 0; r < R; r++)
-        if (mine && D.on[r]) {
-            const int s = D.t[r] * A.nq + D.q[r];   // sums stay in (rank, colex) order
-            A.Slo[(size_t)v * A.WS + s] = acc.lo[r];
-            if (W128 && hr >= 0) A.Shi[(size_t)hr * A.WS + s] = acc.hi[r];
-        }
+#pragma unroll
+        for (int i = 0; i < 2; i++)
+            if (mine && D.on[r] && (i == 0 || D.two[r])) {
+                const int s = (D.t[r] + i) * A.nq + D.q[r];   // sums stay in (rank, colex) order
+                A.Slo[(size_t)v * A.WS + s] = acc.lo[r][i];
+                if (W128 && hr >= 0) A.Shi[(size_t)hr * A.WS + s] = acc.hi[r][i];
+            }
 }
 
 // one row per wave: every row (rows null) or the listed ones, hubs left out
@@ -1120,22 +1138,25 @@ __global__ void __launch_bounds__(WAVE) k_dgather_hub(DGatherArgs A, int chunk)
         uint64_t *plo = A.hub_pre ? A.hub_pre + A.hub_poff[(size_t)A.chunk_q[blockIdx.x] * (SCC_KMAX + 1) + A.hs] : nullptr;
         uint64_t *phi = plo + (size_t)A.WS * nb;
 #pragma unroll
-        for (int r = 0; r < R; r++) {
-            if (!D.on[r]) continue;
-            const int s = D.t[r] * A.nq + D.q[r];
-            if (A.hub_pre) {
-                plo[(size_t)s * nb + blk] = acc.lo[r];
-                if (W128) phi[(size_t)s * nb + blk] = acc.hi[r];
-            } else {
-                unsigned long long *Slo = (unsigned long long *)(A.Slo + (size_t)v * A.WS + s);
-                if (W128) {
-                    unsigned long long *Shi = (unsigned long long *)(A.Shi + (size_t)A.hrow[v] * A.WS + s);
-                    over |= atomic_add128(Slo, Shi, acc.lo[r], acc.hi[r]);
-                } else if (acc.lo[r]) {
-                    atomicAdd(Slo, (unsigned long long)acc.lo[r]);
+        for (int r = 0; r < R; r++)
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                if (!D.on[r] || (i && !D.two[r])) continue;
+                const int s = (D.t[r] + i) * A.nq + D.q[r];
+                const uint64_t lo = acc.lo[r][i], hi = acc.hi[r][i];
+                if (A.hub_pre) {
+                    plo[(size_t)s * nb + blk] = lo;
+                    if (W128) phi[(size_t)s * nb + blk] = hi;
+                } else {
+                    unsigned long long *Slo = (unsigned long long *)(A.Slo + (size_t)v * A.WS + s);
+                    if (W128) {
+                        unsigned long long *Shi = (unsigned long long *)(A.Shi + (size_t)A.hrow[v] * A.WS + s);
+                        over |= atomic_add128(Slo, Shi, lo, hi);
+                    } else if (lo) {
+                        atomicAdd(Slo, (unsigned long long)lo);
+                    }
                 }
             }
-        }
     }
     if (over) atomicOr(A.err, 2);   // the bound left 128 bits: the build reports overflow
 }
@@ -1183,8 +1204,8 @@ __global__ void __launch_bounds__(256) k_row_bounds(GraphView g, int hub_degree,
     if (in) hrow[v] = wide ? base + at + __popcll(bw & lanemask_lt()) : -1;
 }
 
-// The gather kernels for a row of WS entries: the narrowest group of lanes that
-// holds it, two or three entries a lane above 64
+// The gather kernels for a row of so many pairs of entries: the narrowest group of
+// lanes that holds it, two pairs a lane above 64
 struct DGatherKernels {
     void (*row)(DGatherArgs, const int32_t *);
     void (*group)(DGatherArgs, const int32_t *, int64_t);   // null: one row per wave only
@@ -1196,10 +1217,10 @@ template <int GW, int R, bool W128> DGatherKernels dgather_of()
     if constexpr (GW < 64) return {k_dgather_row<GW, R, W128>, k_dgather_group<GW, R, W128>, k_dgather_hub<GW, R, W128>, GW};
     else return {k_dgather_row<GW, R, W128>, nullptr, k_dgather_hub<GW, R, W128>, GW};
 }
-template <bool W128> DGatherKernels dgather_kernels(int WS)
+template <bool W128> DGatherKernels dgather_kernels(int pairs)
 {
-    return WS <= 8 ? dgather_of<8, 1, W128>() : WS <= 16 ? dgather_of<16, 1, W128>() : WS <= 32 ? dgather_of<32, 1, W128>()
-         : WS <= 64 ? dgather_of<64, 1, W128>() : WS <= 128 ? dgather_of<64, 2, W128>() : dgather_of<64, 3, W128>();
+    return pairs <= 8 ? dgather_of<8, 1, W128>() : pairs <= 16 ? dgather_of<16, 1, W128>()
+         : pairs <= 32 ? dgather_of<32, 1, W128>() : pairs <= 64 ? dgather_of<64, 1, W128>() : dgather_of<64, 2, W128>();
 }
 
 // algorithmic bytes of one gather launch (for reports): 4 d_v + neighbours'
@@ -3629,7 +3650,8 @@ static scc_status build_levels(scc_table *T, bool validate)
                 if (!Sx.hi) return set_error(SCC_ENOMEM, "neighbour sums level %d, high words", hs);
                 G.bounded = 1; G.Shi = Sx.hi; G.hrow = Sx.hrow;
             }
-            const DGatherKernels K = w128 ? dgather_kernels<true>(G.WS) : dgather_kernels<false>(G.WS);
+            const int pairs = (G.rr + 1) / 2 * G.nq;
+            const DGatherKernels K = w128 ? dgather_kernels<true>(pairs) : dgather_kernels<false>(pairs);
             const int32_t *rows = G.rows_zero ? zrows : nullptr;
             const int64_t nrows = G.rows_zero ? nzero : n;
             if (nrows && K.group && T->gather_mode != SCC_GATHER_ROW) {
