@@ -613,7 +613,10 @@ typedef struct {
     const scc_allocator *alloc;/* NULL: hipMalloc / hipFree */
     int no_validate;           /* as in scc_build_opts */
     int64_t chunk_terms;       /* terms (neighbour entries or Eq. (1) products) formed and
-                                  sorted at a time; 0 = 2^26. Results do not depend on it. */
+                                  sorted at a time; 0 = 2^26, and levels of few enough
+                                  outputs a vertex (all of k <= 10) aggregate their terms in
+                                  LDS instead, 2^26 possible outputs at a time. Results do
+                                  not depend on it. */
     int max_bits;              /* count width: 128 or 256; 0 (default) = 128, and the
                                   whole build again at 256 when a count needs more bits */
 } scc16_build_opts;
@@ -632,7 +635,7 @@ typedef struct {
     uint64_t t[4];             /* colourful k-treelet copies, four words, least significant first */
     int count_bits;            /* width of the stored counts: 128 or 256 */
     double level_ms[17];       /* device time of level h (products and its sums) */
-    double sort_ms[17];        /* of which radix sorting */
+    double sort_ms[17];        /* of which radix sorting (0 where terms are aggregated) */
     double sort_bytes[17];     /* algorithmic bytes of those sorts: 32 per element and pass
                                   (8 read by the histogram; 12 read and 12 written by the
                                   scatter) */

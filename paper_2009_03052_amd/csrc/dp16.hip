@@ -20,7 +20,8 @@
 // child word of T'; beta_T is then the number of T's root child words equal to
 // its first one.
 //
-// Work is formed as terms and aggregated by sorting. Each level (X_h, and
+// Work is formed as terms and aggregated: in a workgroup's LDS where a vertex's possible
+// outputs fit there (k16_agg: every level of k <= 10), else by sorting. Each level (X_h, and
 // the sums S_h built from it) first counts its terms per vertex -- neighbour
 // entries for S_h, non-zero products of Eq. (1) for X_h -- then, a chunk of
 // vertices at a time, writes each term as one 64-bit word (vertex in the
@@ -31,6 +32,7 @@
 // kernel that carries counts is instantiated for both widths); a product or sum
 // that needs more bits than the build's width ends it with SCC_EOVERFLOW.
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "device.hpp"
@@ -62,7 +64,7 @@ struct Lev16View {
 // Bitstrings and counts
 // ---------------------------------------------------------------------------
 // length of the first root child word of the string s of len bits (0 if len = 0)
-__device__ inline int first_word_len(uint32_t s, int len)
+__host__ __device__ inline int first_word_len(uint32_t s, int len)
 {
     int depth = 0;
     for (int i = 0; i < len; i++) {
@@ -75,10 +77,10 @@ __device__ inline int first_word_len(uint32_t s, int len)
 // The word w (lw bits) is not smaller than the word c (lc bits, lc = 0: no
 // word). Both are primitive Dyck words, and a primitive Dyck word is never a
 // proper prefix of another, so their common-length prefixes decide.
-__device__ inline bool word_not_smaller(uint32_t w, int lw, uint32_t c, int lc)
+__host__ __device__ inline bool word_not_smaller(uint32_t w, int lw, uint32_t c, int lc)
 {
     if (lc == 0) return true;
-    const int m = min(lw, lc);
+    const int m = lw < lc ? lw : lc;
     return (w >> (lw - m)) >= (c >> (lc - m));
 }
 
@@ -586,6 +588,350 @@ __global__ __launch_bounds__(BLOCK) void k16_comb(CombArgs<CT> A)
 }
 
 // ---------------------------------------------------------------------------
+// Terms aggregated in LDS
+// ---------------------------------------------------------------------------
+// Forming, sorting and summing the terms took 370 of the 412 ms of a k = 10 build of
+// 65 536 vertices (Chung-Lu, 131 072 edges): every term is written and read some ten
+// times. A vertex has far fewer outputs than terms, at most r_h binom(k-1, h-1) of X_h
+// and r_j binom(k-1, j) of S_j (4140 at k = 10). Where a 128-bit count for each of these
+// fits the LDS, a workgroup adds a vertex's terms to them as they are formed, by the rank
+// of the shape's string and of the colour set, and writes the non-zero ones in order: the
+// ranks run as the sort keys do. Four waves a workgroup where a CU holds four of these,
+// else sixteen, one to a CU.
+struct AggArgs {
+    int64_t v0, v1;
+    int KB, k, h, hlen;         // (S_j: h = j)
+    int zero_rooting, nout, nsets, nstr, turn;
+    const uint8_t *colors;
+    const int64_t *toff;        // bounds on the vertices' outputs, scanned: v's are written at toff[v] - toff[v0]
+    const uint16_t *rank;       // [2^hlen] rank of each canonical string
+    const uint32_t *str;        // [nstr] the strings, ascending
+    const uint16_t *crank;      // [k][2^k] rank of each colour set of a colour-c vertex's outputs
+    const uint16_t *cset;       // [k][nsets] the sets, ascending
+    uint64_t *okey;
+    u128 *ocnt;
+    int64_t *vcount;            // [n] entries per vertex
+    unsigned long long *cursor; // [0] next vertex of this launch, [1] terms
+    int *err;
+    NbrArgs<u128> N;            // S_j
+    CombArgs<u128> C;           // X_h
+};
+constexpr int AGG_MAX = 4200;                    // outputs of a vertex, at most
+constexpr int AGG_FEW = 1280;                    // up to here four waves a workgroup
+constexpr int AGG_K = 11;
+struct AggWave {                // a wave's part of the LDS
+    uint32_t sp[WAVE], c1[WAVE], lc[WAVE], cp[WAVE], st[WAVE], ex[WAVE], xq[WAVE], pad[WAVE];
+    uint64_t pos[WAVE];
+    u128 cx[WAVE];
+};
+// totals, directory and subsets, binomials, control words, the waves
+constexpr int AGG_DIR = 256;    // binom(AGG_K - 1, (AGG_K - 1) / 2) = 252
+inline size_t agg_lds(int nw, int nout)
+{
+    return (size_t)nout * 16 + AGG_DIR * 10 + K16 * (K16 + 1) * 2 + 96 + nw * sizeof(AggWave);
+}
+
+// ranks of the strings; ranks and lists of the colour sets of every colour: sets of h
+// colours with c (X) or without it
+template <bool X>
+__global__ void k16_agg_ranks(AggArgs A, uint16_t *rank, uint16_t *crank, uint16_t *cset)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < A.nstr) rank[A.str[i]] = (uint16_t)i;
+    if (i >= A.k << A.k) return;
+    const int c = i >> A.k;
+    const uint32_t C = (uint32_t)i & ((1u << A.k) - 1u);
+    if (__popc(C) != A.h || (C >> c & 1u) != (X ? 1u : 0u)) return;
+    int r = 0, t = 1;
+    for (uint32_t D = compress_out(C & ~(1u << c), c); D; D &= D - 1u, t++) r += binom_small(__builtin_ctz(D), t);
+    crank[i] = (uint16_t)r;
+    cset[c * A.nsets + r] = (uint16_t)C;
+}
+
+// one thread per vertex: a bound on its outputs (0: none), clamped to most
+template <bool X>
+__global__ void k16_agg_bound(AggArgs A, int64_t n, int64_t most, int64_t *bound)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v >= n) return;
+    int64_t b = 0;
+    if (X) {
+        if (!(A.zero_rooting && A.h == A.k && A.colors[v] != 0))
+            for (int hp = 1; hp < A.h; hp++) {
+                const int64_t *xo = A.C.X[hp].off + v, *so = A.C.S[A.h - hp].off + v;
+                b += (xo[1] - xo[0]) * (so[1] - so[0]);
+            }
+    } else {
+        for (int64_t e = A.N.row_ptr[v]; e < A.N.row_ptr[v + 1] && b < most; e++) {
+            const int64_t *xo = A.N.X.off + A.N.col_idx[e];
+            b += xo[1] - xo[0];
+        }
+    }
+    bound[v] = b < most ? b : most;
+}
+
+template <bool X, int NW>
+__global__ void __launch_bounds__(NW * WAVE) k16_agg(AggArgs A)
+{
+    extern __shared__ uint64_t smem[];
+    unsigned long long *hlo = (unsigned long long *)smem, *hhi = hlo + A.nout;
+    uint32_t *dir_st = (uint32_t *)(hhi + A.nout), *dir_en = dir_st + AGG_DIR;
+    uint16_t *sub = (uint16_t *)(dir_en + AGG_DIR), *binom_t = sub + AGG_DIR;
+    int *ctl = (int *)(binom_t + K16 * (K16 + 1));          // [0] vertex; [1 + w] outputs of wave w's turn
+    AggWave *waves = (AggWave *)(ctl + 24);
+    constexpr int NT = NW * WAVE;
+    const int w = threadIdx.x / WAVE, lane = lane_id();
+    AggWave &W = waves[w];
+    if (X)
+        for (int q = threadIdx.x; q < K16 * (K16 + 1); q += NT)
+            binom_t[q] = (uint16_t)binom_small(q / (K16 + 1), q % (K16 + 1));
+    auto rank_of = [&](uint32_t Dc) {
+        uint32_t r = 0;
+        for (int t = 1; Dc; Dc &= Dc - 1u, t++) r += binom_t[__builtin_ctz(Dc) * (K16 + 1) + t];
+        return r;
+    };
+    const uint32_t full = (1u << A.k) - 1u;
+    // (thread 0) the next vertex of the turn's, and the turn after it, asked for ahead: a
+    // turn is several vertices, as the shared count takes about 20 ns each time
+    const unsigned long long nv = (unsigned long long)(A.v1 - A.v0);
+    unsigned long long cur = 0, end = 0, next = 0;
+    if (threadIdx.x == 0) next = atomicAdd(&A.cursor[0], (unsigned long long)A.turn);
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (cur == end) {
+                cur = next;
+                end = next + (unsigned long long)A.turn;
+                next = atomicAdd(&A.cursor[0], (unsigned long long)A.turn);
+            }
+            ctl[0] = cur < nv ? (int)cur : -1;
+            cur++;
+        }
+        for (int q = threadIdx.x; q < 2 * A.nout; q += NT) hlo[q] = 0;
+        __syncthreads();
+        if (ctl[0] < 0) break;
+        const int64_t v = A.v0 + ctl[0];
+        const int64_t at = A.toff[v] - A.toff[A.v0];
+        if (A.toff[v + 1] == A.toff[v]) continue;   // (its entry count is 0 already)
+        const int cv = A.colors[v];
+        const uint16_t *crank = A.crank + ((size_t)cv << A.k);
+        bool ovf = false;
+        uint64_t nterms = 0;
+        // count c of shape string s with colours C
+        auto add = [&](uint32_t s, uint32_t C, u128 c) {
+            const uint32_t t = A.rank[s], r = crank[C];
+            const uint32_t slot = X ? t * (uint32_t)A.nsets + r : r * (uint32_t)A.nstr + t;
+            const unsigned long long l = lo64(c), old = atomicAdd(&hlo[slot], l);
+            const unsigned long long h = hi64(c), up = h + (old + l < old ? 1ull : 0ull);
+            if (up < h) ovf = true;
+            if (up) {
+                const unsigned long long oh = atomicAdd(&hhi[slot], up);
+                if (oh + up < oh) ovf = true;
+            }
+            nterms++;
+        };
+        if (!X) {
+            // the neighbours 64 at a time, their records one flat range shared by the waves
+            const uint32_t cbit = 1u << cv;
+            uint32_t *seg_a = W.sp, *seg_h = W.c1, *seg_p = W.lc;   // record starts (two words), flat starts
+            for (int64_t r = A.N.row_ptr[v]; r < A.N.row_ptr[v + 1]; r += WAVE) {
+                const int nn = (int)min<int64_t>(WAVE, A.N.row_ptr[v + 1] - r);
+                int64_t a = 0;
+                uint32_t len = 0;
+                if (lane < nn) {
+                    const int32_t u = A.N.col_idx[r + lane];
+                    a = A.N.X.off[u];
+                    len = (uint32_t)(A.N.X.off[u + 1] - a);
+                }
+                const uint32_t incl = wave_incl_scan32(len);
+                const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+                seg_a[lane] = (uint32_t)a;
+                seg_h[lane] = (uint32_t)((uint64_t)a >> 32);
+                seg_p[lane] = incl - len;
+                __builtin_amdgcn_wave_barrier();
+                for (uint32_t f = (uint32_t)(w * WAVE + lane); f < total; f += NT) {
+                    int lo = 0, hi = nn - 1;
+                    while (lo < hi) {
+                        const int mid = (lo + hi + 1) >> 1;
+                        if (seg_p[mid] <= f) lo = mid; else hi = mid - 1;
+                    }
+                    const int64_t e = (int64_t)((uint64_t)seg_h[lo] << 32 | seg_a[lo]) + (f - seg_p[lo]);
+                    const uint64_t key = A.N.X.key[e];
+                    if (!((uint32_t)key & cbit)) add((uint32_t)(key >> 16), (uint32_t)key & 0xffffu, A.N.X.cnt[e]);
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            for (int hp = 1; hp < A.h; hp++) {
+                const int j = A.h - hp, lp = 2 * (hp - 1), sb = 2 * (j - 1), lw = 2 * j;
+                const Lev16View<u128> XV = A.C.X[hp], S = A.C.S[j];
+                const int64_t xa = XV.off[v], xb = XV.off[v + 1], sa = S.off[v], se = S.off[v + 1];
+                __syncthreads();   // (the directory of the split before is done with)
+                if (xa == xb || sa == se) continue;
+                const uint32_t smask = (1u << sb) - 1u;
+                const uint32_t nb = (uint32_t)(se - sa);
+                const int m = A.k - hp;
+                const int nsub = binom_small(m, j);
+                const int ndir = binom_small(A.k - 1, j);
+                const bool walk = (int64_t)nb <= (int64_t)nsub * 4;
+                if (!walk) {
+                    // where each colour set's sums start and end, by its rank among the sets
+                    // without c_v; and the j-subsets of m free colours
+                    for (int q = threadIdx.x; q < 1 << m; q += NT)
+                        if (__popc(q) == j) sub[rank_of((uint32_t)q)] = (uint16_t)q;
+                    for (int q = threadIdx.x; q < ndir; q += NT) dir_st[q] = dir_en[q] = 0;
+                    __syncthreads();
+                    for (uint32_t e = threadIdx.x; e < nb; e += NT) {
+                        const uint32_t D = (uint32_t)(S.key[sa + e] >> sb);
+                        const uint32_t before = e ? (uint32_t)(S.key[sa + e - 1] >> sb) : 0u;
+                        if (D != before) {
+                            dir_st[rank_of(compress_out(D, cv))] = e;
+                            if (e) dir_en[rank_of(compress_out(before, cv))] = e;
+                        }
+                        if (e == nb - 1) dir_en[rank_of(compress_out(D, cv))] = nb;
+                    }
+                    __syncthreads();
+                }
+                // a wave's tile of own entries: all waves get some
+                const int tx = (int)min<int64_t>(WAVE, (xb - xa + NW - 1) / NW);
+                for (int64_t x0 = xa + (int64_t)w * tx; x0 < xb; x0 += (int64_t)NW * tx) {
+                    const int nx = (int)min<int64_t>(tx, xb - x0);
+                    if (lane < nx) {
+                        const uint64_t kx = XV.key[x0 + lane];
+                        const uint32_t sp = (uint32_t)(kx >> 16);
+                        const int lc = first_word_len(sp, lp);
+                        W.sp[lane] = sp;
+                        W.c1[lane] = lc ? sp >> (lp - lc) : 0u;
+                        W.lc[lane] = (uint32_t)lc;
+                        W.cp[lane] = (uint32_t)kx & 0xffffu;
+                        W.cx[lane] = XV.cnt[x0 + lane];
+                        uint64_t pos = 0;   // its free colours (without c_v), four bits each
+                        int t = 0;
+                        for (uint32_t f = compress_out(full & ~((uint32_t)kx & 0xffffu), cv); f; f &= f - 1u, t++)
+                            pos |= (uint64_t)__builtin_ctz(f) << (4 * t);
+                        W.pos[lane] = pos;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    auto term = [&](int q, int64_t e, uint64_t ks, uint32_t CD) {
+                        const uint32_t wd = (1u << (lw - 1)) | (((uint32_t)ks & smask) << 1);
+                        if (!word_not_smaller(wd, lw, W.c1[q], (int)W.lc[q])) return;
+                        add((wd << lp) | W.sp[q], CD, Cnt<u128>::mul(W.cx[q], S.cnt[e], ovf));
+                    };
+                    if (walk) {
+                        // every pair of an own entry and a sum, 64 at a time
+                        const uint32_t pairs = (uint32_t)nx * nb;
+                        const float inv = 1.0f / (float)nb;
+                        for (uint32_t p0 = lane; p0 < pairs; p0 += WAVE) {
+                            uint32_t q = (uint32_t)((float)p0 * inv);
+                            if (q * nb > p0) q--;
+                            else if (p0 - q * nb >= nb) q++;
+                            const int64_t e = sa + (p0 - q * nb);
+                            const uint64_t ks = S.key[e];
+                            const uint32_t D = (uint32_t)(ks >> sb);
+                            if (!(D & W.cp[q])) term((int)q, e, ks, W.cp[q] | D);
+                        }
+                    } else {
+                        // every pair of an own entry and a j-subset of its free colours, 64 at
+                        // a time; their ranges of sums end to end, 64 sums at a time
+                        const uint32_t pairs = (uint32_t)nx * (uint32_t)nsub;
+                        const float inv = 1.0f / (float)nsub;
+                        for (uint32_t p0 = 0; p0 < pairs; p0 += WAVE) {
+                            const uint32_t p = p0 + lane;
+                            uint32_t cnt = 0, st = 0, q = 0;
+                            if (p < pairs) {
+                                q = (uint32_t)((float)p * inv);
+                                if (q * (uint32_t)nsub > p) q--;
+                                else if (p - q * (uint32_t)nsub >= (uint32_t)nsub) q++;
+                                const uint64_t pos = W.pos[q];
+                                uint32_t r = 0;
+                                int t = 1;
+                                for (uint32_t b = sub[p - q * (uint32_t)nsub]; b; b &= b - 1u, t++)
+                                    r += binom_t[(int)((pos >> (4 * __builtin_ctz(b))) & 15u) * (K16 + 1) + t];
+                                st = dir_st[r];
+                                cnt = dir_en[r] - st;
+                            }
+                            const uint32_t incl = wave_incl_scan32(cnt);
+                            const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, WAVE - 1);
+                            if (!total) continue;
+                            W.st[lane] = st;
+                            W.ex[lane] = incl - cnt;
+                            W.xq[lane] = q;
+                            __builtin_amdgcn_wave_barrier();
+                            for (uint32_t f = lane; f < total; f += WAVE) {
+                                int lo = 0, hi = WAVE - 1;   // the last lane whose range starts at or before f
+                                while (lo < hi) {
+                                    const int mid = (lo + hi + 1) >> 1;
+                                    if (W.ex[mid] <= f) lo = mid; else hi = mid - 1;
+                                }
+                                const int64_t e = sa + W.st[lo] + (f - W.ex[lo]);
+                                const uint64_t ks = S.key[e];
+                                const int own = (int)W.xq[lo];
+                                term(own, e, ks, W.cp[own] | (uint32_t)(ks >> sb));
+                            }
+                            __builtin_amdgcn_wave_barrier();
+                        }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+        }
+        __syncthreads();
+        if (ovf) atomicOr(A.err, E16_OVERFLOW);
+        nterms = wave_sum64(nterms);
+        if (lane == 0 && nterms) atomicAdd(&A.cursor[1], (unsigned long long)nterms);
+        // the non-zero outputs in order
+        int done = 0;
+        for (int q0 = 0; q0 < A.nout; q0 += NT) {
+            const int q = q0 + (int)threadIdx.x;
+            u128 c = q < A.nout ? mk128(hlo[q], hhi[q]) : (u128)0;
+            const uint64_t nz = __ballot(c != 0);
+            if (lane == 0) ctl[1 + w] = __popcll(nz);
+            __syncthreads();
+            int before = done;
+            for (int i = 0; i < NW; i++) {
+                const int m = ctl[1 + i];
+                before += i < w ? m : 0;
+                done += m;
+            }
+            if (c != 0) {
+                const int64_t o = at + before + __popcll(nz & lanemask_lt());
+                uint64_t key;
+                if (X) {
+                    const uint32_t s = A.str[q / A.nsets], C = A.cset[cv * A.nsets + q % A.nsets];
+                    const uint32_t b = beta_of(s, A.hlen);
+                    if (b > 1) {
+                        bool inexact = false;
+                        c = Cnt<u128>::div(c, b, inexact);
+                        if (inexact) atomicOr(A.err, E16_BETA);
+                    }
+                    key = (uint64_t)s << 16 | C;
+                } else {
+                    key = (uint64_t)A.cset[cv * A.nsets + q / A.nstr] << A.hlen | A.str[q % A.nstr];
+                }
+                A.okey[o] = key;
+                A.ocnt[o] = c;
+            }
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) A.vcount[v] = done;
+    }
+}
+
+// the vertices' records from where their bounds put them to where their counts do
+__global__ __launch_bounds__(BLOCK) void k16_agg_pack(const int64_t *toff, int64_t v0, int64_t v1, const int64_t *vcount,
+                                                      const uint64_t *pos, const uint64_t *ikey, const u128 *icnt,
+                                                      uint64_t *okey, u128 *ocnt)
+{
+    const int64_t v = v0 + (int64_t)blockIdx.x * WPB + threadIdx.x / WAVE;
+    if (v >= v1) return;
+    const int64_t from = toff[v] - toff[v0], to = (int64_t)pos[v - v0], cnt = vcount[v];
+    for (int64_t i = lane_id(); i < cnt; i += WAVE) {
+        okey[to + i] = ikey[from + i];
+        ocnt[to + i] = icnt[from + i];
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Exclusive scan of uint64 arrays (blocks of SCAN_TILE, then the block sums)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BLOCK) void k16_scan_tiles(uint64_t *d, int64_t N, uint64_t *tile_sums)
@@ -968,6 +1314,7 @@ struct Lev16 {
 struct scc16_table {
     int k = 0, rooting = SCC_ROOT_ZERO;
     int64_t n = 0, nnz_g = 0, chunk_terms = DEFAULT_CHUNK_TERMS;
+    bool aggregate = true;          // where it can be (build_pass)
     const int64_t *row_ptr = nullptr;
     const int32_t *col_idx = nullptr;
     const uint8_t *colors = nullptr;
@@ -1092,6 +1439,28 @@ struct Timer {
     }
 };
 
+// The strings of the rooted treelets on h <= AGG_K nodes, ascending: w(T'') in front of
+// T''s string wherever it is not smaller than its first word
+const std::vector<uint32_t> &tree_strings(int h)
+{
+    static const std::vector<std::vector<uint32_t>> all = [] {
+        std::vector<std::vector<uint32_t>> t(AGG_K + 1);
+        t[1] = {0};
+        for (int n = 2; n <= AGG_K; n++) {
+            for (int p = 1; p < n; p++)
+                for (uint32_t a : t[p])
+                    for (uint32_t b : t[n - p]) {
+                        const int lp = 2 * (p - 1), lw = 2 * (n - p), lc = first_word_len(a, lp);
+                        const uint32_t w = 1u << (lw - 1) | b << 1;
+                        if (word_not_smaller(w, lw, lc ? a >> (lp - lc) : 0u, lc)) t[n].push_back(w << lp | a);
+                    }
+            std::sort(t[n].begin(), t[n].end());
+        }
+        return t;
+    }();
+    return all[h];
+}
+
 // One level: x_level = 1 builds X_h from X_1..X_{h-1} and S_1..S_{h-1}
 // (Eq. (1)); x_level = 0 builds S_h from X_h. `own` receives the result; its
 // arrays are held by the table (X) or by `hold` (S, freed after the build).
@@ -1118,6 +1487,15 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
 
     NbrArgs<CT> NA{};
     CombArgs<CT> CA{};
+    // outputs of a vertex that fit a workgroup's LDS (every level of k <= 10): the terms
+    // are aggregated as they are formed. A caller's chunk size asks for the sorted form.
+    const std::vector<uint32_t> *str = k <= AGG_K ? &tree_strings(h) : nullptr;
+    int64_t sets = 1, most = AGG_MAX + 1;
+    for (int i = 0, m = x_level ? h - 1 : h; i < m; i++) sets = sets * (k - 1 - i) / (i + 1);   // binom(k-1, m)
+    if (str) most = (int64_t)str->size() * sets;
+    const bool agg = std::is_same<CT, u128>::value && T->aggregate && most <= AGG_MAX;
+    AggArgs GA{};
+    unsigned long long *cursor = nullptr;
     if (x_level) {
         CA.colors = T->colors;
         CA.h = h;
@@ -1132,7 +1510,7 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
         CA.tnum = (int64_t *)toff;
         CA.v0 = 0;
         CA.v1 = n;
-        hipLaunchKernelGGL((k16_comb<false, CT>), dim3(wave_grid(n)), dim3(BLOCK), 0, T->stream, CA);
+        if (!agg) hipLaunchKernelGGL((k16_comb<false, CT>), dim3(wave_grid(n)), dim3(BLOCK), 0, T->stream, CA);
     } else {
         NA.row_ptr = T->row_ptr;
         NA.col_idx = T->col_idx;
@@ -1143,8 +1521,25 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
         NA.tnum = (int64_t *)toff;
         NA.v0 = 0;
         NA.v1 = n;
-        hipLaunchKernelGGL((k16_nbr<false, CT>), dim3(wave_grid(n)), dim3(BLOCK), 0, T->stream, NA);
+        if (!agg) hipLaunchKernelGGL((k16_nbr<false, CT>), dim3(wave_grid(n)), dim3(BLOCK), 0, T->stream, NA);
     }
+    if constexpr (std::is_same<CT, u128>::value)
+        if (agg && n > 0) {
+            const size_t ranks = ((size_t)1 << (2 * (h - 1))) * 2, cr = ((size_t)k << k) * 2, cs = (size_t)k * sets * 2;
+            uint32_t *ds = (uint32_t *)sc.get(str->size() * 4);
+            uint16_t *dr = (uint16_t *)sc.get(ranks + cr + cs);
+            if (!ds || !dr) return set_error(SCC_ENOMEM, "level %d ranks", h);
+            HIP_TRY(hipMemcpyAsync(ds, str->data(), str->size() * 4, hipMemcpyHostToDevice, T->stream));
+            GA.nout = (int)most; GA.nsets = (int)sets; GA.nstr = (int)str->size();
+            GA.str = ds; GA.rank = dr; GA.crank = dr + ranks / 2; GA.cset = dr + (ranks + cr) / 2;
+            GA.KB = KB; GA.k = k; GA.hlen = 2 * (h - 1); GA.h = h; GA.zero_rooting = T->rooting == SCC_ROOT_ZERO;
+            GA.colors = T->colors; GA.toff = (const int64_t *)toff; GA.err = err; GA.N = NA; GA.C = CA;
+            const auto kr = x_level ? k16_agg_ranks<true> : k16_agg_ranks<false>;
+            hipLaunchKernelGGL(kr, dim3(blocks_for(std::max<int64_t>((int64_t)k << k, GA.nstr), 256)), dim3(256), 0, T->stream, GA,
+                               dr, dr + ranks / 2, dr + (ranks + cr) / 2);
+            const auto kb = x_level ? k16_agg_bound<true> : k16_agg_bound<false>;
+            hipLaunchKernelGGL(kb, dim3(blocks_for(n, 256)), dim3(256), 0, T->stream, GA, n, most, (int64_t *)toff);
+        }
     HIP_TRY(hipGetLastError());
     scc_status s = scan_u64(T, toff, n + 1, word);
     if (s) return s;
@@ -1162,7 +1557,7 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
     for (int64_t v = 0; v < n;) {
         int64_t v1 = v + 1;
         while (v1 < n && v1 - v < vmax && ht[(size_t)v1 + 1] - ht[(size_t)v] <= T->chunk_terms) v1++;
-        const int64_t N = ht[(size_t)v1] - ht[(size_t)v];
+        const int64_t N = ht[(size_t)v1] - ht[(size_t)v];   // (aggregated: bounds on the outputs instead of terms)
         if (N > MAX_CHUNK_TERMS)
             return set_error(SCC_ENOMEM, "level %d: vertex %lld forms %lld terms (more than 2^31 - 1)", h,
                              (long long)v, (long long)N);
@@ -1178,7 +1573,57 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
     std::vector<std::pair<uint64_t *, CT *>> parts;
     std::vector<int64_t> part_n;
     Scratch parts_mem(T);
-    if (nmax > 0) {
+    if constexpr (std::is_same<CT, u128>::value) if (agg) {
+        terms_out = 0;
+        if (nmax > 0) {
+            int64_t vmost = 0;
+            for (auto &c : chunks) vmost = std::max(vmost, c.second - c.first);
+            uint64_t *tk = (uint64_t *)sc.get((size_t)nmax * 8), *pos = (uint64_t *)sc.get((size_t)vmost * 8);
+            u128 *tc = (u128 *)sc.get((size_t)nmax * 16);
+            cursor = (unsigned long long *)sc.get(64);
+            if (!tk || !pos || !tc || !cursor) return set_error(SCC_ENOMEM, "level %d outputs", h);
+            const int nw = GA.nout <= AGG_FEW ? 4 : 16;
+            const auto ka = nw == 4 ? (x_level ? k16_agg<true, 4> : k16_agg<false, 4>) : (x_level ? k16_agg<true, 16> : k16_agg<false, 16>);
+            const size_t lds = agg_lds(nw, GA.nout);
+            (void)hipFuncSetAttribute((const void *)ka, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            int dev = 0, ncu = 256;
+            HIP_TRY(hipGetDevice(&dev));
+            HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+            HIP_TRY(hipMemsetAsync(cursor, 0, 64, T->stream));
+            GA.okey = tk; GA.ocnt = tc; GA.vcount = out.off; GA.cursor = cursor;
+            for (auto &c : chunks) {
+                const int64_t v0 = c.first, v1 = c.second;
+                GA.v0 = v0; GA.v1 = v1;
+                HIP_TRY(hipMemsetAsync(cursor, 0, 8, T->stream));
+                const int64_t grid = std::min<int64_t>(v1 - v0, (nw == 4 ? 4 : 1) * ncu);
+                // (sixteen waves: single vertices, which even out better; 81 against 88 ms)
+                GA.turn = nw == 4 ? (int)std::clamp<int64_t>((v1 - v0) / (grid * 8), 1, 16) : 1;
+                hipLaunchKernelGGL(ka, dim3((unsigned)grid), dim3(nw * WAVE), lds,
+                                   T->stream, GA);
+                HIP_TRY(hipGetLastError());
+                HIP_TRY(hipMemcpyAsync(pos, out.off + v0, (size_t)(v1 - v0) * 8, hipMemcpyDeviceToDevice, T->stream));
+                s = scan_u64(T, pos, v1 - v0, word);
+                if (s) return s;
+                uint64_t U = 0;
+                unsigned long long cur[2];
+                HIP_TRY(hipMemcpyAsync(&U, word, 8, hipMemcpyDeviceToHost, T->stream));
+                HIP_TRY(hipMemcpyAsync(cur, cursor, 16, hipMemcpyDeviceToHost, T->stream));
+                HIP_TRY(hipStreamSynchronize(T->stream));
+                terms_out = (int64_t)cur[1];
+                const bool only = chunks.size() == 1;   // straight into the level's arrays
+                uint64_t *ok = (uint64_t *)(only ? keep((size_t)(U + 1) * 8) : parts_mem.get((size_t)(U + 1) * 8));
+                u128 *oc = (u128 *)(only ? keep((size_t)(U + 1) * 16) : parts_mem.get((size_t)(U + 1) * 16));
+                if (!ok || !oc) return set_error(SCC_ENOMEM, "level %d records", h);
+                hipLaunchKernelGGL(k16_agg_pack, dim3(blocks_for(v1 - v0, WPB)), dim3(BLOCK), 0, T->stream,
+                                   (const int64_t *)toff, v0, v1, (const int64_t *)out.off, pos, tk, tc, ok, oc);
+                HIP_TRY(hipGetLastError());
+                parts.push_back({ok, oc});
+                part_n.push_back((int64_t)U);
+                if (only) { out.key = ok; out.cnt = oc; }
+            }
+        }
+    }
+    if (nmax > 0 && !agg) {
         const int64_t nbs = (nmax + SORT_TILE - 1) / SORT_TILE;
         uint64_t *ka = (uint64_t *)sc.get((size_t)nmax * 8), *kb = (uint64_t *)sc.get((size_t)nmax * 8);
         uint32_t *pa = (uint32_t *)sc.get((size_t)nmax * 4), *pb = (uint32_t *)sc.get((size_t)nmax * 4);
@@ -1228,11 +1673,14 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
     int64_t nnz = 0;
     for (int64_t u : part_n) nnz += u;
     out.nnz = nnz;
-    out.key = (uint64_t *)keep((size_t)nnz * 8);
-    out.cnt = keep((size_t)nnz * CB);
+    const bool placed = agg && parts.size() == 1;
+    if (!placed) {
+        out.key = (uint64_t *)keep((size_t)nnz * 8);
+        out.cnt = keep((size_t)nnz * CB);
+    }
     if (!out.key || !out.cnt) return set_error(SCC_ENOMEM, "level %d records", h);
     int64_t at = 0;
-    for (size_t i = 0; i < parts.size(); i++) {
+    for (size_t i = 0; i < parts.size() && !placed; i++) {
         if (part_n[i] == 0) continue;
         HIP_TRY(hipMemcpyAsync(out.key + at, parts[i].first, (size_t)part_n[i] * 8, hipMemcpyDeviceToDevice, T->stream));
         HIP_TRY(hipMemcpyAsync((CT *)out.cnt + at, parts[i].second, (size_t)part_n[i] * CB, hipMemcpyDeviceToDevice,
@@ -1338,6 +1786,7 @@ static scc_status build16(const scc_csr *g, const uint8_t *colors, int k, const 
     T->n = g->n;
     T->nnz_g = g->nnz;
     T->chunk_terms = o.chunk_terms ? std::min(o.chunk_terms, MAX_CHUNK_TERMS) : DEFAULT_CHUNK_TERMS;
+    T->aggregate = !o.chunk_terms;
     T->stream = (hipStream_t)o.stream;
     T->mem.alloc = o.alloc;
     T->mem.stream = T->stream;

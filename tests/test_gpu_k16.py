@@ -87,6 +87,22 @@ def test_k9_to_k12_sparse_graphs(k, n, extra, seed, rooting):
     assert ot.total() > 0
 
 
+@pytest.mark.parametrize("k,n,m", [(9, 700, 1000), (10, 400, 500), (11, 300, 360), (12, 300, 300)])
+@pytest.mark.parametrize("rooting", [O.ROOT_ZERO, O.ROOT_ALL])
+def test_aggregated_equals_sorted(k, n, m, rooting):
+    # levels aggregated in LDS by 4 and by 16 waves (every level at k <= 10, some at
+    # k = 11, none at 12) against the terms sorted a chunk at a time, a hub included
+    g = gg.chung_lu(n, m, 2.3, 60, seed=50 + k)
+    colors = gg.colors(g.n, k, seed=k)
+    dg = scc.DeviceGraph.from_graph(g)
+    a = scc.Table16(dg, colors, k, rooting=rooting)
+    b = scc.Table16(dg, colors, k, rooting=rooting, chunk_terms=1 << 22)
+    _tables_equal(a, b, k, f"k={k}")
+    ia, ib = a.info(), b.info()
+    assert list(ia.terms) == list(ib.terms) and list(ia.nbr_terms) == list(ib.nbr_terms)
+    assert list(ia.sum_nnz) == list(ib.sum_nnz)
+
+
 def test_k10_hub():
     # a hub of degree 40 inside a sparse graph: long neighbour sums at the hub
     g0 = _sparse_graph(70, 10, 7)
