@@ -596,8 +596,12 @@ __global__ __launch_bounds__(BLOCK) void k16_comb(CombArgs<CT> A)
 // and r_j binom(k-1, j) of S_j (4140 at k = 10). Where a 128-bit count for each of these
 // fits the LDS, a workgroup adds a vertex's terms to them as they are formed, by the rank
 // of the shape's string and of the colour set, and writes the non-zero ones in order: the
-// ranks run as the sort keys do. Four waves a workgroup where a CU holds four of these,
-// else sixteen, one to a CU.
+// ranks run as the sort keys do. One wave takes a vertex where its totals are few, four
+// where a CU holds four such groups, else sixteen, one group to a CU. The build takes 130
+// ms now, 81 of them in X_6 to X_9 by sixteen waves: the chain of loads and LDS additions
+// of a split's few rounds. A hash table of the keys instead of the ranks took 250 ms there
+// (1600 vector instructions per 64 terms, for probing), a round per colour subset instead
+// of per pair of own entry and subset 176 ms.
 struct AggArgs {
     int64_t v0, v1;
     int KB, k, h, hlen;         // (S_j: h = j)
@@ -617,7 +621,7 @@ struct AggArgs {
     CombArgs<u128> C;           // X_h
 };
 constexpr int AGG_MAX = 4200;                    // outputs of a vertex, at most
-constexpr int AGG_FEW = 1280;                    // up to here four waves a workgroup
+constexpr int AGG_ONE = 256, AGG_FEW = 1280;     // up to here one, four waves a workgroup
 constexpr int AGG_K = 11;
 struct AggWave {                // a wave's part of the LDS
     uint32_t sp[WAVE], c1[WAVE], lc[WAVE], cp[WAVE], st[WAVE], ex[WAVE], xq[WAVE], pad[WAVE];
@@ -691,8 +695,10 @@ __global__ void __launch_bounds__(NW * WAVE) k16_agg(AggArgs A)
         return r;
     };
     const uint32_t full = (1u << A.k) - 1u;
+    uint64_t nterms = 0;   // of all the workgroup's vertices: one addition to the shared count
     // (thread 0) the next vertex of the turn's, and the turn after it, asked for ahead: a
-    // turn is several vertices, as the shared count takes about 20 ns each time
+    // turn is several vertices, as the shared count takes about 15 ns each time (65 536
+    // vertices one by one: 1.2 ms of the low levels' launches, now 0.2)
     const unsigned long long nv = (unsigned long long)(A.v1 - A.v0);
     unsigned long long cur = 0, end = 0, next = 0;
     if (threadIdx.x == 0) next = atomicAdd(&A.cursor[0], (unsigned long long)A.turn);
@@ -716,7 +722,6 @@ __global__ void __launch_bounds__(NW * WAVE) k16_agg(AggArgs A)
         const int cv = A.colors[v];
         const uint16_t *crank = A.crank + ((size_t)cv << A.k);
         bool ovf = false;
-        uint64_t nterms = 0;
         // count c of shape string s with colours C
         auto add = [&](uint32_t s, uint32_t C, u128 c) {
             const uint32_t t = A.rank[s], r = crank[C];
@@ -877,8 +882,6 @@ __global__ void __launch_bounds__(NW * WAVE) k16_agg(AggArgs A)
         }
         __syncthreads();
         if (ovf) atomicOr(A.err, E16_OVERFLOW);
-        nterms = wave_sum64(nterms);
-        if (lane == 0 && nterms) atomicAdd(&A.cursor[1], (unsigned long long)nterms);
         // the non-zero outputs in order
         int done = 0;
         for (int q0 = 0; q0 < A.nout; q0 += NT) {
@@ -915,6 +918,8 @@ __global__ void __launch_bounds__(NW * WAVE) k16_agg(AggArgs A)
         }
         if (threadIdx.x == 0) A.vcount[v] = done;
     }
+    nterms = wave_sum64(nterms);
+    if (lane == 0 && nterms) atomicAdd(&A.cursor[1], (unsigned long long)nterms);
 }
 
 // the vertices' records from where their bounds put them to where their counts do
@@ -1582,8 +1587,10 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
             u128 *tc = (u128 *)sc.get((size_t)nmax * 16);
             cursor = (unsigned long long *)sc.get(64);
             if (!tk || !pos || !tc || !cursor) return set_error(SCC_ENOMEM, "level %d outputs", h);
-            const int nw = GA.nout <= AGG_FEW ? 4 : 16;
-            const auto ka = nw == 4 ? (x_level ? k16_agg<true, 4> : k16_agg<false, 4>) : (x_level ? k16_agg<true, 16> : k16_agg<false, 16>);
+            const int nw = GA.nout <= AGG_ONE ? 1 : GA.nout <= AGG_FEW ? 4 : 16, per = nw == 1 ? 12 : nw == 4 ? 4 : 1;
+            const auto ka = nw == 1 ? (x_level ? k16_agg<true, 1> : k16_agg<false, 1>)
+                          : nw == 4 ? (x_level ? k16_agg<true, 4> : k16_agg<false, 4>)
+                                    : (x_level ? k16_agg<true, 16> : k16_agg<false, 16>);
             const size_t lds = agg_lds(nw, GA.nout);
             (void)hipFuncSetAttribute((const void *)ka, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             int dev = 0, ncu = 256;
@@ -1595,9 +1602,9 @@ scc_status build_pass(scc16_table *T, int x_level, int h, const Lev16 *S, Lev16 
                 const int64_t v0 = c.first, v1 = c.second;
                 GA.v0 = v0; GA.v1 = v1;
                 HIP_TRY(hipMemsetAsync(cursor, 0, 8, T->stream));
-                const int64_t grid = std::min<int64_t>(v1 - v0, (nw == 4 ? 4 : 1) * ncu);
-                // (sixteen waves: single vertices, which even out better; 81 against 88 ms)
-                GA.turn = nw == 4 ? (int)std::clamp<int64_t>((v1 - v0) / (grid * 8), 1, 16) : 1;
+                const int64_t grid = std::min<int64_t>(v1 - v0, per * ncu);
+                // (sixteen waves: single vertices, which even out better: 81 against 88 ms)
+                GA.turn = nw < 16 ? (int)std::clamp<int64_t>((v1 - v0) / (grid * 2), 1, 16) : 1;
                 hipLaunchKernelGGL(ka, dim3((unsigned)grid), dim3(nw * WAVE), lds,
                                    T->stream, GA);
                 HIP_TRY(hipGetLastError());
