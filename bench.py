@@ -22,6 +22,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -411,7 +412,7 @@ def run_batching(a, emit=True):
     out = {
         "metric": "DP table build s & colorful-treelet samples/sec, batched/served vs plain",
         "value": len(inst) / b_s,
-        "unit": "tables built per second (the batch scheduler: instances of at least 2^21 CSR entries on the "
+        "unit": "tables built per second (the batch scheduler: instances of at least 2^13 CSR entries on the "
                 "level kernels, the rest in one persistent launch)",
         "n_gpus": 1, "steps": a.steps, "warmup": 1, "ms_per_step": b_s * 1e3, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "u64/u128", "data": "synthetic",
@@ -587,8 +588,9 @@ def run_k16(a):
     dt = (time.perf_counter() - t0) / a.steps
     inf = infos[-1]
     prof = profile_fields16("k16_k10_hbm_traffic.txt")
-    sort_ms = sum(inf.sort_ms[h] for h in range(1, k + 1))
-    sort_b = sum(inf.sort_bytes[h] for h in range(1, k + 1))
+    sort_ms = sum(inf.sort_ms[h] for h in range(1, k + 1))   # levels too wide for the LDS only
+    moved = 24.0 * sum(inf.nnz[h] + inf.sum_nnz[h] + inf.nbr_terms[h] + (h - 1) * (inf.nnz[h - 1] + inf.sum_nnz[h - 1])
+                       for h in range(1, k + 1))
     print(f"# timed {a.steps} builds: {dt * 1e3:.1f} ms/build, sorts {sort_ms:.1f} ms", file=sys.stderr, flush=True)
     out = {
         "metric": "DP table build s & colorful-treelet samples/sec, batched/served vs plain",
@@ -605,15 +607,12 @@ def run_k16(a):
         "terms": [int(inf.terms[h]) for h in range(1, k + 1)],
         "nbr_terms": [int(inf.nbr_terms[h]) for h in range(1, k + 1)],
         "table_bytes": int(inf.bytes), "peak_bytes": int(inf.peak_bytes),
-        "roofline": {"bound": "hbm", "achieved": sort_b / (sort_ms * 1e6) if sort_ms > 0 else None,
-                     "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": sort_b / (sort_ms * 1e6) / HBM_PEAK_GBS if sort_ms > 0 else None,
-                     "traffic": float(prof["sort_traffic_bytes_per_build"]) if prof else None,
-                     "traffic_gbs": (float(prof["sort_traffic_bytes_per_build"]) / (sort_ms * 1e6)
-                                     if prof and sort_ms > 0 else None),
-                     "traffic_unit": "HBM bytes per build of k16_hist + k16_scatter from TCC_EA0 requests",
-                     "kernel": "radix sort of the terms (k16_hist, k16_scatter and their scans): 32 B per "
-                               "element and pass", "bytes_per_build": sort_b, "ms_per_build": sort_ms},
+        "roofline": {"bound": "latency and LDS additions (the terms never reach HBM)", "achieved": moved / (dt * 1e9),
+                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": moved / (dt * 1e9) / HBM_PEAK_GBS,
+                     "kernel": "the whole build: 24 B per stored count and sum written, per neighbour entry and per "
+                               "own and sum entry of each level read", "bytes_per_build": moved,
+                     "traffic": float(prof["traffic_bytes_per_build"]) if prof else None,
+                     "sort_ms": sort_ms, "terms_per_s": sum(inf.terms[h] + inf.nbr_terms[h] for h in range(1, k + 1)) / dt},
     }
     if base is not None:
         out["cpu_baseline"] = base
@@ -728,6 +727,14 @@ def rooflines(tab, infos, k, samp_ms, ns, prof):
     the sampler. Bytes are algorithmic (from the stored record lengths), times
     the HIP-event durations of the timed builds (mean over steps)."""
     gb = tab.gather_bytes()
+    # A dense level's records (level 2, and levels after one with at least half its possible
+    # counts) are read without keys and only where the set lacks the row's colour: 8 of 10
+    # bytes, (k - h) / (k - 1) of the sets, (k - 1) / k of the neighbours.
+    rooted = (0, 1, 1, 2, 4, 9, 20, 48, 115)
+    inf = infos[-1]
+    for h in range(2, k):
+        if h == 2 or inf.nnz[h - 1] >= 0.5 * inf.n * rooted[h - 1] * math.comb(k - 1, h - 2):
+            gb[h] *= 0.8 * (k - h) / k
     cb, tb = tab.combine_bytes()
     mean = lambda f: sum(f(x) for x in infos) / len(infos)
     g_ms = mean(lambda x: sum(x.gather_ms[h] for h in range(2, k)))
@@ -748,14 +755,14 @@ def rooflines(tab, infos, k, samp_ms, ns, prof):
             out["traffic_frac"] = out["traffic_gbs"] / HBM_PEAK_GBS
         return out
 
-    join = entry(j_bytes, j_ms, "DP join: k_gather1, k_gather*, k_hub_prepare, k_combine*, k_words, scans, k_pack, "
+    join = entry(j_bytes, j_ms, "DP join: k_gather1, k_dgather*, k_gather*, k_row_bounds, k_dcombine, k_combine*, scans, k_pack, "
                  "k_totals and scans (every level of the build plus the level-k totals)", "traffic_bytes_per_build")
     join["traffic_unit"] = "HBM bytes per build from TCC_EA0 read requests by size (32/64/128 B) and write requests"
     parts = {
-        "gather": entry(g_bytes, g_ms, "neighbour-sum gather of levels 2..k-1 (k_gather_group, k_gather_list, "
-                        "k_gather, k_gather_wide, k_gather_hub, k_hub_prepare)", "gather_traffic_bytes_per_build"),
-        "combine": entry(c_bytes, c_ms, "combine of levels 2..k with compaction and packing (k_combine*, "
-                         "k_combine_list, k_combine_wide, k_words, scans, k_pack)", "combine_traffic_bytes_per_build"),
+        "gather": entry(g_bytes, g_ms, "neighbour-sum gather of levels 2..k-1 (k_row_bounds, k_dgather_row, "
+                        "k_dgather_group, k_dgather_hub; k_gather* from sparse records)", "gather_traffic_bytes_per_build"),
+        "combine": entry(c_bytes, c_ms, "combine of levels 2..k with compaction and packing (k_dcombine, "
+                         "k_combine*, scans, k_pack)", "combine_traffic_bytes_per_build"),
     }
     sp = {"bound": "hbm random access", "samples_per_s": ns / (samp_ms / 1e3) if samp_ms > 0 else 0.0,
           "ms_per_launch": samp_ms, "kernel": "k_sample"}
@@ -966,11 +973,11 @@ def _short_kernel(name):
 
 def _first_build(names):
     """Indices of the first table build: from its first kernel to the last one before
-    the first sampling call's preparation (per-edge colours, hub running sums built
-    apart from the build) or, without one, before the first k_sample."""
+    the first sampling call's preparation (vertex words, hub running sums built apart
+    from the build) or, without one, before the first k_sample."""
     start = next(i for i, nm in enumerate(names) if nm in ("k_row_lists", "k_validate_rows"))
-    prep = ("k_sample", "k_edge_colours", "k_hub_info", "k_hub_index", "k_hubpre_chunk")
-    end = next(i for i, nm in enumerate(names) if i > start and nm in prep)
+    prep = ("k_sample", "k_vertex_info", "k_hub_info", "k_hub_index", "k_hubpre_chunk")
+    end = next(i for i, nm in enumerate(names) if i > start and nm.startswith(prep))
     return start, end
 
 
@@ -997,7 +1004,7 @@ def summarise_trace(path):
             print(f"| {nm} | {c} | {d / 1e6:.2f} | {100 * d / busy:.1f} |")
     print()
     for want in ("k_sample", "k_classify"):
-        ds = [dur(r) for r, nm in zip(rows, names) if nm == want]
+        ds = [dur(r) for r, nm in zip(rows, names) if nm.split("<")[0] == want]
         if ds:
             print(f"{want}: {len(ds)} calls, average {sum(ds) / len(ds) / 1e6:.3f} ms")
 
@@ -1038,9 +1045,10 @@ def summarise_counters(label, ns, dir_a, dir_b):
         return best
 
     def cls(nm):
-        if (nm.startswith("k_gather") and nm != "k_gather_bytes") or nm == "k_hub_prepare":
+        if (nm.startswith(("k_gather", "k_dgather")) and nm != "k_gather_bytes") or nm in (
+                "k_hub_prepare", "k_dhub_prepare", "k_row_bounds"):
             return "gather"
-        if nm.startswith("k_combine") or nm.startswith("k_pack") or nm == "k_words":
+        if nm.startswith(("k_combine", "k_dcombine", "k_pack", "k_dense_")):
             return "combine"
         return "other"
 
