@@ -903,13 +903,15 @@ __global__ void __launch_bounds__(WAVE) k_gather_hub(GatherArgs A, int chunk)
 // GW lanes hold a row's entries, R pairs each; a wave has 64 / GW groups,
 // which take a row each (short rows) or every (64/GW)-th neighbour of one row.
 // W128: some neighbour or row may need 128 bits.
-// The gather is bound by HBM reads: two or three waits for it a row, one after
-// another. At k = 8 (Chung-Lu, 4*10^6 vertices, 6*10^7 arcs) the sparse records of
-// levels 2..7 took 1.26 TB of reads and 250 ms a build, the dense ones take 95 ms; with
+// The gather is bound by HBM traffic. At k = 8 (Chung-Lu, 4*10^6 vertices, 6*10^7
+// edges) the dense records take 583 GB of reads, all of whole 128-byte lines, and 36 GB
+// of writes: 103 ms a build at 6.0 TB/s. The sparse records of levels 2..7 took 1.6 TB
+// and 259 ms. For 4*10^6 vertices and 3*10^7 edges: 250 and 95 ms; with
 // what the combine and the pack no longer do the build went from 418 to 237 ms (k = 6,
 // 10^6 vertices, 10^7 edges: 10.4 to 8.1 ms; k = 7, 5*10^5 and 5*10^6: 13.3 to 9.3 ms).
 // Whole lines copied to LDS, more neighbours in flight a wave, resident waves with
-// tables, sums stored in whole lines: none made levels 4 to 6 of k = 8 faster.
+// tables, sums stored in whole lines, the lanes' sets in the records' order: none made
+// levels 4 to 6 of k = 8 faster.
 // ---------------------------------------------------------------------------
 struct DGatherArgs {
     GraphView g;
