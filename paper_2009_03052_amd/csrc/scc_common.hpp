@@ -73,8 +73,8 @@ struct DevLut {
     // position, the colour sets D (size h-1, without the vertex's own colour) in the
     // order of setpos[h], and within a set the r_h shapes by rank:
     //   position = setpos[h][D] r_h + rank.
-    // Consecutive sets differ in one colour, so that the sets without a given colour,
-    // which are all that a neighbour of that colour reads, lie in few runs. plane[h] is
+    // The order keeps the sets without a given colour, which are all that a neighbour
+    // of that colour reads, in few runs or lines. plane[h] is
     // the record's words, W_h rounded up to whole 64-byte lines.
     uint8_t setpos[SCC_KMAX + 1][128];
     int plane[SCC_KMAX + 2];
