@@ -904,14 +904,15 @@ __global__ void __launch_bounds__(WAVE) k_gather_hub(GatherArgs A, int chunk)
 // which take a row each (short rows) or every (64/GW)-th neighbour of one row.
 // W128: some neighbour or row may need 128 bits.
 // The gather is bound by HBM traffic. At k = 8 (Chung-Lu, 4*10^6 vertices, 6*10^7
-// edges) the dense records take 583 GB of reads, all of whole 128-byte lines, and 36 GB
-// of writes: 103 ms a build at 6.0 TB/s. The sparse records of levels 2..7 took 1.6 TB
-// and 259 ms. For 4*10^6 vertices and 3*10^7 edges: 250 and 95 ms; with
-// what the combine and the pack no longer do the build went from 418 to 237 ms (k = 6,
-// 10^6 vertices, 10^7 edges: 10.4 to 8.1 ms; k = 7, 5*10^5 and 5*10^6: 13.3 to 9.3 ms).
+// edges) the dense records take 557 GB of reads, all of whole 128-byte lines, and 36 GB
+// of writes: 100 ms a build at 5.95 TB/s. The sparse records of levels 2..7 took 1.6 TB
+// and 259 ms. With what the combine and the pack no longer did when the records became
+// dense, the build went from 418 to 237 ms (k = 6, 10^6 vertices, 10^7 edges: 10.4 to
+// 8.1 ms; k = 7, 5*10^5 and 5*10^6: 13.3 to 9.3 ms).
 // Whole lines copied to LDS, more neighbours in flight a wave, resident waves with
 // tables, sums stored in whole lines, the lanes' sets in the records' order: none made
-// levels 4 to 6 of k = 8 faster.
+// levels 4 to 6 of k = 8 faster, as the requests already match the lines that hold the
+// needed counts; an order of the sets with fewer lines did (level 5 24.8 to 23.0 ms).
 // ---------------------------------------------------------------------------
 struct DGatherArgs {
     GraphView g;
